@@ -40,6 +40,16 @@ namespace lbm {
 
 constexpr int LMAX = 128;  // largest chunk height (rows) k_step marches (halo arrays in LDS)
 
+// Constants of the MRT collision: rates s of the energy (e), energy-square (eps),
+// energy-flux (q) and stress (n, 1/tau) moments over the squared row norms, h = 1
+// - s/2, and sigma / (1/s - 1/2) of the improved scheme.
+struct MrtDev {
+  double e, eS, sig_e;      // -s_e/36, 6 h_e/36
+  double p, pS, sig_eps;    // -s_eps/36, -6 h_eps/36
+  double qa, qaF, qd, qdF;  // s_q/6, (1 + h_q)/6, -s_q/12, 1/6 - h_q/12
+  double n, nxx, nxy;       // -s_n/4, h_n/2, h_n/4
+};
+
 // Per-lattice constants, prepared on the host.
 struct RunDev {
   int32_t nx, ny, pitch, eos;
@@ -48,23 +58,20 @@ struct RunDev {
   int64_t elems;            // elements of the lattice's population buffer
   int64_t off;              // element offset of this lattice in the population pool
   double RT, c1, c2;        // EOS constants (see EosConst)
-  double two_over_G, mG;    // 2/G and -G
+  // folded EOS constants: eA = 2 RT/G, eB = c2/RT, eC = 1/(3 RT) (see psi2_of)
+  double eA, eB, eC;
+  double mG12;              // -G/12: w(2) = 1/12 taken out of the force stencil
   double inv_tau;
   // forcing scheme in general form: u_eq = u + c_eq F/rho,
-  // F_a = w_a [3 Be e.F + Ce (9 (e.vf)(e.F) - 3 vf.F)], vf = u + c_f F/rho + sig F/psi^2
-  double c_eq, c_f, sig, Be, Ce;
-  // products used by the collision: w0 Ce, w1 Ce, w2 Ce and 3 w1 Be, 3 w2 Be
-  // (w0, w1, w2 = 4/9, 1/9, 1/36); om w0, om w1, om w2, 3 om w1, 3 om w2 and
-  // 1 - om with om = 1/tau
-  double wCe0, wCe1, wCe2, wBe3_1, wBe3_2;
-  double om_w0, om_w1, om_w2, om_3w1, om_3w2, om1;
+  // F_a = w_a [3 Be e.F + Ce (9 (e.vf)(e.F) - 3 vf.F)], vf = u + c_f F/rho + sig F/psi^2,
+  // written vf = u_eq + (c_d/rho + sig/psi^2) F with c_d = c_f - c_eq
+  double c_eq, c_d, sig, Ce;
+  // products used by the collision, om = 1/tau: 1 - om, om/2, om/9, om/3, Be/3
+  double om1, om_2, om_9, om_3, Be_3;
   double rho_ref;           // deviation reference density (0 for FP64 storage)
   int32_t run;
-  int32_t mrt;              // 1: multiple-relaxation-time collision (collide_mrt)
-  // MRT rates of the energy, energy-square and energy-flux moments (the others
-  // relax at inv_tau) and the improved scheme's sigma / (1/s - 1/2) for the
-  // energy and energy-square moments (sig above is the stress moments' value)
-  double s_e, s_eps, s_q, sig_e, sig_eps;
+  int32_t mrt;              // 1: multiple-relaxation-time collision (collide_mrt with m)
+  MrtDev m;
 };
 
 
@@ -109,12 +116,13 @@ template <typename S> struct Store;
 // the density they are evaluated at (FP64 for every storage type: the EOS and
 // psi stay FP64 in the reduced-precision forms).  kConserve: after the FP32
 // collision, restore the node's mass and momentum change exactly (see
-// conserve()).
+// conserve()).  kDev: values are deviations from w_a rho_ref.
 template <> struct Store<double> {
   using E = double;
   using R = double;
   using P = double;
   static constexpr bool kConserve = false;
+  static constexpr bool kDev = false;
   static __device__ __forceinline__ R ld(const E* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ void st(E* p, R v) { __builtin_nontemporal_store(v, p); }
   static __device__ __forceinline__ R round(R v) { return v; }
@@ -124,6 +132,7 @@ template <> struct Store<float> {
   using R = float;
   using P = double;
   static constexpr bool kConserve = true;
+  static constexpr bool kDev = true;
   static __device__ __forceinline__ R ld(const E* p) { return *p; }
   static __device__ __forceinline__ void st(E* p, R v) { *p = v; }
   static __device__ __forceinline__ R round(R v) { return v; }
@@ -133,6 +142,7 @@ template <> struct Store<f32s_f64a> {
   using R = double;
   using P = double;
   static constexpr bool kConserve = false;
+  static constexpr bool kDev = true;
   static __device__ __forceinline__ R ld(const E* p) { return double(__builtin_nontemporal_load(p)); }
   static __device__ __forceinline__ void st(E* p, R v) { __builtin_nontemporal_store(float(v), p); }
   static __device__ __forceinline__ R round(R v) { return double(float(v)); }
@@ -142,6 +152,7 @@ template <> struct Store<__half> {
   using R = float;
   using P = double;
   static constexpr bool kConserve = false;
+  static constexpr bool kDev = true;
   // The narrowing to FP16 takes its operand through an empty asm statement:
   // the backend otherwise folds it into the FMA that produced the operand (a
   // mixed-precision FMA with an FP16 result, one rounding instead of two) at
@@ -189,13 +200,16 @@ __device__ __forceinline__ bool index_ok(int64_t, int64_t) { return true; }
 __device__ constexpr double kW[9] = {4.0 / 9.0, 1.0 / 9.0, 1.0 / 9.0, 1.0 / 9.0, 1.0 / 9.0,
                                      1.0 / 36.0, 1.0 / 36.0, 1.0 / 36.0, 1.0 / 36.0};
 
-// Reciprocals: the hardware estimate refined by two Newton steps (FP64, about
-// 1 ulp), or the single-precision estimate (FP32 arithmetic paths, 1 ulp).
-// Arguments are positive normal numbers (or non-finite in a diverged state).
+// Reciprocals: the hardware estimate (relative error below 2^-24, measured over
+// 1e-9 .. 1e9) refined by one third-order step, r (1 + e + e^2) with e = 1 - x r
+// (FP64; the truncation e^3 is below 2^-72, so about 1 ulp; one operation less
+// than two Newton steps), or the single-precision estimate (FP32 arithmetic
+// paths, 1 ulp).  Arguments are positive normal numbers (or non-finite in a
+// diverged state).
 __device__ __forceinline__ double rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
@@ -250,29 +264,45 @@ __device__ __forceinline__ R sum9(const R (&s)[9]) {
   return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])) + s[8];
 }
 
-// psi^2 = 2 (p_EOS(rho) - rho/3) / G (Eq. 8 with Eq. 23 or Peng-Robinson), in
-// the type P.
-template <typename P>
-__device__ __forceinline__ P psi2_of(P rho, const RunDev& d) {
+// psi^2 = 2 (p_EOS(rho) - rho/3) / G (Eq. 8 with Eq. 23 or Peng-Robinson) with
+// the constants of the lattice folded into three: psi^2 = rho eA q, where
+//   Carnahan-Starling  q = (1 + e + e^2 - e^3)/(1 - e)^3 - eC - eB rho, e = b rho/4
+//   Peng-Robinson      q = 1/(1 - b) - eB rho/(1 + b(2 - b)) - eC over one reciprocal
+// (each operation takes one constant from a scalar register).
+__device__ __forceinline__ double psi2_of(double rho, const RunDev& d) {
 #pragma clang fp contract(off)
-  P p;
-  const P one = P(1);
+  double q;
   if (d.eos == 0) {
-    // rho RT (1 + e + e^2 - e^3)/(1 - e)^3 - c2 rho^2, e = b rho / 4
-    const P e = P(d.c1) * rho, m = one - e;
-    const P poly = fma(e, fma(e, one - e, one), one);
-    p = fma((rho * P(d.RT)) * poly, rcp((m * m) * m), -((P(d.c2) * rho) * rho));
+    const double e = d.c1 * rho, m = 1.0 - e;
+    const double poly = fma(e, fma(e, m, 1.0), 1.0);
+    q = fma(-d.eB, rho, fma(poly, rcp((m * m) * m), -d.eC));
   } else {
-    // rho RT/(1 - b) - c2 rho^2/(1 + b(2 - b)) over one common reciprocal
-    const P b = P(d.c1) * rho;
-    const P q1 = one - b, q2 = fma(b, P(2) - b, one);
-    p = fma(rho * P(d.RT), q2, -(((P(d.c2) * rho) * rho) * q1)) * rcp(q1 * q2);
+    const double b = d.c1 * rho;
+    const double q1 = 1.0 - b, q2 = fma(b, 2.0 - b, 1.0);
+    q = fma(fma(-(d.eB * rho), q1, q2), rcp(q1 * q2), -d.eC);
   }
-  return fma(rho, P(-1.0 / 3.0), p) * P(d.two_over_G);
+  return (rho * d.eA) * q;
 }
 
-// psi from psi^2 (the correctly rounded FP64 square root).
-__device__ __forceinline__ double psi_root(double x) { return sqrt(x); }
+// psi = sqrt(x) and 1/psi^2 from x = psi^2 by one hardware reciprocal square
+// root y (relative error below 2^-24): with e = 1 - x y^2, sqrt(x) = x y (1 +
+// e/2 + 3 e^2/8 + ...) and 1/sqrt(x) likewise, each to about 1 ulp; a last
+// residual step makes the root the correctly rounded one but for rare ties.
+// No scaling for subnormal or huge x and no special cases: a run whose x is not
+// a positive normal number has diverged (both results are NaN for x <= 0).
+struct PsiPair {
+  double psi, ip2;
+};
+__device__ __forceinline__ PsiPair psi_pair(double x) {
+#pragma clang fp contract(off)
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = fma(-g, y, 1.0);
+  const double t = e * fma(0.375, e, 0.5);
+  const double r = fma(y, t, y);   // 1/sqrt(x)
+  const double g1 = fma(g, t, g);  // sqrt(x)
+  return PsiPair{fma(fma(-g1, g1, x), 0.5 * y, g1), r * r};
+}
 
 __device__ __forceinline__ double pressure_of(double rho, const RunDev& d) {
   if (d.eos == 0) {
@@ -282,20 +312,28 @@ __device__ __forceinline__ double pressure_of(double rho, const RunDev& d) {
   return rho * d.RT / (1.0 - d.c1 * rho) - d.c2 * rho * rho / (1.0 + d.c1 * rho * (2.0 - d.c1 * rho));
 }
 
-// Interaction force of Eq. (3) from the 3x3 psi neighbourhood (row-major:
-// s = y-1, c = y, n = y+1; index 0 = x-1, 1 = x, 2 = x+1), w(1)=1/3, w(2)=1/12.
-template <typename P>
-__device__ __forceinline__ void force3x3(const P* rs, const P* rc, const P* rn, int i, P mG, P& Fx,
-                                         P& Fy) {
+// Interaction force of Eq. (3), w(1) = 1/3, w(2) = 1/12, with w(2) taken out of
+// the sums and the 3x3 psi neighbourhood summed by columns first: with U = 4
+// psi(y) + psi(y+1) + psi(y-1) and D = psi(y+1) - psi(y-1) of a column,
+//   F = (-G/12) psi (U(x+1) - U(x-1), 4 D(x) + D(x+1) + D(x-1)).
+// Only U and D of the neighbour columns cross lanes.
+__device__ __forceinline__ double col_u(double s, double c, double n) {
 #pragma clang fp contract(off)
-  const P w1 = P(1.0 / 3.0), w2 = P(1.0 / 12.0);
-  const P dNE = rn[i + 1] - rs[i - 1];   // psi(x+e5) - psi(x-e5)
-  const P dNW = rn[i - 1] - rs[i + 1];   // psi(x+e6) - psi(x-e6)
-  const P Sx = fma(w1, rc[i + 1] - rc[i - 1], w2 * (dNE - dNW));
-  const P Sy = fma(w1, rn[i] - rs[i], w2 * (dNE + dNW));
-  const P c = mG * rc[i];
-  Fx = c * Sx;
-  Fy = c * Sy;
+  return fma(4.0, c, n + s);
+}
+__device__ __forceinline__ void force_ud(double mG12, double psi, double Ul, double Ur, double Dl,
+                                         double D, double Dr, double& Fx, double& Fy) {
+#pragma clang fp contract(off)
+  const double c = mG12 * psi;
+  Fx = c * (Ur - Ul);
+  Fy = c * fma(4.0, D, Dl + Dr);
+}
+// The same from three psi rows (row-major: s = y-1, c = y, n = y+1; index i = x).
+__device__ __forceinline__ void force3x3(const double* rs, const double* rc, const double* rn, int i,
+                                         double mG12, double& Fx, double& Fy) {
+#pragma clang fp contract(off)
+  force_ud(mG12, rc[i], col_u(rs[i - 1], rc[i - 1], rn[i - 1]), col_u(rs[i + 1], rc[i + 1], rn[i + 1]),
+           rn[i - 1] - rs[i - 1], rn[i] - rs[i], rn[i + 1] - rs[i + 1], Fx, Fy);
 }
 
 // BGK collision with the forcing scheme in general form (see RunDev).
@@ -303,19 +341,17 @@ __device__ __forceinline__ void force3x3(const P* rs, const P* rc, const P* rn, 
 // For direction a the update is s_a + om (seq_a - s_a) + F_a with
 //   seq_a = w (drho + rho (3 e.u + 4.5 (e.u)^2 - 1.5 u.u))        (Eq. 2, deviation form)
 //   F_a   = w [3 B_e e.F + C_e (9 (e.v)(e.F) - 3 v.F)]             (Eq. 12)
-// The opposite direction (e -> -e) flips the odd terms only, so each pair is
-// evaluated once: om seq = om w X +- 3 om w rho e.u with X = drho + rho (4.5
-// (e.u)^2 - 1.5 u.u), F_a = C +- D, and s' = (1 - om) s + (P +- Q) with
-// P = om w X + C, Q = 3 om w rho e.u + D (the products of om and the weights
-// are per-lattice constants).
+// The even part of om seq + F is a quadratic form of e: with m = rho u_eq = j +
+// c_eq F and the symmetric tensor (both terms already times w1 = 1/9)
+//   T = om/2 m u + C_e v F,  S = T_xx + T_yy,
+// it is 4 base, base + T_xx, base + T_yy and (base + S +- T_xy)/4 with base =
+// om/9 drho - S/3 (1.5/4.5 = 3/9 = 1/3), and the odd part is q.e with q = om/3 m
+// + B_e/3 F (over 4 for the diagonals).  Each pair of opposite directions is
+// then s' = (1 - om) s + (P +- Q).  55 operations besides the moments and 1/rho,
+// against 85 with the per-pair products (e.u)^2 and (e.v)(e.F) evaluated apart.
 template <typename R>
-__device__ __forceinline__ void collide_pair(R& sa, R& sb, R eu, R eF, R ev, R omw, R omwr3, R wCe,
-                                             R wBe3, R rho, R drho, R usq, R vF3, R om1) {
+__device__ __forceinline__ void relax_pair(R& sa, R& sb, R P, R Q, R om1) {
 #pragma clang fp contract(off)
-  const R X = fma(rho, fma(R(4.5) * eu, eu, -usq), drho);
-  const R C = wCe * fma(R(9) * ev, eF, -vF3);
-  const R P = fma(omw, X, C);
-  const R Q = fma(omwr3, eu, wBe3 * eF);
   sa = fma(om1, sa, P + Q);
   sb = fma(om1, sb, P - Q);
 }
@@ -325,27 +361,26 @@ __device__ __forceinline__ void collide(R (&s)[9], R drho, R rho, R jx, R jy, R 
                                         R inv_psi2, const RunDev& d) {
 #pragma clang fp contract(off)
   const R inv_rho = rcp(rho);
-  const R ux = jx * inv_rho, uy = jy * inv_rho;
-  const R Fr_x = Fx * inv_rho, Fr_y = Fy * inv_rho;
-  const R wx = fma(R(d.c_eq), Fr_x, ux), wy = fma(R(d.c_eq), Fr_y, uy);
-  const R sg = R(d.sig) * inv_psi2;
-  const R vx = fma(sg, Fx, fma(R(d.c_f), Fr_x, ux)), vy = fma(sg, Fy, fma(R(d.c_f), Fr_y, uy));
-  const R om1 = R(d.om1);
-  const R usq = R(1.5) * fma(wx, wx, wy * wy);
-  const R vF3 = R(3) * fma(vx, Fx, vy * Fy);
-  const R omw1 = R(d.om_w1), omw2 = R(d.om_w2);
-  const R omwr3_1 = R(d.om_3w1) * rho, omwr3_2 = R(d.om_3w2) * rho;
-  const R wCe1 = R(d.wCe1), wBe3_1 = R(d.wBe3_1), wCe2 = R(d.wCe2), wBe3_2 = R(d.wBe3_2);
-  // rest direction: e = 0
-  s[0] = fma(om1, s[0], fma(R(d.om_w0), fma(rho, -usq, drho), R(d.wCe0) * -vF3));
+  const R mx = fma(R(d.c_eq), Fx, jx), my = fma(R(d.c_eq), Fy, jy);
+  const R wx = mx * inv_rho, wy = my * inv_rho;
+  const R k = fma(R(d.c_d), inv_rho, R(d.sig) * inv_psi2);
+  const R vx = fma(k, Fx, wx), vy = fma(k, Fy, wy);
+  const R om_2 = R(d.om_2), Ce = R(d.Ce), om1 = R(d.om1);
+  const R ax = om_2 * mx, ay = om_2 * my, bx = Ce * Fx, by = Ce * Fy;
+  const R Txx = fma(ax, wx, bx * vx), Tyy = fma(ay, wy, by * vy);
+  const R Txy = fma(ax, wy, fma(ay, wx, fma(bx, vy, by * vx)));
+  const R S = Txx + Tyy;
+  const R base = fma(R(-1.0 / 3.0), S, R(d.om_9) * drho);
+  const R om_3 = R(d.om_3), Be_3 = R(d.Be_3);
+  const R qx = fma(om_3, mx, Be_3 * Fx), qy = fma(om_3, my, Be_3 * Fy);
+  const R D = R(0.25) * (base + S);
+  s[0] = fma(R(4), base, om1 * s[0]);
   // axis pairs (e1, e3 = -e1), (e2, e4 = -e2)
-  collide_pair(s[1], s[3], wx, Fx, vx, omw1, omwr3_1, wCe1, wBe3_1, rho, drho, usq, vF3, om1);
-  collide_pair(s[2], s[4], wy, Fy, vy, omw1, omwr3_1, wCe1, wBe3_1, rho, drho, usq, vF3, om1);
+  relax_pair(s[1], s[3], base + Txx, qx, om1);
+  relax_pair(s[2], s[4], base + Tyy, qy, om1);
   // diagonal pairs (e5 = (1,1), e7 = -e5), (e6 = (-1,1), e8 = -e6)
-  collide_pair(s[5], s[7], wx + wy, Fx + Fy, vx + vy, omw2, omwr3_2, wCe2, wBe3_2, rho, drho, usq,
-               vF3, om1);
-  collide_pair(s[6], s[8], wy - wx, Fy - Fx, vy - vx, omw2, omwr3_2, wCe2, wBe3_2, rho, drho, usq,
-               vF3, om1);
+  relax_pair(s[5], s[7], fma(R(0.25), Txy, D), R(0.25) * (qx + qy), om1);
+  relax_pair(s[6], s[8], fma(R(-0.25), Txy, D), R(0.25) * (qy - qx), om1);
 }
 
 // Multiple-relaxation-time collision with the improved forcing scheme, on the
@@ -362,58 +397,48 @@ __device__ __forceinline__ void collide(R (&s)[9], R drho, R rho, R jx, R jy, R 
 // momentum rate gives this).  In deviation storage the moments of w rho_ref,
 // rho_ref (1, -2, 1, 0, ...), are taken out of rho, e and eps.  With every rate
 // 1/tau this is the BGK update of collide() up to rounding.
+//
+// Only the changes of the moments go through the inverse transform, added to
+// the populations as they are: with m = j + F/2 = rho v the changes over the
+// row norms are r1 (e), r2 (eps), r7 (p_xx), r8 (p_xy), and the j and q changes
+// enter the axis directions as ox, oy and the diagonal ones as X +- Y (per-lattice
+// constants hold the rates over the norms, see MrtDev).
 template <typename R>
 __device__ __forceinline__ void collide_mrt(R (&s)[9], R drho, R rho, R jx, R jy, R Fx, R Fy,
                                             R inv_psi2, const RunDev& d) {
 #pragma clang fp contract(off)
+  const MrtDev& k = d.m;
   const R inv_rho = rcp(rho);
-  const R vx = fma(R(0.5) * Fx, inv_rho, jx * inv_rho), vy = fma(R(0.5) * Fy, inv_rho, jy * inv_rho);
-  const R v2 = fma(vx, vx, vy * vy), vF = fma(vx, Fx, vy * Fy);
+  const R mx = fma(R(0.5), Fx, jx), my = fma(R(0.5), Fy, jy);
+  const R vx = mx * inv_rho, vy = my * inv_rho;
+  const R w = fma(mx, vx, my * vy), vF = fma(vx, Fx, vy * Fy);  // rho |v|^2, v.F
   const R FF = fma(Fx, Fx, Fy * Fy) * inv_psi2;
-  // moments of the stored values
   const R ax = s[1] + s[3], ay = s[2] + s[4], a = ax + ay;
-  const R dg = (s[5] + s[7]) + (s[6] + s[8]);
+  const R p57 = s[5] + s[7], p68 = s[6] + s[8], dg = p57 + p68;
   const R e = fma(R(-4), s[0], fma(R(2), dg, -a));
   const R ep = fma(R(4), s[0], fma(R(-2), a, dg));
-  const R qx = fma(R(-2), s[1] - s[3], (s[5] - s[7]) + (s[8] - s[6]));
-  const R qy = fma(R(-2), s[2] - s[4], (s[5] - s[7]) + (s[6] - s[8]));
-  const R pxx = ax - ay;
-  const R pxy = (s[5] + s[7]) - (s[6] + s[8]);
-  // equilibria (deviation form: rho_ref (1, -2, 1) removed from rho, e, eps)
-  const R r3v2 = R(3) * rho * v2;
-  const R e_eq = fma(R(-2), drho, r3v2), ep_eq = drho - r3v2;
-  const R se = R(d.s_e), sp = R(d.s_eps), sq = R(d.s_q), sn = R(d.inv_tau);
-  const R S_e = R(6) * fma(R(d.sig_e), FF, vF);
-  const R S_ep = R(-6) * fma(R(d.sig_eps), FF, vF);
-  const R sgn = R(2) * R(d.sig) * inv_psi2;
-  const R S_xx = fma(R(2), fma(vx, Fx, -(vy * Fy)), sgn * fma(Fx, Fx, -(Fy * Fy)));
-  const R S_xy = fma(vx, Fy, vy * Fx) + sgn * (Fx * Fy);
-  // m' = m - s (m - m_eq) + (1 - s/2) S
-  const R e1 = fma(-se, e - e_eq, e) + (R(1) - R(0.5) * se) * S_e;
-  const R ep1 = fma(-sp, ep - ep_eq, ep) + (R(1) - R(0.5) * sp) * S_ep;
-  const R hq = R(1) - R(0.5) * sq;
-  const R qx1 = fma(-sq, fma(rho, vx, qx), qx) - hq * Fx;
-  const R qy1 = fma(-sq, fma(rho, vy, qy), qy) - hq * Fy;
-  const R hn = R(1) - R(0.5) * sn;
-  const R pxx1 = fma(-sn, pxx - rho * fma(vx, vx, -(vy * vy)), pxx) + hn * S_xx;
-  const R pxy1 = fma(-sn, pxy - (rho * vx) * vy, pxy) + hn * S_xy;
-  const R jx1 = jx + Fx, jy1 = jy + Fy;
-  // back to populations: f = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4) m'
-  const R r0 = drho * R(1.0 / 9.0), r1 = e1 * R(1.0 / 36.0), r2 = ep1 * R(1.0 / 36.0);
-  const R r3 = jx1 * R(1.0 / 6.0), r4 = qx1 * R(1.0 / 12.0), r5 = jy1 * R(1.0 / 6.0),
-          r6 = qy1 * R(1.0 / 12.0), r7 = pxx1 * R(0.25), r8 = pxy1 * R(0.25);
-  s[0] = fma(R(4), r2 - r1, r0);
-  const R A = fma(R(-2), r2, r0 - r1), Dg = fma(R(2), r1, r0 + r2);
-  const R ox = fma(R(-2), r4, r3), oy = fma(R(-2), r6, r5);
-  s[1] = (A + ox) + r7;
-  s[3] = (A - ox) + r7;
-  s[2] = (A + oy) - r7;
-  s[4] = (A - oy) - r7;
-  const R X = r3 + r4, Y = r5 + r6;
-  s[5] = (Dg + (X + Y)) + r8;
-  s[6] = (Dg - (X - Y)) - r8;
-  s[7] = (Dg - (X + Y)) + r8;
-  s[8] = (Dg + (X - Y)) - r8;
+  const R r1 = fma(R(k.e), fma(R(-3), w, fma(R(2), drho, e)), R(k.eS) * fma(R(k.sig_e), FF, vF));
+  const R r2 = fma(R(k.p), fma(R(3), w, ep - drho), R(k.pS) * fma(R(k.sig_eps), FF, vF));
+  // q + m = j - 3 (s1 - s3) + m, and likewise in y
+  const R gx = fma(R(-3), s[1] - s[3], jx) + mx, gy = fma(R(-3), s[2] - s[4], jy) + my;
+  const R ox = fma(R(k.qa), gx, R(k.qaF) * Fx), oy = fma(R(k.qa), gy, R(k.qaF) * Fy);
+  const R X = fma(R(k.qd), gx, R(k.qdF) * Fx), Y = fma(R(k.qd), gy, R(k.qdF) * Fy);
+  const R kn = R(d.sig) * inv_psi2;
+  const R ux = fma(kn, Fx, vx), uy = fma(kn, Fy, vy);           // v' of the stress moments
+  const R dxx = (ax - ay) - fma(mx, vx, -(my * vy)), dxy = fma(-mx, vy, p57 - p68);
+  const R r7 = fma(R(k.n), dxx, R(k.nxx) * fma(ux, Fx, -(uy * Fy)));
+  const R r8 = fma(R(k.n), dxy, R(k.nxy) * fma(ux, Fy, uy * Fx));
+  s[0] = fma(R(4), r2 - r1, s[0]);
+  const R A = fma(R(-2), r2, -r1), Dg = fma(R(2), r1, r2);
+  const R Ap = A + r7, Am = A - r7, Dp = Dg + r8, Dm = Dg - r8, XpY = X + Y, XmY = X - Y;
+  s[1] += Ap + ox;
+  s[3] += Ap - ox;
+  s[2] += Am + oy;
+  s[4] += Am - oy;
+  s[5] += Dp + XpY;
+  s[7] += Dp - XpY;
+  s[6] += Dm - XmY;
+  s[8] += Dm + XmY;
 }
 
 // The collision of a node: BGK (collide) or MRT (collide_mrt).
@@ -426,13 +451,13 @@ __device__ __forceinline__ void collide_any(R (&s)[9], R drho, R rho, R jx, R jy
     collide<R>(s, drho, rho, jx, jy, Fx, Fy, inv_psi2, d);
 }
 
+// Momentum sum_a s_a e_a in the arithmetic type.
 template <typename R>
-__device__ __forceinline__ R mom_x(const R (&s)[9]) {
-  return ((s[1] - s[3]) + (s[5] - s[7])) + (s[8] - s[6]);
-}
-template <typename R>
-__device__ __forceinline__ R mom_y(const R (&s)[9]) {
-  return ((s[2] - s[4]) + (s[5] - s[7])) + (s[6] - s[8]);
+__device__ __forceinline__ void momentum(const R (&s)[9], R& jx, R& jy) {
+#pragma clang fp contract(off)
+  const R u = s[5] - s[7], v = s[8] - s[6];
+  jx = ((s[1] - s[3]) + u) + v;
+  jy = ((s[2] - s[4]) + u) - v;
 }
 
 // Momentum of FP32 values (as FP64 t) summed in FP64: exact unless the
@@ -493,11 +518,54 @@ __device__ __forceinline__ void update_node(typename Store<S>::R (&s)[9],
   if constexpr (Store<S>::kConserve) {
     double m0, jx0, jy0;
     exact_moments(s, m0, jx0, jy0);
-    collide_any<MRT, R>(s, drho, R(rho), mom_x(s), mom_y(s), R(Fx), R(Fy), ip2, d);
+    R jx, jy;
+    momentum(s, jx, jy);
+    collide_any<MRT, R>(s, drho, R(rho), jx, jy, R(Fx), R(Fy), ip2, d);
     conserve(s, m0, jx0 + double(Fx), jy0 + double(Fy));
   } else {
-    collide_any<MRT, R>(s, drho, R(rho), mom_x(s), mom_y(s), R(Fx), R(Fy), ip2, d);
+    R jx, jy;
+    momentum(s, jx, jy);
+    collide_any<MRT, R>(s, drho, R(rho), jx, jy, R(Fx), R(Fy), ip2, d);
   }
+}
+
+// What a pulled row keeps for its collision: the density (deviation) it summed
+// and 1/psi^2.
+template <typename S> struct NodeQ {
+  typename Store<S>::R drho = 0, ip2 = 0;
+};
+
+// Density from the summed stored values.
+template <typename S>
+__device__ __forceinline__ typename Store<S>::P density(typename Store<S>::R drho, const RunDev& d) {
+  using P = typename Store<S>::P;
+  if constexpr (Store<S>::kDev) return P(d.rho_ref) + P(drho);
+  return drho;
+}
+
+// psi of a pulled node; q receives what its collision needs.
+template <typename S>
+__device__ __forceinline__ typename Store<S>::P eval_psi(const typename Store<S>::R (&f)[9],
+                                                         const RunDev& d, NodeQ<S>& q) {
+  q.drho = sum9(f);
+  const PsiPair w = psi_pair(psi2_of(density<S>(q.drho, d), d));
+  q.ip2 = typename Store<S>::R(w.ip2);
+  return w.psi;
+}
+
+// Force and collision of a node from the psi rows around it; true if the node is
+// bad (density or psi^2 not positive, or not a number).
+template <typename S, bool MRT>
+__device__ __forceinline__ bool finish_node(typename Store<S>::R (&f)[9], const NodeQ<S>& q,
+                                            const typename Store<S>::P* rs,
+                                            const typename Store<S>::P* rc,
+                                            const typename Store<S>::P* rn, int i, const RunDev& d) {
+  using P = typename Store<S>::P;
+  P Fx, Fy;
+  force3x3(rs, rc, rn, i, P(d.mG12), Fx, Fy);
+  const P rho = density<S>(q.drho, d);
+  update_node<S, MRT>(f, q.drho, rho, Fx, Fy, q.ip2, d);
+  return !(q.ip2 > 0) || !(rho > P(0));
 }
 
 // One tile: columns [x0, x0+ncols), rows [y0, y0+nrows), nrows <= LMAX.
@@ -515,7 +583,6 @@ __device__ __forceinline__ void tile_step(const typename Store<S>::E* __restrict
                                           typename Store<S>::P* haloL, typename Store<S>::P* haloR) {
   using T = Store<S>;
   using R = typename T::R;
-  using P = typename T::P;
   constexpr int SW = 64 * NW;
   const int tid = threadIdx.x;
   LBM_TILE_CHECK(ncols >= 1 && ncols <= SW && nrows >= 1 && nrows <= LMAX && x0 >= 0 &&
@@ -525,7 +592,6 @@ __device__ __forceinline__ void tile_step(const typename Store<S>::E* __restrict
   const Cols cx = cols_of(act ? x : x0, d.nx);
   const int xl = x0 == 0 ? d.nx - 1 : x0 - 1;
   const int xr = x0 + ncols >= d.nx ? 0 : x0 + ncols;
-  const P rref = P(d.rho_ref);
   bool bad = false;
 
   // preload rows y0-1 (ring slot 0) and y0 (slot 1); with PF = 2 also issue row
@@ -545,15 +611,14 @@ __device__ __forceinline__ void tile_step(const typename Store<S>::E* __restrict
     yy = yy < 0 ? yy + d.ny : (yy >= d.ny ? yy - d.ny : yy);
     R f[9];
     pull9<S>(src, d, cols_of((i & 1) ? xr : xl, d.nx), yy, f);
-    const P rho = rref + P(sum9(f));
-    ((i & 1) ? haloR : haloL)[k] = psi_root(psi2_of(rho, d));
+    NodeQ<S> q;
+    ((i & 1) ? haloR : haloL)[k] = eval_psi<S>(f, d, q);
   }
 
-  P psi2c = P(0);
+  NodeQ<S> qc;
   if (act) {
-    ring[0][tid + 1] = psi_root(psi2_of(rref + P(sum9(fp)), d));
-    psi2c = psi2_of(rref + P(sum9(fc)), d);
-    ring[1][tid + 1] = psi_root(psi2c);
+    ring[0][tid + 1] = eval_psi<S>(fp, d, qc);
+    ring[1][tid + 1] = eval_psi<S>(fc, d, qc);
   }
   __syncthreads();  // the halo columns are in LDS
   if (tid == 0) {
@@ -568,15 +633,14 @@ __device__ __forceinline__ void tile_step(const typename Store<S>::E* __restrict
     const int yn = y + 1 == d.ny ? 0 : y + 1;
     const int sl = (j + 2) & 3;
     R fnn[9];
-    P psi2n = P(0);
+    NodeQ<S> qn;
     if (act) {
       if (PF == 2) {
         if (j + 1 < nrows) pull9<S>(src, d, cx, yn + 1 == d.ny ? 0 : yn + 1, fnn);
       } else {
         pull9<S>(src, d, cx, yn, fn);
       }
-      psi2n = psi2_of(rref + P(sum9(fn)), d);
-      ring[sl][tid + 1] = psi_root(psi2n);
+      ring[sl][tid + 1] = eval_psi<S>(fn, d, qn);
     }
     if (tid == 0) {
       ring[sl][0] = haloL[j + 2];
@@ -584,20 +648,14 @@ __device__ __forceinline__ void tile_step(const typename Store<S>::E* __restrict
     }
     __syncthreads();
     if (act) {
-      P Fx, Fy;
-      force3x3(ring[j & 3], ring[(j + 1) & 3], ring[sl], tid + 1, P(d.mG), Fx, Fy);
-      const R drho = sum9(fc);
-      const P rho = rref + P(drho);
-      bad |= !(psi2c > P(0)) || !(rho > P(0));
-      const R ip2 = d.sig != 0.0 ? rcp(R(psi2c)) : R(0);
-      update_node<S, MRT>(fc, drho, rho, Fx, Fy, ip2, d);
+      bad |= finish_node<S, MRT>(fc, qc, ring[j & 3], ring[(j + 1) & 3], ring[sl], tid + 1, d);
       typename T::E* row = dst + (int64_t)y * d.rs;
 #pragma unroll
       for (int a = 0; a < 9; ++a)
         if (index_ok(row + a * d.plane + cx.x - dst, d.elems)) T::st(row + a * d.plane + cx.x, fc[a]);
 #pragma unroll
       for (int a = 0; a < 9; ++a) fc[a] = fn[a];
-      psi2c = psi2n;
+      qc = qn;
       if (PF == 2 && j + 1 < nrows) {
 #pragma unroll
         for (int a = 0; a < 9; ++a) fn[a] = fnn[a];
@@ -731,7 +789,6 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
                                            typename Store<S>::R (*xch)[64 * NW]) {
   using T = Store<S>;
   using R = typename T::R;
-  using P = typename T::P;
   const int tid = threadIdx.x;
   LBM_TILE_CHECK(ncols >= 1 && ncols <= 64 * NW - 6 && nrows >= 1 && x0 >= 0 &&
                  x0 + ncols <= d.nx && y0 >= 0 && y0 + nrows <= d.ny);
@@ -746,28 +803,26 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
   auto wrapx = [&](int x) { return x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x); };
   auto wrapy = [&](int y) { return y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y); };
   const Cols cx = cols_of(wrapx(x0 - 3 + min(tid, n0 - 1)), d.nx);
-  const P rref = P(d.rho_ref);
   bool bad1 = false, bad2 = false;
   const int ya = y0 - 3;                            // first psi(t) row
 
   // preload: psi(t) of rows y0-3 (ring slot 0) and y0-2 (slot 1); pulled row y0-2
   R fc[9] = {}, fn[9] = {};
-  P psi2c = P(0);
+  NodeQ<S> qc;
   if (act0) {
     R f[9];
     pull9<S>(src, d, cx, wrapy(ya), f);
     pull9<S>(src, d, cx, wrapy(ya + 1), fc);
     if (PF == 2) pull9<S>(src, d, cx, wrapy(ya + 2), fn);
-    ring1[0][tid] = psi_root(psi2_of(rref + P(sum9(f)), d));
-    psi2c = psi2_of(rref + P(sum9(fc)), d);
-    ring1[1][tid] = psi_root(psi2c);
+    ring1[0][tid] = eval_psi<S>(f, d, qc);
+    ring1[1][tid] = eval_psi<S>(fc, d, qc);
   }
 
   // f*(t+1) of the last three step-one rows, kept for step two:
   // gA = row y1-1 (all 9), gB = row y1-2 (0,1,3,2,5,6), gC = row y1-3 (2,5,6)
   R gA[9] = {}, gB[6] = {}, gC[3] = {};
   R hp[9] = {};     // step-two pulled populations of the row collided next
-  P psi2p = P(0);
+  NodeQ<S> qp;
   const int n_one = nrows + 4;                      // step-one rows y0-2 .. y0+nrows+1
   // One row of the march.  Mode (MODE: SteadyMode, or kBatchSteadyMode in the
   // batched kernel) bit 16 marks a steady row, in
@@ -782,7 +837,7 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
     const int y1 = y0 - 2 + j;                      // step-one row collided at this j
     // ---- phase 1: psi(t) of row y1+1; exchange of the rows step two pulls
     R fnn[9];
-    P psi2n = P(0);
+    NodeQ<S> qn;
     if ((St || j < n_one) && ((M & kRowPsi) || act0)) {
       // the row loads go out at raised wave priority, so a wave about to issue
       // them is not held behind the other wave's arithmetic (FP64: 1 % faster)
@@ -793,8 +848,7 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
         pull9<S>(src, d, cx, wrapy(y1 + 1), fn);
       }
       __builtin_amdgcn_s_setprio(0);
-      psi2n = psi2_of(rref + P(sum9(fn)), d);
-      ring1[(j + 2) & 3][tid] = psi_root(psi2n);
+      ring1[(j + 2) & 3][tid] = eval_psi<S>(fn, d, qn);
     }
     if ((St || j >= 3) && ((M & kRowPsi) || act1)) {  // step two pulls row q = y1 - 2 below
       xch[0][tid] = gB[1];
@@ -808,7 +862,7 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
     // ---- phase 2: step-two pull of row q = y1-2 and its psi(t+1); step-one collide of row y1
     const int q = y1 - 2;
     R hn[9];
-    P psi2q = P(0);
+    NodeQ<S> qh;
     if ((St || j >= 3) && ((M & kRowPull2) || pull2)) {
       hn[0] = gB[0];
       hn[1] = xch[0][tc - 1];
@@ -819,8 +873,7 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
       hn[6] = xch[3][tc + 1];
       hn[7] = xch[4][tc + 1];
       hn[8] = xch[5][tc - 1];
-      psi2q = psi2_of(rref + P(sum9(hn)), d);
-      ring2[(q - (y0 - 1)) & 3][tid] = psi_root(psi2q);
+      ring2[(q - (y0 - 1)) & 3][tid] = eval_psi<S>(hn, d, qh);
     }
     if (St || j >= 1) {  // rotate the kept step-one rows (gA was produced at j-1)
       gC[0] = gB[3]; gC[1] = gB[4]; gC[2] = gB[5];
@@ -829,20 +882,14 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
     }
     if ((St || j < n_one) && ((M & kRowCollide1) || act0)) {
       if ((M & kRowCollide1) || act1) {
-        P Fx, Fy;
-        force3x3(ring1[j & 3], ring1[(j + 1) & 3], ring1[(j + 2) & 3], tc, P(d.mG), Fx, Fy);
-        const R drho = sum9(fc);
-        const P rho = rref + P(drho);
         const bool chk = out && y1 >= y0 && y1 < y0 + nrows;
-        bad1 |= chk && (!(psi2c > P(0)) || !(rho > P(0)));
-        const R ip2 = d.sig != 0.0 ? rcp(R(psi2c)) : R(0);
-        update_node<S, MRT>(fc, drho, rho, Fx, Fy, ip2, d);
+        bad1 |= finish_node<S, MRT>(fc, qc, ring1[j & 3], ring1[(j + 1) & 3], ring1[(j + 2) & 3], tc, d) && chk;
 #pragma unroll
         for (int a = 0; a < 9; ++a) gA[a] = T::round(fc[a]);
       }
 #pragma unroll
       for (int a = 0; a < 9; ++a) fc[a] = fn[a];
-      psi2c = psi2n;
+      qc = qn;
       if (PF == 2 && (St || j + 1 < n_one)) {
 #pragma unroll
         for (int a = 0; a < 9; ++a) fn[a] = fnn[a];
@@ -852,14 +899,8 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
     // ---- phase 3: step-two collide of row r = q-1 and store
     const int r = q - 1;
     if ((St || (j >= 4 && r >= y0 && r < y0 + nrows)) && ((M & kRowCollide2) || out)) {
-      P Fx, Fy;
-      force3x3(ring2[(r - 1 - (y0 - 1)) & 3], ring2[(r - (y0 - 1)) & 3], ring2[(q - (y0 - 1)) & 3],
-               tc, P(d.mG), Fx, Fy);
-      const R drho = sum9(hp);
-      const P rho = rref + P(drho);
-      bad2 |= out && (!(psi2p > P(0)) || !(rho > P(0)));
-      const R ip2 = d.sig != 0.0 ? rcp(R(psi2p)) : R(0);
-      update_node<S, MRT>(hp, drho, rho, Fx, Fy, ip2, d);
+      bad2 |= finish_node<S, MRT>(hp, qp, ring2[(r - 1 - (y0 - 1)) & 3], ring2[(r - (y0 - 1)) & 3],
+                                  ring2[(q - (y0 - 1)) & 3], tc, d) && out;
       if (out) {
         typename T::E* orow = dst + (int64_t)wrapy(r) * d.rs;
 #pragma unroll
@@ -870,7 +911,7 @@ __device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restric
     if (St || j >= 3) {
 #pragma unroll
       for (int a = 0; a < 9; ++a) hp[a] = hn[a];
-      psi2p = psi2q;
+      qp = qh;
     }
   };
   // rows 0..4 fill the pipeline, 5 .. n_one-2 are steady, the last two drain it
@@ -998,7 +1039,6 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
                                            typename Store<S>::R (*xch2)[64 * NW]) {
   using T = Store<S>;
   using R = typename T::R;
-  using P = typename T::P;
   const int tid = threadIdx.x;
   LBM_TILE_CHECK(ncols >= 1 && ncols <= 64 * NW - 10 && nrows >= 1 && x0 >= 0 &&
                  x0 + ncols <= d.nx && y0 >= 0 && y0 + nrows <= d.ny);
@@ -1013,21 +1053,19 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
   auto wrapx = [&](int x) { return x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x); };
   auto wrapy = [&](int y) { return y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y); };
   const Cols cx = cols_of(wrapx(x0 - 5 + min(tid, n0 - 1)), d.nx);
-  const P rref = P(d.rho_ref);
   bool bad1 = false, bad2 = false, bad3 = false;
   const int ya = y0 - 5;                            // first psi(t) row (ring1 slot 0)
   const int yb = y0 - 3;                            // first psi(t+1) row (ring2 slot 0)
   const int yc = y0 - 1;                            // first psi(t+2) row (ring3 slot 0)
 
   R fc[9] = {}, fn[9] = {};
-  P psi2c = P(0);
+  NodeQ<S> qc;
   if (act0) {
     R f[9];
     pull9<S>(src, d, cx, wrapy(ya), f);
     pull9<S>(src, d, cx, wrapy(ya + 1), fc);
-    ring1[0][tid] = psi_root(psi2_of(rref + P(sum9(f)), d));
-    psi2c = psi2_of(rref + P(sum9(fc)), d);
-    ring1[1][tid] = psi_root(psi2c);
+    ring1[0][tid] = eval_psi<S>(f, d, qc);
+    ring1[1][tid] = eval_psi<S>(fc, d, qc);
   }
   // f*(t+1) kept for step two: gA = row y1-1 (all 9), gB = y1-2 (0,1,3,2,5,6),
   // gC = y1-3 (2,5,6); f*(t+2) kept for step three likewise (kA, kB, kC, rows
@@ -1035,19 +1073,18 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
   R gA[9] = {}, gB[6] = {}, gC[3] = {};
   R kA[9] = {}, kB[6] = {}, kC[3] = {};
   R hp[9] = {}, hp3[9] = {};   // pulled rows of steps two and three collided next
-  P psi2p = P(0), psi3p = P(0);
+  NodeQ<S> qp, qp3;
   const int n_one = nrows + 8;                      // step-one rows y0-4 .. y0+nrows+3
   auto row = [&](const int j, auto steady) __attribute__((always_inline)) {
     constexpr bool St = decltype(steady)::value;
     const int y1 = y0 - 4 + j;
     // ---- phase 1: psi(t) of row y1+1; exchange rows for steps two and three
-    P psi2n = P(0);
+    NodeQ<S> qn;
     if ((St || j < n_one) && act0) {
       __builtin_amdgcn_s_setprio(2);
       pull9<S>(src, d, cx, wrapy(y1 + 1), fn);
       __builtin_amdgcn_s_setprio(0);
-      psi2n = psi2_of(rref + P(sum9(fn)), d);
-      ring1[(j + 2) & 3][tid] = psi_root(psi2n);
+      ring1[(j + 2) & 3][tid] = eval_psi<S>(fn, d, qn);
     }
     const bool lv2 = St || (j >= 3 && j <= n_one);  // step two pulls q2 = y1-2
     const bool lv3 = St || j >= 8;                  // step three pulls q3 = y1-5
@@ -1075,7 +1112,7 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
     // ---- phase 2: pulls of steps two and three and their psi; step-one collide
     const int q2 = y1 - 2, q3 = y1 - 5;
     R hn[9], hn3[9];
-    P psi2q = P(0), psi3q = P(0);
+    NodeQ<S> qh, qh3;
     if (lv2 && (St || pull2)) {
       hn[0] = gB[0];
       hn[1] = xch1[0][tc - 1];
@@ -1086,8 +1123,7 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
       hn[6] = xch1[3][tc + 1];
       hn[7] = xch1[4][tc + 1];
       hn[8] = xch1[5][tc - 1];
-      psi2q = psi2_of(rref + P(sum9(hn)), d);
-      ring2[(q2 - yb) & 3][tid] = psi_root(psi2q);
+      ring2[(q2 - yb) & 3][tid] = eval_psi<S>(hn, d, qh);
     }
     if (lv3 && (St || pull3)) {
       hn3[0] = kB[0];
@@ -1099,8 +1135,7 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
       hn3[6] = xch2[3][tc + 1];
       hn3[7] = xch2[4][tc + 1];
       hn3[8] = xch2[5][tc - 1];
-      psi3q = psi2_of(rref + P(sum9(hn3)), d);
-      ring3[(q3 - yc) & 3][tid] = psi_root(psi3q);
+      ring3[(q3 - yc) & 3][tid] = eval_psi<S>(hn3, d, qh3);
     }
     if (St || j >= 1) {  // rotate the kept step-one rows (gA was produced at j-1)
       gC[0] = gB[3]; gC[1] = gB[4]; gC[2] = gB[5];
@@ -1109,20 +1144,14 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
     }
     if ((St || j < n_one) && act0) {
       if (act1) {
-        P Fx, Fy;
-        force3x3(ring1[j & 3], ring1[(j + 1) & 3], ring1[(j + 2) & 3], tc, P(d.mG), Fx, Fy);
-        const R drho = sum9(fc);
-        const P rho = rref + P(drho);
         const bool chk = out && y1 >= y0 && y1 < y0 + nrows;
-        bad1 |= chk && (!(psi2c > P(0)) || !(rho > P(0)));
-        const R ip2 = d.sig != 0.0 ? rcp(R(psi2c)) : R(0);
-        update_node<S, MRT>(fc, drho, rho, Fx, Fy, ip2, d);
+        bad1 |= finish_node<S, MRT>(fc, qc, ring1[j & 3], ring1[(j + 1) & 3], ring1[(j + 2) & 3], tc, d) && chk;
 #pragma unroll
         for (int a = 0; a < 9; ++a) gA[a] = T::round(fc[a]);
       }
 #pragma unroll
       for (int a = 0; a < 9; ++a) fc[a] = fn[a];
-      psi2c = psi2n;
+      qc = qn;
     }
     __syncthreads();
     // ---- phase 3: step-two collide of row r2 = q2-1; step-three collide of r3 = q3-1 and store
@@ -1133,15 +1162,9 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
       kB[0] = kA[0]; kB[1] = kA[1]; kB[2] = kA[3];
       kB[3] = kA[2]; kB[4] = kA[5]; kB[5] = kA[6];
       if (act2) {
-        P Fx, Fy;
-        force3x3(ring2[(r2 - 1 - yb) & 3], ring2[(r2 - yb) & 3], ring2[(q2 - yb) & 3], tc, P(d.mG),
-                 Fx, Fy);
-        const R drho = sum9(hp);
-        const P rho = rref + P(drho);
         const bool chk = out && r2 >= y0 && r2 < y0 + nrows;
-        bad2 |= chk && (!(psi2p > P(0)) || !(rho > P(0)));
-        const R ip2 = d.sig != 0.0 ? rcp(R(psi2p)) : R(0);
-        update_node<S, MRT>(hp, drho, rho, Fx, Fy, ip2, d);
+        bad2 |= finish_node<S, MRT>(hp, qp, ring2[(r2 - 1 - yb) & 3], ring2[(r2 - yb) & 3],
+                                    ring2[(q2 - yb) & 3], tc, d) && chk;
 #pragma unroll
         for (int a = 0; a < 9; ++a) kA[a] = T::round(hp[a]);
       }
@@ -1149,17 +1172,11 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
     if (lv2) {
 #pragma unroll
       for (int a = 0; a < 9; ++a) hp[a] = hn[a];
-      psi2p = psi2q;
+      qp = qh;
     }
     if ((St || j >= 10) && out) {
-      P Fx, Fy;
-      force3x3(ring3[(r3 - 1 - yc) & 3], ring3[(r3 - yc) & 3], ring3[(q3 - yc) & 3], tc, P(d.mG),
-               Fx, Fy);
-      const R drho = sum9(hp3);
-      const P rho = rref + P(drho);
-      bad3 |= !(psi3p > P(0)) || !(rho > P(0));
-      const R ip2 = d.sig != 0.0 ? rcp(R(psi3p)) : R(0);
-      update_node<S, MRT>(hp3, drho, rho, Fx, Fy, ip2, d);
+      bad3 |= finish_node<S, MRT>(hp3, qp3, ring3[(r3 - 1 - yc) & 3], ring3[(r3 - yc) & 3],
+                                  ring3[(q3 - yc) & 3], tc, d);
       typename T::E* orow = dst + (int64_t)wrapy(r3) * d.rs;
 #pragma unroll
       for (int a = 0; a < 9; ++a)
@@ -1168,7 +1185,7 @@ __device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restric
     if (lv3) {
 #pragma unroll
       for (int a = 0; a < 9; ++a) hp3[a] = hn3[a];
-      psi3p = psi3q;
+      qp3 = qh3;
     }
   };
   // rows 0..9 fill the pipeline, 10 .. n_one-1 are steady (every row condition
@@ -1390,8 +1407,10 @@ __global__ void k_moments1(const typename Store<S>::E* __restrict__ src, RunDev 
     const double r = d.rho_ref + double(drho);
     const int64_t o = (int64_t)y * d.nx + x;
     rho[o] = r;
-    ux[o] = double(mom_x(f) / R(r));
-    uy[o] = double(mom_y(f) / R(r));
+    R jx, jy;
+    momentum(f, jx, jy);
+    ux[o] = double(jx / R(r));
+    uy[o] = double(jy / R(r));
     psi[o] = sqrt(psi2_of(r, d));
   }
 }
@@ -1410,7 +1429,7 @@ __global__ void k_moments2(RunDev d, const double* __restrict__ psi, const doubl
     const double s[3] = {rs[xm], rs[x], rs[xp]}, c[3] = {rc[xm], rc[x], rc[xp]},
                  n[3] = {rn[xm], rn[x], rn[xp]};
     double Fx, Fy;
-    force3x3(s, c, n, 1, d.mG, Fx, Fy);
+    force3x3(s, c, n, 1, d.mG12, Fx, Fy);
     const int64_t o = (int64_t)y * d.nx + x;
     const double r = rho[o];
     vx[o] += Fx / (2.0 * r);
@@ -1439,7 +1458,7 @@ __global__ void k_normal_pressure(const double* __restrict__ rbar, RunDev d, dou
   const double pm = sqrt(psi2_of(rbar[xm], d)), pc = sqrt(psi2_of(rbar[x], d)),
                pp = sqrt(psi2_of(rbar[xp], d));
   const double d1 = 0.5 * (pp - pm), d2 = (pp - 2.0 * pc) + pm;
-  const double G = -d.mG;
+  const double G = -12.0 * d.mG12;
   pn[x] = rbar[x] * (1.0 / 3.0) + 0.5 * G * pc * pc + (G / 12.0) * (3.0 * pc * d2) +
           2.0 * G * G * sigma * d1 * d1;
 }
@@ -1466,7 +1485,7 @@ __global__ __launch_bounds__(256) void k_surface_tension(const double* __restric
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const double G = -d.mG;
+    const double G = -12.0 * d.mG12;
     out[0] = (-G / 6.0 + 2.0 * G * G * sigma) * sm[0] * 0.5;
   }
 }

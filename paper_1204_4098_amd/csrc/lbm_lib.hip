@@ -86,58 +86,54 @@ RunDev make_rundev(const lbm_params& p, const EosConst& k, double rho_ref, int64
   d.RT = k.RT;
   d.c1 = k.c1;
   d.c2 = k.c2;
-  d.two_over_G = k.two_over_G;
-  d.mG = -p.G;
+  d.eA = k.RT * k.two_over_G;
+  d.eB = k.c2 / k.RT;
+  d.eC = 1.0 / (3.0 * k.RT);
+  d.mG12 = -p.G / 12.0;
   d.inv_tau = 1.0 / p.tau;
+  double c_f = 0.0, Be = 0.0;
   switch (p.scheme) {
     case LBM_SCHEME_SHANCHEN:  // Eqs. (9)-(10): u_eq = u + tau F/rho, no forcing term
       d.c_eq = p.tau;
-      d.c_f = 0.0;
+      c_f = 0.0;
       d.sig = 0.0;
-      d.Be = d.Ce = 0.0;
+      Be = d.Ce = 0.0;
       break;
     case LBM_SCHEME_EDM:  // Eq. (11) = Eq. (16): B_e = C_e = 1, velocity u + F/(2 rho)
       d.c_eq = 0.0;
-      d.c_f = 0.5;
+      c_f = 0.5;
       d.sig = 0.0;
-      d.Be = d.Ce = 1.0;
+      Be = d.Ce = 1.0;
       break;
     case LBM_SCHEME_EDM_MODIFIED:  // Sec. III.C: EDM with C_e = 1/tau
       d.c_eq = 0.0;
-      d.c_f = 0.5;
+      c_f = 0.5;
       d.sig = 0.0;
-      d.Be = 1.0;
+      Be = 1.0;
       d.Ce = 1.0 / p.tau;
       break;
     case LBM_SCHEME_LADD:  // Table I: u in the equilibrium and in F_a, B_e = C_e = 1
       d.c_eq = 0.0;
-      d.c_f = 0.0;
+      c_f = 0.0;
       d.sig = 0.0;
-      d.Be = d.Ce = 1.0;
+      Be = d.Ce = 1.0;
       break;
     default:  // Eq. (31): u_eq = v, B_e = C_e = 1 - 1/(2 tau), v' = v + sigma F/((tau - 1/2) psi^2)
       d.c_eq = 0.5;
-      d.c_f = 0.5;
+      c_f = 0.5;
       d.sig = p.sigma / (p.tau - 0.5);
-      d.Be = d.Ce = 1.0 - 0.5 / p.tau;
+      Be = d.Ce = 1.0 - 0.5 / p.tau;
       break;
   }
-  d.wCe0 = 4.0 / 9.0 * d.Ce;
-  d.wCe1 = 1.0 / 9.0 * d.Ce;
-  d.wCe2 = 1.0 / 36.0 * d.Ce;
-  d.wBe3_1 = 3.0 / 9.0 * d.Be;
-  d.wBe3_2 = 3.0 / 36.0 * d.Be;
-  d.om_w0 = 4.0 / 9.0 * d.inv_tau;
-  d.om_w1 = 1.0 / 9.0 * d.inv_tau;
-  d.om_w2 = 1.0 / 36.0 * d.inv_tau;
-  d.om_3w1 = 3.0 / 9.0 * d.inv_tau;
-  d.om_3w2 = 3.0 / 36.0 * d.inv_tau;
+  d.c_d = c_f - d.c_eq;
   d.om1 = 1.0 - d.inv_tau;
+  d.om_2 = d.inv_tau / 2.0;
+  d.om_9 = d.inv_tau / 9.0;
+  d.om_3 = d.inv_tau / 3.0;
+  d.Be_3 = Be / 3.0;
   d.rho_ref = rho_ref;
   d.run = run;
   d.mrt = 0;
-  d.s_e = d.s_eps = d.s_q = d.inv_tau;
-  d.sig_e = d.sig_eps = d.sig;
   return d;
 }
 
@@ -145,12 +141,13 @@ RunDev make_rundev(const lbm_params& p, const EosConst& k, double rho_ref, int64
 // and energy-flux rates r[0..2] (the density, momentum and stress moments relax
 // at 1/tau): sigma / (1/s - 1/2) of the improved scheme per moment.
 void set_mrt(RunDev& d, const lbm_params& p, const double* r) {
+  auto h = [](double s) { return 1.0 - 0.5 * s; };
+  const double n = d.inv_tau;
   d.mrt = 1;
-  d.s_e = r[0];
-  d.s_eps = r[1];
-  d.s_q = r[2];
-  d.sig_e = p.sigma / (1.0 / r[0] - 0.5);
-  d.sig_eps = p.sigma / (1.0 / r[1] - 0.5);
+  d.m = MrtDev{-r[0] / 36.0, h(r[0]) / 6.0,  p.sigma / (1.0 / r[0] - 0.5),
+               -r[1] / 36.0, -h(r[1]) / 6.0, p.sigma / (1.0 / r[1] - 0.5),
+               r[2] / 6.0,   (1.0 + h(r[2])) / 6.0, -r[2] / 12.0, 1.0 / 6.0 - h(r[2]) / 12.0,
+               -n / 4.0,     h(n) / 2.0,     h(n) / 4.0};
 }
 
 // Encode FP64 populations into the storage buffer (layout::encode): FP64 as
@@ -1502,10 +1499,7 @@ int lbm_batch_set_mrt(lbm_batch* b, const double* rates) {
   }
   for (int r = 0; r < b->nruns; ++r) {
     RunDev& d = b->d[r];
-    // back to the BGK values make_rundev sets, then the run's MRT rates
     d.mrt = 0;
-    d.s_e = d.s_eps = d.s_q = d.inv_tau;
-    d.sig_e = d.sig_eps = d.sig;
     if (rates) set_mrt(d, b->p[r], rates + 3 * r);
   }
   HIPCHK(hipMemcpyAsync(b->d_runs, b->d.data(), b->nruns * sizeof(RunDev), hipMemcpyHostToDevice, b->st));
