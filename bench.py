@@ -158,7 +158,7 @@ def main():
                     help="steps of the batched FP32-vs-FP64 coexistence comparison")
     ap.add_argument("--tile", default=None,
                     help="waves,rows,depth[,steps]: fixed launch shape (no tuning); steps = time "
-                         "steps per launch (1, or 2 for the two-step kernel)")
+                         "steps per launch (1 to 4)")
     ap.add_argument("--batch-case", default=None, choices=["f64", "f32", "f32dev", "f32_f64arith"],
                     help="time only this case of the batched leg (no plain-path timing, no "
                          "coexistence comparison): a short run for the counter profiles")
@@ -213,7 +213,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                      "traffic": traffic_for(args.workload, args.precision, res["tile"]),
-                     "kernel": {1: "k_step", 2: "k_step2", 3: "k_step3"}[ts], "steps_per_launch": ts,
+                     "kernel": "k_step" if ts == 1 else "k_pipe", "steps_per_launch": ts,
                      "bytes_per_lup": bpl / ts, "kernel_avg_us": round(launch_ms * 1e3, 2),
                      # MLUPS x the single-step 144 B/LUP over the peak (exceeds 1 only
                      # when steps are fused; not a bandwidth)
@@ -238,9 +238,8 @@ def main():
                                                  "frac": round(gbs / PEAK_HBM_GBS, 4),
                                                  "bytes_per_lup": BYTES_PER_LUP[prec] / r["tile"][3]}
             log(f"precision {PREC_NAME[prec]}: {r['mlups']:.0f} MLUPS")
-        # the FP64 one- and two-step kernels on the same workload, each with its own
-        # roofline fraction (per launch: every population read and written once),
-        # when the tuner has picked the three-step one
+        # the FP64 kernels of one and two steps per launch on the same workload, each with
+        # its own roofline fraction (per launch: every population read and written once)
         for name, t1 in (("f64_one_step", (16, 0, 1, 1)), ("f64_two_step", (4, 0, 2, 2))):
             r = time_lattice(lbm, torch, nx, ny, rho0, kw, 0, args.steps, args.warmup,
                              args.graph_steps, False, t1, settle_ms=args.settle_ms)
@@ -325,7 +324,7 @@ def time_lattice(lbm, torch, nx, ny, rho0, kw, precision, steps, warmup, graph_s
     ts = tile[3]
     # a graph holds whole launches of the tile: its length is rounded down to a
     # multiple of the tile's steps (and of 2)
-    g = graph_steps - graph_steps % (6 if ts == 3 else 2) if graph_steps else 0
+    g = graph_steps - graph_steps % math.lcm(ts, 2) if graph_steps else 0
     if g:
         lat.set_graph_steps(g)   # captures and uploads the graphs of both parities now
     settle(lat, torch, settle_ms)

@@ -208,21 +208,23 @@ int lbm_state_bytes(lbm_ctx* c, size_t* bytes);
 int lbm_save_state(lbm_ctx* c, void* host_buf, size_t bytes);
 int lbm_load_state(lbm_ctx* c, const void* host_buf, size_t bytes);
 
-/* Launch shape ("tile") of the step kernel.  A work-group of 64*waves threads
+/* Launch shape ("tile") of the step kernel.  `steps` (1 to 4) is the number of
+ * time steps one launch advances.  steps = 1: a work-group of 64*waves threads
  * owns a strip of 64*waves columns (one column per thread) and marches up
- * `rows` rows; rows = 0 selects the balanced schedule, in which a grid sized
- * to the GPU's resident capacity splits all strip rows evenly.  `depth` (1 or
- * 2) is how many rows of loads are in flight while a row is collided.
- * `steps` (1, 2 or 3) is the number of time steps one launch advances: with
- * 2, the populations of the intermediate step stay on chip (registers and
- * LDS), so they cross HBM once per two steps; its strips are at most
- * 64*waves - 6 columns wide (the six extra columns are recomputed), spread
- * evenly over nx (FP64: strip edges on 64-byte boundaries), waves in {4, 8}.
- * With 3 (FP64 and FP32-storage-FP64-collision lattices of at least 5 x 5;
- * waves 4 or 8, depth 1; else LBM_ENOTSUP or LBM_EINVAL) they cross HBM once per
- * three steps, strips at most 64*waves - 10 columns wide.  A remainder of
- * lbm_step(n) smaller than `steps` runs as one launch of that many steps.
- * waves in {1, 2, 4, 8, 16}; rows in [0, 128].  lbm_tune times the candidates
+ * `rows` rows; waves in {1, 2, 4, 8, 16}; `depth` (1 or 2) is how many rows of
+ * loads are in flight while a row is collided.  steps > 1: the populations of
+ * the intermediate steps stay on chip (a work-group has one group of waves per
+ * step, which hand them on through LDS), so they cross HBM once per launch;
+ * waves selects the strip width, 4 or 8 for at most 64*k - (4*steps - 2)
+ * columns (k = 4 with FP16 storage, else 3; the 4*steps - 2 extra columns are
+ * recomputed), and with steps = 4 also 2 for k = 2; strips are spread evenly
+ * over nx (FP64: strip edges on 64-byte boundaries).  steps = 2: depth 1 or 2
+ * (the same); steps = 3 and 4: depth 1; steps = 3: FP64 and
+ * FP32-storage-FP64-collision lattices of at least 5 x 5 only (else
+ * LBM_ENOTSUP or LBM_EINVAL).  rows = 0 selects the balanced schedule, in which
+ * a grid sized to the GPU's resident capacity splits all strip rows evenly;
+ * rows in [0, 128].  A remainder of lbm_step(n) smaller than `steps` runs as
+ * one or two launches of fewer steps.  lbm_tune times the candidates
  * on the current state without advancing it and keeps the fastest per lattice
  * step; the choice is cached per (nx, ny, precision, collision operator) for
  * the life of the process.  Every tile gives bitwise identical results. */
@@ -231,7 +233,7 @@ int lbm_set_tile(lbm_ctx* c, int32_t waves, int32_t rows, int32_t depth, int32_t
 int lbm_get_tile(lbm_ctx* c, int32_t* waves, int32_t* rows, int32_t* depth, int32_t* steps);
 
 /* Replay n steps through captured HIP graphs of k steps each (k even, >= 2;
- * 0 disables; a graph holds k / steps launches of the tile and one launch for
+ * 0 disables; a graph holds k / steps launches of the tile and the launches of
  * a remainder).  Needs a non-null stream.  The graphs of both buffer parities
  * are captured, instantiated and uploaded by this call (and again by
  * lbm_set_tile / lbm_tune when the tile changes), so lbm_step only replays
@@ -248,9 +250,8 @@ int lbm_set_graph_steps(lbm_ctx* c, int32_t k);
  * c_s^2 (1/s_e - 1/2).  Each moment gets Eq. (31)'s forcing moment with
  * v' = v + sigma F / ((1/s - 1/2) psi^2) for its own rate s, so rates all equal
  * to 1/tau give the BGK improved scheme.  Improved scheme only, FP64 or FP32
- * deviation storage (else LBM_ENOTSUP); every tile of the lattice's precision
- * (one, two and, for FP64, three steps per launch), bitwise equal to one
- * another.  Captured graphs are rebuilt. */
+ * deviation storage (else LBM_ENOTSUP); every tile of the lattice's precision,
+ * bitwise equal to one another.  Captured graphs are rebuilt. */
 int lbm_set_mrt(lbm_ctx* c, const double* rates);
 
 /* Number of graphs captured over the context's life (a tool can check that a
@@ -304,9 +305,8 @@ int lbm_batch_get_populations(lbm_batch* b, int32_t run, double* f);
  * over the grid; rows = 0: the balanced schedule, in which the rows of all
  * whole-run strips, concatenated, are split evenly over a grid sized to the
  * resident capacity), tuned over the whole batch like lbm_tune;
- * waves in {1, 2, 4, 8}; steps = 2 (waves 2, 4 or 8) runs two time steps per
- * launch as for a single lattice, with strips of at most 64*waves - 6
- * columns. */
+ * waves in {1, 2, 4, 8}; steps = 2 or 4 (waves 2, 4 or 8) runs that many time
+ * steps per launch as for a single lattice, with the strips of the same class. */
 int lbm_batch_tune(lbm_batch* b, int32_t* waves, int32_t* rows, int32_t* depth, int32_t* steps);
 int lbm_batch_set_tile(lbm_batch* b, int32_t waves, int32_t rows, int32_t depth, int32_t steps);
 int lbm_batch_get_tile(lbm_batch* b, int32_t* waves, int32_t* rows, int32_t* depth, int32_t* steps);
@@ -316,7 +316,7 @@ int lbm_batch_set_graph_steps(lbm_batch* b, int32_t k);
  * 3*i+2] = s_e, s_eps, s_q of run i (each in (0, 2), else LBM_EINVAL);
  * rates = NULL restores BGK.  Every run must use the improved scheme and the
  * batch FP64 or FP32 deviation storage (else LBM_ENOTSUP; nothing changes on
- * an error).  One- and two-step batch tiles; each run's results are bitwise
+ * an error).  Every batch tile; each run's results are bitwise
  * those of a single lattice with the same rates.  The descriptor table is
  * uploaded and captured graphs are rebuilt (synchronous). */
 int lbm_batch_set_mrt(lbm_batch* b, const double* rates);

@@ -27,9 +27,8 @@ constexpr int kEY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 // 9 pitch, so the nine direction rows of one lattice row are consecutive in
 // memory.  A row of the march then reads and writes three 9-row blocks close
 // together instead of 18 rows in nine planes far apart: on the 4096 x 4096
-// FP64 workload the two-step kernel runs 491 us per launch against 525 us with
-// plane-major storage (plane = ny pitch, rs = pitch), and a memory-only
-// marching probe reaches 5.5 against 5.2 TB/s.
+// FP64 workload a memory-only marching probe reaches 5.5 TB/s against 5.2 with
+// plane-major storage (plane = ny pitch, rs = pitch).
 inline int pitch_of(int nx) { return (nx + 63) / 64 * 64; }
 inline int64_t plane_of(int nx) { return (int64_t)pitch_of(nx); }
 inline int64_t rs_of(int nx) { return 9 * (int64_t)pitch_of(nx); }
@@ -74,26 +73,27 @@ inline int64_t run_elems(int nx, int ny) { return (elems_of(nx, ny) + 63) / 64 *
 inline int max_items(int nx, int ny) { return ((nx + 63) / 64) * ((ny + 3) / 4); }
 
 // Work list of a batch tile: per run, chunks of L rows times strips of 64*nw
-// columns, or for the two-step tile (ts = 2) strips of at most 64*nw - 6
+// columns, or for a multi-step tile (ts > 1) strips of at most 64*nw - (4 ts - 2)
 // columns spread evenly over the run's width with their edges rounded down to
-// multiples of `align` columns (such items also suit the one-step kernel,
-// which runs an odd remainder step).  L = 0: whole-height strips with row0 set
+// multiples of `align` columns (such items also suit the kernels of fewer steps,
+// which run a remainder).  L = 0: whole-height strips with row0 set
 // for the balanced schedule.  Returns the rows of all items (the balanced
 // schedule's row space).
 inline int64_t build_items(int nruns, const int* nx, const int* ny, int nw, int L, int ts,
                            std::vector<Item>& items, int align = 1) {
   items.clear();
-  const int SW = 64 * nw, A = ts == 2 ? std::max(1, align) : 1;
+  const int SW = 64 * nw, A = ts > 1 ? std::max(1, align) : 1;
+  const int M = SW - (4 * ts - 2);  // widest strip of a multi-step tile
   int64_t rows = 0;
   for (int r = 0; r < nruns; ++r) {
     const int Lr = L > 0 ? L : ny[r];
-    // strips of at most SW - 6 columns once their edges are rounded down to A
-    const int ns = ts == 2 ? (nx[r] + SW - 7 - (A - 1)) / (SW - 6 - (A - 1)) : (nx[r] + SW - 1) / SW;
+    // strips of at most M columns once their edges are rounded down to A
+    const int ns = ts == 1 ? (nx[r] + SW - 1) / SW : nx[r] <= M ? 1 : (nx[r] + M - A) / (M - A + 1);
     auto edge = [&](int k) { return k >= ns ? nx[r] : (int)((int64_t)k * nx[r] / ns) / A * A; };
     for (int y0 = 0; y0 < ny[r]; y0 += Lr)
       for (int sx = 0; sx < ns; ++sx) {
-        const int x0 = ts == 2 ? edge(sx) : sx * SW;
-        const int x1 = ts == 2 ? edge(sx + 1) : std::min(nx[r], x0 + SW);
+        const int x0 = ts > 1 ? edge(sx) : sx * SW;
+        const int x1 = ts > 1 ? edge(sx + 1) : std::min(nx[r], x0 + SW);
         const int n = std::min(Lr, ny[r] - y0);
         items.push_back(Item{r, x0, y0, x1 - x0, n, L > 0 ? 0 : (int32_t)std::min<int64_t>(rows, INT32_MAX)});
         rows += n;

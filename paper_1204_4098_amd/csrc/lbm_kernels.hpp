@@ -18,9 +18,9 @@
 // neighbour strips' halo reads hit L2), so a step moves 2*9*sizeof(storage)
 // bytes per node.  The paper gives no kernel design; this layout is ours.
 //
-// k_step2 advances two time steps per launch with the intermediate
-// populations kept on chip (registers and LDS), so the populations cross HBM
-// once per two steps; k_batch_step runs many lattices from one work list.
+// k_pipe advances two to four time steps per launch with the intermediate
+// populations kept in LDS, so the populations cross HBM once per launch;
+// k_batch_step and k_batch_pipe run many lattices from one work list.
 // All kernels share the node arithmetic below and give identical bits.
 //
 // Storage: FP64 populations, or deviations s_a = f_a - w_a rho_ref in FP32 /
@@ -66,8 +66,9 @@ struct RunDev {
   // F_a = w_a [3 Be e.F + Ce (9 (e.vf)(e.F) - 3 vf.F)], vf = u + c_f F/rho + sig F/psi^2,
   // written vf = u_eq + (c_d/rho + sig/psi^2) F with c_d = c_f - c_eq
   double c_eq, c_d, sig, Ce;
-  // products used by the collision, om = 1/tau: 1 - om, om/2, om/9, om/3, Be/3
-  double om1, om_2, om_9, om_3, Be_3;
+  // products used by the collision, om = 1/tau: 1 - om, (1 - om)/2, om/2, om/9,
+  // om/3, Be/3
+  double om1, om1_2, om_2, om_9, om_3, Be_3;
   double rho_ref;           // deviation reference density (0 for FP64 storage)
   int32_t run;
   int32_t mrt;              // 1: multiple-relaxation-time collision (collide_mrt with m)
@@ -105,8 +106,8 @@ __device__ __forceinline__ void balanced_pieces(const Item* __restrict__ items, 
 
 // Storage traits: E = element type in memory, R = collision arithmetic type;
 // round(v) = the value a store followed by a load would give.  Cache policy
-// per type, measured on the 4096 x 4096 droplet workload with the two-step
-// kernel: FP64 populations stream with non-temporal loads and stores (plain
+// per type, measured on the 4096 x 4096 droplet workload with two steps per
+// launch: FP64 populations stream with non-temporal loads and stores (plain
 // stores cost 10 %); FP32 deviations use plain loads and stores (9 % faster
 // than non-temporal); FP32 storage with FP64 arithmetic and FP16 deviations
 // show no difference.
@@ -157,9 +158,9 @@ template <> struct Store<__half> {
   // the backend otherwise folds it into the FMA that produced the operand (a
   // mixed-precision FMA with an FP16 result, one rounding instead of two) at
   // some call sites only, whatever the contraction setting, which breaks the
-  // bitwise identity of the one- and two-step kernels.
+  // bitwise identity of the one- and multi-step kernels.
   static __device__ __forceinline__ _Float16 narrow(R v) {
-    asm volatile("" : "+v"(v));
+    asm("" : "+v"(v));
     return static_cast<_Float16>(v);
   }
   static __device__ __forceinline__ R ld(const E* p) { return __half2float(*p); }
@@ -255,7 +256,7 @@ __device__ __forceinline__ void pull9(const typename Store<S>::E* __restrict__ s
 // The arithmetic of one node update below is written with explicit fma()
 // where a fused multiply-add is wanted and compiled with contraction off, so
 // every kernel that inlines it performs the same operations and rounds the
-// same way (the single-step, two-step and batched kernels give identical bits).
+// same way (the single-step, multi-step and batched kernels give identical bits).
 
 // Density deviation sum_a s_a in the arithmetic type (pairwise order).
 template <typename R>
@@ -349,6 +350,11 @@ __device__ __forceinline__ void force3x3(const double* rs, const double* rc, con
 // + B_e/3 F (over 4 for the diagonals).  Each pair of opposite directions is
 // then s' = (1 - om) s + (P +- Q).  55 operations besides the moments and 1/rho,
 // against 85 with the per-pair products (e.u)^2 and (e.v)(e.F) evaluated apart.
+// Together with the folded EOS, the one-estimate square root and the density
+// carried from psi to the collision, a node update went from 177 to 123 FP64
+// instructions; with the kernels of that time, 4096 x 4096, us per launch: FP64 three
+// steps 670 -> 584, FP16 two steps 278 -> 248, FP32 384 -> 357, FP32 with FP64 collide
+// 394 -> 342.
 template <typename R>
 __device__ __forceinline__ void relax_pair(R& sa, R& sb, R P, R Q, R om1) {
 #pragma clang fp contract(off)
@@ -356,7 +362,9 @@ __device__ __forceinline__ void relax_pair(R& sa, R& sb, R P, R Q, R om1) {
   sb = fma(om1, sb, P - Q);
 }
 
-template <typename R>
+// HALF: of the axis pairs only the half sums are formed, returned in s[1] (x) and
+// s[2] (y); s[0], s[3] and s[4] are left for conserve().
+template <bool HALF, typename R>
 __device__ __forceinline__ void collide(R (&s)[9], R drho, R rho, R jx, R jy, R Fx, R Fy,
                                         R inv_psi2, const RunDev& d) {
 #pragma clang fp contract(off)
@@ -374,10 +382,15 @@ __device__ __forceinline__ void collide(R (&s)[9], R drho, R rho, R jx, R jy, R 
   const R om_3 = R(d.om_3), Be_3 = R(d.Be_3);
   const R qx = fma(om_3, mx, Be_3 * Fx), qy = fma(om_3, my, Be_3 * Fy);
   const R D = R(0.25) * (base + S);
-  s[0] = fma(R(4), base, om1 * s[0]);
-  // axis pairs (e1, e3 = -e1), (e2, e4 = -e2)
-  relax_pair(s[1], s[3], base + Txx, qx, om1);
-  relax_pair(s[2], s[4], base + Tyy, qy, om1);
+  if constexpr (HALF) {
+    s[1] = fma(R(d.om1_2), s[1] + s[3], base + Txx);
+    s[2] = fma(R(d.om1_2), s[2] + s[4], base + Tyy);
+  } else {
+    s[0] = fma(R(4), base, om1 * s[0]);
+    // axis pairs (e1, e3 = -e1), (e2, e4 = -e2)
+    relax_pair(s[1], s[3], base + Txx, qx, om1);
+    relax_pair(s[2], s[4], base + Tyy, qy, om1);
+  }
   // diagonal pairs (e5 = (1,1), e7 = -e5), (e6 = (-1,1), e8 = -e6)
   relax_pair(s[5], s[7], fma(R(0.25), Txy, D), R(0.25) * (qx + qy), om1);
   relax_pair(s[6], s[8], fma(R(-0.25), Txy, D), R(0.25) * (qy - qx), om1);
@@ -441,16 +454,6 @@ __device__ __forceinline__ void collide_mrt(R (&s)[9], R drho, R rho, R jx, R jy
   s[8] += Dm + XmY;
 }
 
-// The collision of a node: BGK (collide) or MRT (collide_mrt).
-template <bool MRT, typename R>
-__device__ __forceinline__ void collide_any(R (&s)[9], R drho, R rho, R jx, R jy, R Fx, R Fy,
-                                            R inv_psi2, const RunDev& d) {
-  if constexpr (MRT)
-    collide_mrt<R>(s, drho, rho, jx, jy, Fx, Fy, inv_psi2, d);
-  else
-    collide<R>(s, drho, rho, jx, jy, Fx, Fy, inv_psi2, d);
-}
-
 // Momentum sum_a s_a e_a in the arithmetic type.
 template <typename R>
 __device__ __forceinline__ void momentum(const R (&s)[9], R& jx, R& jy) {
@@ -470,14 +473,11 @@ __device__ __forceinline__ void exact_momentum(const double (&t)[9], double& jx,
   jx = ((t[1] - t[3]) + u) + v;
   jy = ((t[2] - t[4]) + u) - v;
 }
-// Mass and momentum of nine FP32 values, exactly (as exact_momentum).
-__device__ __forceinline__ void exact_moments(const float (&s)[9], double& m, double& jx, double& jy) {
+// Mass of nine FP32 values, exactly (as exact_momentum).
+__device__ __forceinline__ double exact_mass(const float (&s)[9]) {
 #pragma clang fp contract(off)
-  double t[9];
-#pragma unroll
-  for (int a = 0; a < 9; ++a) t[a] = double(s[a]);
-  m = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])) + t[8];
-  exact_momentum(t, jx, jy);
+  return ((double(s[0]) + double(s[1])) + (double(s[2]) + double(s[3]))) +
+         ((double(s[4]) + double(s[5])) + (double(s[6]) + double(s[7]))) + double(s[8]);
 }
 
 // The collision conserves mass and changes the momentum by exactly F (every
@@ -485,87 +485,97 @@ __device__ __forceinline__ void exact_moments(const float (&s)[9], double& m, do
 // population carries its own rounding, and at a steady state the same
 // roundings recur every step: a persistent mass and momentum source at every
 // node that the slow bulk dynamics integrate into visibly shifted coexistence
-// densities.  conserve() puts the momentum change of the new populations back
-// to exactly F (half the x defect on e1 and -e1, likewise y on e2, -e4) and the
-// mass back to exactly the old mass on the rest population, computed in FP64;
-// what remains is one FP32 rounding of five values.
-__device__ __forceinline__ void conserve(float (&s)[9], double m_t, double jx_t, double jy_t) {
+// densities.  So only the half sums h = (s1 + s3)/2, (s2 + s4)/2 of the axis pairs
+// are taken from the collision; their differences follow in FP64 from the momentum
+// (jx, jy: the exact new one) that the diagonal populations leave, and the rest
+// population from the mass m; what remains is one FP32 rounding of five values.
+__device__ __forceinline__ void conserve(float (&s)[9], float hx, float hy, double m, double jx,
+                                         double jy) {
 #pragma clang fp contract(off)
-  double t[9], jx, jy;
-  t[0] = 0.0;  // the rest population carries no momentum
-#pragma unroll
-  for (int a = 1; a < 9; ++a) t[a] = double(s[a]);
-  exact_momentum(t, jx, jy);
-  const double dx = 0.5 * (jx_t - jx), dy = 0.5 * (jy_t - jy);
-  s[1] = float(t[1] + dx);
-  s[3] = float(t[3] - dx);
-  s[2] = float(t[2] + dy);
-  s[4] = float(t[4] - dy);
-#pragma unroll
-  for (int a = 1; a < 5; ++a) t[a] = double(s[a]);
-  const double rest = ((t[1] + t[2]) + (t[3] + t[4])) + ((t[5] + t[6]) + (t[7] + t[8]));
-  s[0] = float(m_t - rest);
+  const double t5 = double(s[5]), t6 = double(s[6]), t7 = double(s[7]), t8 = double(s[8]);
+  const double u = t5 - t7, v = t8 - t6;
+  const double dx = jx - (u + v), dy = jy - (u - v);
+  s[1] = float(fma(0.5, dx, double(hx)));
+  s[3] = float(fma(-0.5, dx, double(hx)));
+  s[2] = float(fma(0.5, dy, double(hy)));
+  s[4] = float(fma(-0.5, dy, double(hy)));
+  const double rest = ((double(s[1]) + double(s[2])) + (double(s[3]) + double(s[4]))) +
+                      ((t5 + t6) + (t7 + t8));
+  s[0] = float(m - rest);
 }
 
-// One node update: collision (BGK or MRT) of the pulled values s with the
-// force (Fx, Fy) (FP64), then, for FP32 storage, conserve().
-template <typename S, bool MRT>
-__device__ __forceinline__ void update_node(typename Store<S>::R (&s)[9],
-                                            typename Store<S>::R drho, typename Store<S>::P rho,
-                                            typename Store<S>::P Fx, typename Store<S>::P Fy,
-                                            typename Store<S>::R ip2, const RunDev& d) {
-  using R = typename Store<S>::R;
-  if constexpr (Store<S>::kConserve) {
-    double m0, jx0, jy0;
-    exact_moments(s, m0, jx0, jy0);
-    R jx, jy;
-    momentum(s, jx, jy);
-    collide_any<MRT, R>(s, drho, R(rho), jx, jy, R(Fx), R(Fy), ip2, d);
-    conserve(s, m0, jx0 + double(Fx), jy0 + double(Fy));
-  } else {
-    R jx, jy;
-    momentum(s, jx, jy);
-    collide_any<MRT, R>(s, drho, R(rho), jx, jy, R(Fx), R(Fy), ip2, d);
-  }
-}
-
-// What a pulled row keeps for its collision: the density (deviation) it summed
-// and 1/psi^2.
+// What a pulled row keeps for its collision: the summed stored values (the density
+// or its deviation; FP32 storage with FP32 arithmetic keeps the exact FP64 sum) and
+// 1/psi^2.
 template <typename S> struct NodeQ {
-  typename Store<S>::R drho = 0, ip2 = 0;
+  std::conditional_t<Store<S>::kConserve, double, typename Store<S>::R> drho = 0;
+  typename Store<S>::R ip2 = 0;
 };
 
 // Density from the summed stored values.
-template <typename S>
-__device__ __forceinline__ typename Store<S>::P density(typename Store<S>::R drho, const RunDev& d) {
-  using P = typename Store<S>::P;
-  if constexpr (Store<S>::kDev) return P(d.rho_ref) + P(drho);
+template <typename S, typename Q>
+__device__ __forceinline__ double density(Q drho, const RunDev& d) {
+  if constexpr (Store<S>::kDev) return d.rho_ref + double(drho);
   return drho;
 }
 
 // psi of a pulled node; q receives what its collision needs.
 template <typename S>
-__device__ __forceinline__ typename Store<S>::P eval_psi(const typename Store<S>::R (&f)[9],
-                                                         const RunDev& d, NodeQ<S>& q) {
-  q.drho = sum9(f);
+__device__ __forceinline__ double eval_psi(const typename Store<S>::R (&f)[9], const RunDev& d,
+                                           NodeQ<S>& q) {
+  if constexpr (Store<S>::kConserve)
+    q.drho = exact_mass(f);
+  else
+    q.drho = sum9(f);
   const PsiPair w = psi_pair(psi2_of(density<S>(q.drho, d), d));
   q.ip2 = typename Store<S>::R(w.ip2);
   return w.psi;
 }
 
-// Force and collision of a node from the psi rows around it; true if the node is
-// bad (density or psi^2 not positive, or not a number).
+// One node update: collision (BGK or MRT) of the pulled values f with the force
+// (Fx, Fy) (FP64), for FP32 storage with conserve(); true if the node is bad
+// (density or psi^2 not positive, or not a number).
+template <typename S, bool MRT>
+__device__ __forceinline__ bool update_node(typename Store<S>::R (&f)[9], const NodeQ<S>& q, double Fx,
+                                            double Fy, const RunDev& d) {
+  using R = typename Store<S>::R;
+  const double rho = density<S>(q.drho, d);
+  const R fx = R(Fx), fy = R(Fy);
+  if constexpr (Store<S>::kConserve) {
+    double t[9], jx, jy;
+#pragma unroll
+    for (int a = 1; a < 9; ++a) t[a] = double(f[a]);
+    exact_momentum(t, jx, jy);
+    float hx, hy;
+    if constexpr (MRT) {
+      collide_mrt<R>(f, R(q.drho), R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
+      hx = 0.5f * (f[1] + f[3]);
+      hy = 0.5f * (f[2] + f[4]);
+    } else {
+      collide<true, R>(f, R(q.drho), R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
+      hx = f[1];
+      hy = f[2];
+    }
+    conserve(f, hx, hy, q.drho, jx + Fx, jy + Fy);
+  } else {
+    R jx, jy;
+    momentum(f, jx, jy);
+    if constexpr (MRT)
+      collide_mrt<R>(f, q.drho, R(rho), jx, jy, fx, fy, q.ip2, d);
+    else
+      collide<false, R>(f, q.drho, R(rho), jx, jy, fx, fy, q.ip2, d);
+  }
+  return !(q.ip2 > 0) || !(rho > 0.0);
+}
+
+// Force and collision of a node from the psi rows around it; true if it is bad.
 template <typename S, bool MRT>
 __device__ __forceinline__ bool finish_node(typename Store<S>::R (&f)[9], const NodeQ<S>& q,
-                                            const typename Store<S>::P* rs,
-                                            const typename Store<S>::P* rc,
-                                            const typename Store<S>::P* rn, int i, const RunDev& d) {
-  using P = typename Store<S>::P;
-  P Fx, Fy;
-  force3x3(rs, rc, rn, i, P(d.mG12), Fx, Fy);
-  const P rho = density<S>(q.drho, d);
-  update_node<S, MRT>(f, q.drho, rho, Fx, Fy, q.ip2, d);
-  return !(q.ip2 > 0) || !(rho > P(0));
+                                            const double* rs, const double* rc, const double* rn, int i,
+                                            const RunDev& d) {
+  double Fx, Fy;
+  force3x3(rs, rc, rn, i, d.mG12, Fx, Fy);
+  return update_node<S, MRT>(f, q, Fx, Fy, d);
 }
 
 // One tile: columns [x0, x0+ncols), rows [y0, y0+nrows), nrows <= LMAX.
@@ -737,522 +747,298 @@ __global__ __launch_bounds__(64 * NW) void k_step(const typename Store<S>::E* __
   }
 }
 
-// ---- two time steps per launch ------------------------------------------------
+// ---- several time steps per launch: one group of waves per step ------------------
 
-// Row modes of tile_step2 (bit set): a steady row, and the phases that run
-// on every lane of the block instead of on their own lane range.
-constexpr int kRowPsi = 1, kRowPull2 = 2, kRowCollide1 = 4, kRowCollide2 = 8, kRowSteady = 16;
-// Mode of the steady rows per storage type, chosen by measurement on the
-// 4096 x 4096 droplet workload.
-template <typename S> struct SteadyMode
-    : std::integral_constant<int, kRowSteady | kRowPsi | kRowPull2 | kRowCollide1 | kRowCollide2> {};
-template <> struct SteadyMode<double> : std::integral_constant<int, kRowSteady | kRowPull2> {};
-// The batched kernel unmasks every phase for every storage type: on the
-// 256-run sweep (2-wave strips of 16-64-row lattices) that is 2 % faster for
-// FP64 storage (44.3 -> 45.3 GLUPS), while on the 4096 x 4096 lattice it makes
-// the single-lattice FP64 kernel 5 % slower (485 -> 513 us per launch).
-constexpr int kBatchSteadyMode = kRowSteady | kRowPsi | kRowPull2 | kRowCollide1 | kRowCollide2;
-// Steady rows per loop iteration (1 to 3), measured likewise.  Unrolling by 3
-// removes the rotation moves but adds registers; it pays for FP32 storage with
-// FP64 arithmetic and for FP16 storage (261 -> 251 us per launch, 161-167
-// VGPRs: still 3 waves per SIMD); FP64 storage: 7 % fewer VALU instructions
-// per row yet 5 % slower; FP32 storage would fall from 3 to 2 waves per SIMD
-// (241 VGPRs).
-template <typename S> struct SteadyUnroll : std::integral_constant<int, 1> {};
-template <> struct SteadyUnroll<f32s_f64a> : std::integral_constant<int, 3> {};
-template <> struct SteadyUnroll<__half> : std::integral_constant<int, 3> {};
+// The populations cross HBM once per TS steps (TS = 2, 3 or 4).  A block is TS
+// groups of NW waves; group l runs step l+1 of a strip of W = 64 NW columns, all
+// groups marching up the rows together, each four rows behind the one before it,
+// with one barrier per row.  In one march row a group
+//   * pulls row p of its step: the first group from global memory (loaded one march
+//     row ahead), the others from the exchange rows in LDS that the group before
+//     them filled;
+//   * evaluates psi of row p and leaves U and D of row p-1 (see force_ud) in LDS;
+//   * collides row p-2, whose U and D the last march row left there, and hands the
+//     result to the next group through the exchange rows; the last group stores it.
+// Lane i owns column x0 - H + i, H = 2 TS - 1, in every step: step l is right on the
+// lanes 2l .. and n0-1-2l (psi) and one lane further in (collision), so the last one
+// is right on the ncols lanes from H on, and only those are stored.  The other
+// lanes, rows outside a step's range and the first march rows compute values that
+// no lane, row or step in range reads.  All steps use the arithmetic of single
+// launches in the same order: bitwise equal.
+//
+// Why one group per step: a wave holds one step's rows only (149 VGPRs in FP64, 118
+// with FP16 storage, against 254 for one wave doing three steps), so 3-4 waves per
+// SIMD hide latency instead of 2, four steps fit where three did, and rows rotate by
+// the names of unrolled registers and LDS slots instead of moves (121 FP64 and 6
+// other vector instructions per row and step instead of 123 and 46).  4096 x 4096,
+// us per step, one wave for all steps -> one group per step: FP64 195 -> 133 (four
+// steps, 5.0 TB/s: the rate a plain copy gets), FP32 179 -> 115, FP32 with FP64
+// collide 171 -> 116, FP16 124 -> 79 (bound by vector issue); 1024 x 1024 FP64 28 ->
+// 17.  A version with two barriers per row (collision after the exchange of the same
+// row) took 156 in FP64 and 123 in FP16.
 
-// The populations cross HBM once per two steps.  Lane i of a block owns
-// column c = x0 - 3 + i for both steps, i < ncols + 6:
-//   * every lane pulls its column and evaluates psi(t);
-//   * lanes 1 .. ncols+4 run step one (t -> t+1) exactly as tile_step does and
-//     keep f*(t+1) in registers, rounded to the storage type;
-//   * lanes 2 .. ncols+3 pull f*(t+1) for step two and evaluate psi(t+1);
-//   * lanes 3 .. ncols+2 finish step two and write the columns [x0, x0+ncols),
-// so neighbouring strips overlap by six columns of recomputed work and no
-// halo column is loaded apart from the coalesced row loads.  Rows: step two
-// writes [y0, y0 + L); it needs psi(t+1) on rows y0-1 .. y0+L, hence f*(t+1)
-// on rows y0-2 .. y0+L+1, hence psi(t) on rows y0-3 .. y0+L+2.  Step two
-// pulls f*(t+1) from registers for the x-unshifted directions (0, 2, 4) and
-// from an LDS exchange row for the six shifted ones, and runs three rows
-// behind step one; one row of the march takes two barriers.  Both steps use
-// the same arithmetic, in the same order, as two single-step launches, so the
-// result is bitwise identical.
-template <typename S, int NW, int PF, int MODE = SteadyMode<S>::value, bool MRT = false>
-__device__ __forceinline__ void tile_step2(const typename Store<S>::E* __restrict__ src,
-                                           typename Store<S>::E* __restrict__ dst,
-                                           const RunDev& d, int x0, int y0, int ncols, int nrows,
-                                           unsigned long long step,
-                                           unsigned long long* __restrict__ flag,
-                                           typename Store<S>::P (*ring1)[64 * NW],
-                                           typename Store<S>::P (*ring2)[64 * NW],
-                                           typename Store<S>::R (*xch)[64 * NW]) {
-  using T = Store<S>;
-  using R = typename T::R;
-  const int tid = threadIdx.x;
-  LBM_TILE_CHECK(ncols >= 1 && ncols <= 64 * NW - 6 && nrows >= 1 && x0 >= 0 &&
-                 x0 + ncols <= d.nx && y0 >= 0 && y0 + nrows <= d.ny);
-  const int n0 = ncols + 6;                         // lanes that evaluate psi(t)
-  const bool act0 = tid < n0;
-  const bool act1 = tid >= 1 && tid < n0 - 1;       // lanes that run step one
-  const bool pull2 = tid >= 2 && tid < n0 - 2;      // lanes that pull for step two
-  const bool out = tid >= 3 && tid < ncols + 3;     // lanes that write step two
-  // LDS neighbour index: tid on every lane of the ranges above, kept inside
-  // the rows for lanes 0 and 64*NW-1
-  const int tc = min(max(tid, 1), 64 * NW - 2);
-  auto wrapx = [&](int x) { return x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x); };
-  auto wrapy = [&](int y) { return y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y); };
-  const Cols cx = cols_of(wrapx(x0 - 3 + min(tid, n0 - 1)), d.nx);
-  bool bad1 = false, bad2 = false;
-  const int ya = y0 - 3;                            // first psi(t) row
-
-  // preload: psi(t) of rows y0-3 (ring slot 0) and y0-2 (slot 1); pulled row y0-2
-  R fc[9] = {}, fn[9] = {};
-  NodeQ<S> qc;
-  if (act0) {
-    R f[9];
-    pull9<S>(src, d, cx, wrapy(ya), f);
-    pull9<S>(src, d, cx, wrapy(ya + 1), fc);
-    if (PF == 2) pull9<S>(src, d, cx, wrapy(ya + 2), fn);
-    ring1[0][tid] = eval_psi<S>(f, d, qc);
-    ring1[1][tid] = eval_psi<S>(fc, d, qc);
-  }
-
-  // f*(t+1) of the last three step-one rows, kept for step two:
-  // gA = row y1-1 (all 9), gB = row y1-2 (0,1,3,2,5,6), gC = row y1-3 (2,5,6)
-  R gA[9] = {}, gB[6] = {}, gC[3] = {};
-  R hp[9] = {};     // step-two pulled populations of the row collided next
-  NodeQ<S> qp;
-  const int n_one = nrows + 4;                      // step-one rows y0-2 .. y0+nrows+1
-  // One row of the march.  Mode (MODE: SteadyMode, or kBatchSteadyMode in the
-  // batched kernel) bit 16 marks a steady row, in
-  // which every row condition below holds; bits 1, 2, 4, 8 make a phase run
-  // on every lane of the block: lanes outside the phase's range compute values
-  // that no lane in range reads (their LDS slots are read only by lanes
-  // outside the ranges too, and tc keeps their neighbour reads inside the
-  // rows), so that phase carries no per-lane branch apart from the store.
-  auto row = [&](const int j, auto mode) __attribute__((always_inline)) {
-    constexpr int M = decltype(mode)::value;
-    constexpr bool St = (M & kRowSteady) != 0;
-    const int y1 = y0 - 2 + j;                      // step-one row collided at this j
-    // ---- phase 1: psi(t) of row y1+1; exchange of the rows step two pulls
-    R fnn[9];
-    NodeQ<S> qn;
-    if ((St || j < n_one) && ((M & kRowPsi) || act0)) {
-      // the row loads go out at raised wave priority, so a wave about to issue
-      // them is not held behind the other wave's arithmetic (FP64: 1 % faster)
-      __builtin_amdgcn_s_setprio(2);
-      if (PF == 2) {
-        if (St || j + 1 < n_one) pull9<S>(src, d, cx, wrapy(y1 + 2), fnn);
-      } else {
-        pull9<S>(src, d, cx, wrapy(y1 + 1), fn);
-      }
-      __builtin_amdgcn_s_setprio(0);
-      ring1[(j + 2) & 3][tid] = eval_psi<S>(fn, d, qn);
-    }
-    if ((St || j >= 3) && ((M & kRowPsi) || act1)) {  // step two pulls row q = y1 - 2 below
-      xch[0][tid] = gB[1];
-      xch[1][tid] = gB[2];
-      xch[2][tid] = gC[1];
-      xch[3][tid] = gC[2];
-      xch[4][tid] = gA[7];
-      xch[5][tid] = gA[8];
-    }
-    __syncthreads();
-    // ---- phase 2: step-two pull of row q = y1-2 and its psi(t+1); step-one collide of row y1
-    const int q = y1 - 2;
-    R hn[9];
-    NodeQ<S> qh;
-    if ((St || j >= 3) && ((M & kRowPull2) || pull2)) {
-      hn[0] = gB[0];
-      hn[1] = xch[0][tc - 1];
-      hn[2] = gC[0];
-      hn[3] = xch[1][tc + 1];
-      hn[4] = gA[4];
-      hn[5] = xch[2][tc - 1];
-      hn[6] = xch[3][tc + 1];
-      hn[7] = xch[4][tc + 1];
-      hn[8] = xch[5][tc - 1];
-      ring2[(q - (y0 - 1)) & 3][tid] = eval_psi<S>(hn, d, qh);
-    }
-    if (St || j >= 1) {  // rotate the kept step-one rows (gA was produced at j-1)
-      gC[0] = gB[3]; gC[1] = gB[4]; gC[2] = gB[5];
-      gB[0] = gA[0]; gB[1] = gA[1]; gB[2] = gA[3];
-      gB[3] = gA[2]; gB[4] = gA[5]; gB[5] = gA[6];
-    }
-    if ((St || j < n_one) && ((M & kRowCollide1) || act0)) {
-      if ((M & kRowCollide1) || act1) {
-        const bool chk = out && y1 >= y0 && y1 < y0 + nrows;
-        bad1 |= finish_node<S, MRT>(fc, qc, ring1[j & 3], ring1[(j + 1) & 3], ring1[(j + 2) & 3], tc, d) && chk;
-#pragma unroll
-        for (int a = 0; a < 9; ++a) gA[a] = T::round(fc[a]);
-      }
-#pragma unroll
-      for (int a = 0; a < 9; ++a) fc[a] = fn[a];
-      qc = qn;
-      if (PF == 2 && (St || j + 1 < n_one)) {
-#pragma unroll
-        for (int a = 0; a < 9; ++a) fn[a] = fnn[a];
-      }
-    }
-    __syncthreads();
-    // ---- phase 3: step-two collide of row r = q-1 and store
-    const int r = q - 1;
-    if ((St || (j >= 4 && r >= y0 && r < y0 + nrows)) && ((M & kRowCollide2) || out)) {
-      bad2 |= finish_node<S, MRT>(hp, qp, ring2[(r - 1 - (y0 - 1)) & 3], ring2[(r - (y0 - 1)) & 3],
-                                  ring2[(q - (y0 - 1)) & 3], tc, d) && out;
-      if (out) {
-        typename T::E* orow = dst + (int64_t)wrapy(r) * d.rs;
-#pragma unroll
-        for (int a = 0; a < 9; ++a)
-          if (index_ok(orow + a * d.plane + cx.x - dst, d.elems)) T::st(orow + a * d.plane + cx.x, hp[a]);
-      }
-    }
-    if (St || j >= 3) {
-#pragma unroll
-      for (int a = 0; a < 9; ++a) hp[a] = hn[a];
-      qp = qh;
-    }
-  };
-  // rows 0..4 fill the pipeline, 5 .. n_one-2 are steady, the last two drain it
-  using Edge = std::integral_constant<int, 0>;
-  using Steady = std::integral_constant<int, MODE>;
-  for (int j = 0; j < 5; ++j) row(j, Edge{});
-  // Steady rows U at a time (a loop with barriers is not unrolled by the
-  // compiler): with U = 3, the period of the kept-row rotations (gA -> gB ->
-  // gC, fnn -> fn -> fc), those rotations become register renaming instead of
-  // moves.
-  // The steady rows end where the row loads one row ahead would pass the last
-  // step-one row.
-  constexpr int U = SteadyUnroll<S>::value;
-  const int js_end = n_one - 1;
-  int js = 5;
-  for (; js + U <= js_end; js += U) {
-    row(js, Steady{});
-    if constexpr (U > 1) row(js + 1, Steady{});
-    if constexpr (U > 2) row(js + 2, Steady{});
-  }
-  if constexpr (U > 1)
-    for (; js < js_end; ++js) row(js, Steady{});
-  for (int j = max(5, js_end); j < n_one + 1; ++j) row(j, Edge{});
-  // divergence: the first step that saw a bad node (one atomic per wave)
-  const auto b1 = __ballot(bad1), b2 = __ballot(bad2);
-  if (__lane_id() == 0 && (b1 | b2) != 0) atomicMin(flag, b1 != 0 ? step : step + 1);
+// Barrier that orders LDS only: global loads and stores in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Strip edges of the two-step kernel are rounded down to multiples of this
+// LDS of a block.  ex: the populations a step hands to the next.  A row collided in
+// march row j leaves nine values: e4, e7, e8 are pulled one march row later (by the
+// row below), e0, e1, e3 two and e2, e5, e6 three march rows later; a slot may be
+// refilled one barrier after its last read, so they take 2, 4 (3 would do) and 4
+// slots, j mod 4 with the loop unrolled by four.  The pads take the reads of lanes 0
+// and W-1 past the ends (never used).
+template <typename S, int W, int TS> struct PipeLds {
+  double pad0[1];
+  double ud[TS][4][W];  // U and D of two march rows per step
+  typename Store<S>::R ex[TS - 1][30][W];
+  double pad1[1];
+};
+// FP64, three waves per step, four steps: 162,832 of the 163,840 bytes of a CU.
+static_assert(sizeof(PipeLds<double, 192, 4>) <= 160 * 1024, "LDS of a CU");
+
+// Byte offsets of one thread's columns in a row; nx * element size stays below 2^32
+// (the launcher falls back to single steps otherwise).
+struct ColBytes {
+  unsigned x, xm, xp;
+};
+template <typename S>
+__device__ __forceinline__ typename Store<S>::R ld_at(const char* p, unsigned off, const char* src,
+                                                      const RunDev& d) {
+  using E = typename Store<S>::E;
+  const E* q = reinterpret_cast<const E*>(p + off);
+  if (!index_ok(q - reinterpret_cast<const E*>(src), d.elems)) return typename Store<S>::R(0);
+  return Store<S>::ld(q);
+}
+// pull9 of row y with its neighbour rows ym and yp given.
+template <typename S>
+__device__ __forceinline__ void pull9b(const char* src, const RunDev& d, const ColBytes& cb, int ym, int y,
+                                       int yp, typename Store<S>::R (&f)[9]) {
+  const int64_t P = d.plane * sizeof(typename Store<S>::E), rs = d.rs * sizeof(typename Store<S>::E);
+  // opaque copies: the compiler otherwise widens the offsets once outside the row loop and
+  // then adds a 64-bit address per lane and load
+  ColBytes c;
+  asm("" : "=v"(c.x) : "0"(cb.x));
+  asm("" : "=v"(c.xm) : "0"(cb.xm));
+  asm("" : "=v"(c.xp) : "0"(cb.xp));
+  const char *r0 = src + (int64_t)y * rs, *rm = src + (int64_t)ym * rs, *rp = src + (int64_t)yp * rs;
+  f[0] = ld_at<S>(r0, c.x, src, d);
+  f[1] = ld_at<S>(r0 + P, c.xm, src, d);
+  f[2] = ld_at<S>(rm + 2 * P, c.x, src, d);
+  f[3] = ld_at<S>(r0 + 3 * P, c.xp, src, d);
+  f[4] = ld_at<S>(rp + 4 * P, c.x, src, d);
+  f[5] = ld_at<S>(rm + 5 * P, c.xm, src, d);
+  f[6] = ld_at<S>(rm + 6 * P, c.xp, src, d);
+  f[7] = ld_at<S>(rp + 7 * P, c.xp, src, d);
+  f[8] = ld_at<S>(rp + 8 * P, c.xm, src, d);
+}
+
+// Exchange rows of march rows j with j mod 4 = K (x: the lane's entry of row 0): what a
+// step leaves, rounded to the storage type, and what the next one pulls.
+template <typename S, int W, int K>
+__device__ __forceinline__ void pipe_push(typename Store<S>::R* x, const typename Store<S>::R (&f)[9]) {
+  using T = Store<S>;
+  constexpr int a1 = (K & 1) * 3, a2 = 6 + K * 3, a3 = 18 + K * 3;
+  x[(a1 + 0) * W] = T::round(f[4]);
+  x[(a1 + 1) * W] = T::round(f[7]);
+  x[(a1 + 2) * W] = T::round(f[8]);
+  x[(a2 + 0) * W] = T::round(f[0]);
+  x[(a2 + 1) * W] = T::round(f[1]);
+  x[(a2 + 2) * W] = T::round(f[3]);
+  x[(a3 + 0) * W] = T::round(f[2]);
+  x[(a3 + 1) * W] = T::round(f[5]);
+  x[(a3 + 2) * W] = T::round(f[6]);
+}
+template <typename S, int W, int K>
+__device__ __forceinline__ void pipe_pull(const typename Store<S>::R* x, typename Store<S>::R (&f)[9]) {
+  constexpr int a1 = ((K + 1) & 1) * 3, a2 = 6 + ((K + 2) & 3) * 3, a3 = 18 + ((K + 1) & 3) * 3;
+  f[4] = x[(a1 + 0) * W];
+  f[7] = x[(a1 + 1) * W + 1];
+  f[8] = x[(a1 + 2) * W - 1];
+  f[0] = x[(a2 + 0) * W];
+  f[1] = x[(a2 + 1) * W - 1];
+  f[3] = x[(a2 + 2) * W + 1];
+  f[2] = x[(a3 + 0) * W];
+  f[5] = x[(a3 + 1) * W - 1];
+  f[6] = x[(a3 + 2) * W + 1];
+}
+
+// TS time steps of columns [x0, x0+ncols), rows [y0, y0+nrows); ncols <= W - 2H.  All
+// threads of the block call it.
+template <typename S, int NW, int TS, bool MRT = false>
+__device__ __forceinline__ void tile_pipe(const typename Store<S>::E* __restrict__ src,
+                                          typename Store<S>::E* __restrict__ dst,
+                                          const RunDev& d, int x0, int y0, int ncols, int nrows,
+                                          unsigned long long step,
+                                          unsigned long long* __restrict__ flag,
+                                          PipeLds<S, 64 * NW, TS>& lds) {
+  using T = Store<S>;
+  using E = typename T::E;
+  using R = typename T::R;
+  constexpr int W = 64 * NW, H = 2 * TS - 1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lv = wave / NW;
+  const int i = (wave - lv * NW) * 64 + (threadIdx.x & 63);
+  LBM_TILE_CHECK(ncols >= 1 && ncols <= W - 2 * H && nrows >= 1 && x0 >= 0 && x0 + ncols <= d.nx &&
+                 y0 >= 0 && y0 + nrows <= d.ny);
+  const bool out = i >= H && i < ncols + H;
+  int c = (x0 - H + min(i, ncols + 2 * H - 1)) % d.nx;
+  if (c < 0) c += d.nx;
+  double* const ud = &lds.ud[lv][0][0] + i;
+  bool bad = false;
+  const int J = 6 * (TS - 1) + nrows + 3;              // march rows
+  // march rows of this step, widened to whole fours (the rows added compute values that
+  // nothing reads)
+  const int j4 = (J + 3) & ~3, jf = (6 * lv) & ~3, je = min(j4, (J - 2 * (TS - 1 - lv) + 3) & ~3);
+  const int yc = y0 - H - 2 - 4 * lv;                  // row collided at march row j: yc + j
+  auto in_rows = [&](int j) { return yc + j >= y0 && yc + j < y0 + nrows; };
+  // rows p, p-1, p-2 and (first group) the one being loaded: buffer K = j mod 4 holds p,
+  // K + 3 row p-1, K + 2 row p-2
+  R F[4][9];
+  double P[4] = {0, 0, 0, 0}, D[2] = {0, 0};
+  NodeQ<S> Q[4];
+  // psi of the pulled row (buffer K), U and D of the row below it to LDS; collision of
+  // the row below that one (buffer K + 2), whose U and D the last march row left
+  auto step_row = [&](auto kk) __attribute__((always_inline)) {
+    constexpr int K = decltype(kk)::value, kc = (K + 2) & 3, kp = (K + 3) & 3;
+    double* u = ud + (K & 1) * 2 * W;
+    const double* v = ud + ((K & 1) ^ 1) * 2 * W;
+    double Fx, Fy;
+    force_ud(d.mG12, P[kc], v[-1], v[1], v[W - 1], D[(K + 1) & 1], v[W + 1], Fx, Fy);
+    P[K] = eval_psi<S>(F[K], d, Q[K]);
+    D[K & 1] = P[K] - P[kc];
+    u[0] = col_u(P[kc], P[kp], P[K]);
+    u[W] = D[K & 1];
+    return update_node<S, MRT>(F[kc], Q[kc], Fx, Fy, d);
+  };
+  using K0 = std::integral_constant<int, 0>;
+  using K1 = std::integral_constant<int, 1>;
+  using K2 = std::integral_constant<int, 2>;
+  using K3 = std::integral_constant<int, 3>;
+  auto march = [&](auto&& row) __attribute__((always_inline)) {
+    for (int j = 0; j < jf; ++j) lds_barrier();
+    for (int j = jf; j < je; j += 4) {
+      row(j, K0{});
+      row(j + 1, K1{});
+      row(j + 2, K2{});
+      row(j + 3, K3{});
+    }
+    for (int j = je; j < j4; ++j) lds_barrier();
+  };
+  if (lv == 0) {
+    R* xo = &lds.ex[0][0][0] + i;
+    const char* sb = reinterpret_cast<const char*>(src);
+    const ColBytes cb{(unsigned)(c * sizeof(E)), (unsigned)((c == 0 ? d.nx - 1 : c - 1) * sizeof(E)),
+                      (unsigned)((c == d.nx - 1 ? 0 : c + 1) * sizeof(E))};
+    auto next = [&](int v) { return v + 1 == d.ny ? 0 : v + 1; };
+    int ym = (y0 - H - 1) % d.ny;
+    if (ym < 0) ym += d.ny;
+    int y = next(ym), yp = next(y);
+    pull9b<S>(sb, d, cb, ym, y, yp, F[0]);
+    auto row = [&](int j, auto kk) __attribute__((always_inline)) {
+      constexpr int K = decltype(kk)::value;
+      ym = y;
+      y = yp;
+      yp = next(yp);
+      pull9b<S>(sb, d, cb, ym, y, yp, F[(K + 1) & 3]);
+      bad |= step_row(kk) && out && in_rows(j);
+      pipe_push<S, W, K>(xo, F[(K + 2) & 3]);
+      lds_barrier();
+    };
+    march(row);
+  } else if (lv < TS - 1) {
+    const R* xi = &lds.ex[lv - 1][0][0] + i;
+    R* xo = &lds.ex[lv < TS - 1 ? lv : 0][0][0] + i;
+    auto row = [&](int j, auto kk) __attribute__((always_inline)) {
+      constexpr int K = decltype(kk)::value;
+      pipe_pull<S, W, K>(xi, F[K]);
+      bad |= step_row(kk) && out && in_rows(j);
+      pipe_push<S, W, K>(xo, F[(K + 2) & 3]);
+      lds_barrier();
+    };
+    march(row);
+  } else {
+    const R* xi = &lds.ex[TS - 2][0][0] + i;
+    const unsigned cb = (unsigned)(c * sizeof(E));
+    auto row = [&](int j, auto kk) __attribute__((always_inline)) {
+      constexpr int K = decltype(kk)::value;
+      pipe_pull<S, W, K>(xi, F[K]);
+      bad |= step_row(kk) && out && in_rows(j);
+      if (out && in_rows(j)) {
+        char* orow = reinterpret_cast<char*>(dst + (int64_t)(yc + j) * d.rs);
+        unsigned co;
+        asm("" : "=v"(co) : "0"(cb));
+#pragma unroll
+        for (int a = 0; a < 9; ++a) {
+          E* q = reinterpret_cast<E*>(orow + a * d.plane * sizeof(E) + co);
+          if (index_ok(q - dst, d.elems)) T::st(q, F[(K + 2) & 3][a]);
+        }
+      }
+      lds_barrier();
+    };
+    march(row);
+  }
+  if (__ballot(bad) != 0 && __lane_id() == 0) atomicMin(flag, step + lv);
+}
+
+// Strip edges of the multi-step kernels are rounded down to multiples of this
 // many columns (FP64: 8 columns = 64 B, so no 64-byte segment of a population
-// row is written by two blocks; 3 % faster on the 4096 x 4096 droplet
-// workload).  Strips then span at most nx / nstrips + A - 1 columns, which the
-// launcher's strip count keeps within 64*NW - 6.
-template <typename S> struct Step2Align : std::integral_constant<int, 1> {};
-template <> struct Step2Align<double> : std::integral_constant<int, 8> {};
+// row is written by two blocks).
+template <typename S> struct StripAlign : std::integral_constant<int, 1> {};
+template <> struct StripAlign<double> : std::integral_constant<int, 8> {};
 
-// Two steps per launch over the single lattice; strips of at most 64*NW - 6
-// columns, spread evenly over nx (edges aligned as Step2Align says).  L > 0: one block per (strip, L-row chunk);
-// L == 0: balanced schedule, every block marches one contiguous share of the
-// strip-major row space (no length cap: the tile holds no per-row arrays); a
-// share is split where it crosses a strip boundary.  (With the row-interleaved
-// layout a band-major order -- the blocks of one XCD marching one band of rows
-// across all strips -- measured no faster for any storage type.)
-template <typename S, int NW, int PF, bool MRT = false>
-__global__ __launch_bounds__(64 * NW) void k_step2(const typename Store<S>::E* __restrict__ src,
-                                                   typename Store<S>::E* __restrict__ dst,
-                                                   RunDev d, int L, int nstrips,
-                                                   const unsigned long long* stepbase,
-                                                   unsigned long long steplocal,
-                                                   unsigned long long* flag) {
-  using R = typename Store<S>::R;
-  __shared__ typename Store<S>::P ring1[4][64 * NW];
-  __shared__ typename Store<S>::P ring2[4][64 * NW];
-  __shared__ R xch[6][64 * NW];
+// Waves per step of a multi-step tile: the strip class `waves` 4 (8 is the same) gives
+// strips of 64 k columns less the halo with k = 4, or 3 with FP64 arithmetic or FP32
+// storage (FP64: a CU's LDS holds four steps of 192 columns, not of 256, and three
+// waves per SIMD have the registers that four have not; FP32: 16 waves would spill 26
+// registers, 115 us per step either way on 4096 x 4096); 2 gives the narrow ones,
+// k = 2, for lattices that leave lanes of a wide strip idle.
+template <typename S> constexpr int pipe_nw(int waves) {
+  return waves == 2 ? 2 : std::is_same<S, __half>::value ? 4 : 3;
+}
+
+// Single lattice: strips of at most W - 2H columns spread evenly over nx.  L > 0: one
+// block per (strip, L-row chunk).  L == 0: balanced schedule, every block marches one
+// contiguous share of the strip-major row space; a share is split where it crosses a
+// strip boundary.
+template <typename S, int NW, int TS, bool MRT = false>
+__global__ __launch_bounds__(64 * NW * TS) void k_pipe(const typename Store<S>::E* __restrict__ src,
+                                                       typename Store<S>::E* __restrict__ dst, RunDev d,
+                                                       int L, int nstrips,
+                                                       const unsigned long long* stepbase,
+                                                       unsigned long long steplocal,
+                                                       unsigned long long* flag) {
+  __shared__ PipeLds<S, 64 * NW, TS> lds;
   const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
   const bool frozen = *flag < step;  // diverged at an earlier step
   const int t = xcd_remap(blockIdx.x, gridDim.x);
-  auto strip = [&](int sx, int& x0, int& nc) {
-    constexpr int A = Step2Align<S>::value;
-    auto edge = [&](int k) {
-      return k >= nstrips ? d.nx : (int)((int64_t)k * d.nx / nstrips) / A * A;
-    };
-    x0 = edge(sx);
-    nc = edge(sx + 1) - x0;
+  auto edge = [&](int k) {
+    constexpr int A = StripAlign<S>::value;
+    return k >= nstrips ? d.nx : (int)((int64_t)k * d.nx / nstrips) / A * A;
   };
-  if (L > 0) {
-    const int sy = t / nstrips, sx = t - sy * nstrips;
-    int x0, nc;
-    strip(sx, x0, nc);
-    const int y0 = sy * L;
-    if (frozen)
-      copy_tile<S, 64 * NW>(src, dst, d, x0, y0, nc, min(L, d.ny - y0));
-    else
-      tile_step2<S, NW, PF, SteadyMode<S>::value, MRT>(src, dst, d, x0, y0, nc, min(L, d.ny - y0),
-                                                       step, flag, ring1, ring2,
-                            xch);
-    return;
-  }
-  const int64_t total = (int64_t)nstrips * d.ny;
-  int64_t r = total * t / gridDim.x;
-  const int64_t e = total * (t + 1) / gridDim.x;
-  while (r < e) {
-    const int s = (int)(r / d.ny), y = (int)(r - (int64_t)s * d.ny);
-    const int n = (int)min(e - r, (int64_t)(d.ny - y));
-    int x0, nc;
-    strip(s, x0, nc);
+  auto piece = [&](int s, int y, int n) {
+    const int x0 = edge(s), nc = edge(s + 1) - x0;
     if (frozen)
       copy_tile<S, 64 * NW>(src, dst, d, x0, y, nc, n);
     else
-      tile_step2<S, NW, PF, SteadyMode<S>::value, MRT>(src, dst, d, x0, y, nc, n, step, flag, ring1,
-                                                       ring2, xch);
-    r += n;
-    __syncthreads();  // LDS is reused by the next piece
-  }
-}
-
-// ---- three time steps per launch ----------------------------------------------
-
-// Three steps per launch: the pipeline of tile_step2 with a third level.  Lane
-// i of a block owns column c = x0 - 5 + i for all three steps, i < ncols + 10:
-//   * every lane pulls its column and evaluates psi(t);
-//   * lanes 1 .. ncols+8 run step one and keep f*(t+1) (the last three rows);
-//   * lanes 2 .. ncols+7 pull f*(t+1) and evaluate psi(t+1), lanes 3 ..
-//     ncols+6 run step two and keep f*(t+2) likewise;
-//   * lanes 4 .. ncols+5 pull f*(t+2) and evaluate psi(t+2), lanes 5 ..
-//     ncols+4 run step three and write the columns [x0, x0+ncols).
-// Rows: step three writes [y0, y0+nrows), so step two produces rows y0-2 ..
-// y0+nrows+1, step one rows y0-4 .. y0+nrows+3, and psi(t) is evaluated on
-// rows y0-5 .. y0+nrows+4.  At march row j step one collides y1 = y0-4+j,
-// step two pulls y1-2 and collides y1-3, step three pulls y1-5 and collides
-// y1-6.  Each step pulls the x-unshifted directions of the previous step's
-// rows from the lane's own registers and the six shifted ones through an LDS
-// exchange row, as in tile_step2; two barriers per march row.  Same
-// arithmetic in the same order as three single-step launches: bitwise equal.
-template <typename S, int NW, bool MRT = false>
-__device__ __forceinline__ void tile_step3(const typename Store<S>::E* __restrict__ src,
-                                           typename Store<S>::E* __restrict__ dst,
-                                           const RunDev& d, int x0, int y0, int ncols, int nrows,
-                                           unsigned long long step,
-                                           unsigned long long* __restrict__ flag,
-                                           typename Store<S>::P (*ring1)[64 * NW],
-                                           typename Store<S>::P (*ring2)[64 * NW],
-                                           typename Store<S>::P (*ring3)[64 * NW],
-                                           typename Store<S>::R (*xch1)[64 * NW],
-                                           typename Store<S>::R (*xch2)[64 * NW]) {
-  using T = Store<S>;
-  using R = typename T::R;
-  const int tid = threadIdx.x;
-  LBM_TILE_CHECK(ncols >= 1 && ncols <= 64 * NW - 10 && nrows >= 1 && x0 >= 0 &&
-                 x0 + ncols <= d.nx && y0 >= 0 && y0 + nrows <= d.ny);
-  const int n0 = ncols + 10;                        // lanes that evaluate psi(t)
-  const bool act0 = tid < n0;
-  const bool act1 = tid >= 1 && tid < n0 - 1;       // step one
-  const bool pull2 = tid >= 2 && tid < n0 - 2;      // step-two pull, psi(t+1)
-  const bool act2 = tid >= 3 && tid < n0 - 3;       // step two
-  const bool pull3 = tid >= 4 && tid < n0 - 4;      // step-three pull, psi(t+2)
-  const bool out = tid >= 5 && tid < n0 - 5;        // step three and the store
-  const int tc = min(max(tid, 1), 64 * NW - 2);     // LDS neighbour index inside the rows
-  auto wrapx = [&](int x) { return x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x); };
-  auto wrapy = [&](int y) { return y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y); };
-  const Cols cx = cols_of(wrapx(x0 - 5 + min(tid, n0 - 1)), d.nx);
-  bool bad1 = false, bad2 = false, bad3 = false;
-  const int ya = y0 - 5;                            // first psi(t) row (ring1 slot 0)
-  const int yb = y0 - 3;                            // first psi(t+1) row (ring2 slot 0)
-  const int yc = y0 - 1;                            // first psi(t+2) row (ring3 slot 0)
-
-  R fc[9] = {}, fn[9] = {};
-  NodeQ<S> qc;
-  if (act0) {
-    R f[9];
-    pull9<S>(src, d, cx, wrapy(ya), f);
-    pull9<S>(src, d, cx, wrapy(ya + 1), fc);
-    ring1[0][tid] = eval_psi<S>(f, d, qc);
-    ring1[1][tid] = eval_psi<S>(fc, d, qc);
-  }
-  // f*(t+1) kept for step two: gA = row y1-1 (all 9), gB = y1-2 (0,1,3,2,5,6),
-  // gC = y1-3 (2,5,6); f*(t+2) kept for step three likewise (kA, kB, kC, rows
-  // produced one, two and three march rows ago)
-  R gA[9] = {}, gB[6] = {}, gC[3] = {};
-  R kA[9] = {}, kB[6] = {}, kC[3] = {};
-  R hp[9] = {}, hp3[9] = {};   // pulled rows of steps two and three collided next
-  NodeQ<S> qp, qp3;
-  const int n_one = nrows + 8;                      // step-one rows y0-4 .. y0+nrows+3
-  auto row = [&](const int j, auto steady) __attribute__((always_inline)) {
-    constexpr bool St = decltype(steady)::value;
-    const int y1 = y0 - 4 + j;
-    // ---- phase 1: psi(t) of row y1+1; exchange rows for steps two and three
-    NodeQ<S> qn;
-    if ((St || j < n_one) && act0) {
-      __builtin_amdgcn_s_setprio(2);
-      pull9<S>(src, d, cx, wrapy(y1 + 1), fn);
-      __builtin_amdgcn_s_setprio(0);
-      ring1[(j + 2) & 3][tid] = eval_psi<S>(fn, d, qn);
-    }
-    const bool lv2 = St || (j >= 3 && j <= n_one);  // step two pulls q2 = y1-2
-    const bool lv3 = St || j >= 8;                  // step three pulls q3 = y1-5
-    // In steady rows the exchange writes and the pulls of steps two and three
-    // run on every lane: a lane outside a range writes and reads only LDS slots
-    // that no lane inside the range reads (tc keeps its neighbour reads inside
-    // the rows), so its values are never used.
-    if (lv2 && (St || act1)) {
-      xch1[0][tid] = gB[1];
-      xch1[1][tid] = gB[2];
-      xch1[2][tid] = gC[1];
-      xch1[3][tid] = gC[2];
-      xch1[4][tid] = gA[7];
-      xch1[5][tid] = gA[8];
-    }
-    if (lv3 && (St || act2)) {
-      xch2[0][tid] = kB[1];
-      xch2[1][tid] = kB[2];
-      xch2[2][tid] = kC[1];
-      xch2[3][tid] = kC[2];
-      xch2[4][tid] = kA[7];
-      xch2[5][tid] = kA[8];
-    }
-    __syncthreads();
-    // ---- phase 2: pulls of steps two and three and their psi; step-one collide
-    const int q2 = y1 - 2, q3 = y1 - 5;
-    R hn[9], hn3[9];
-    NodeQ<S> qh, qh3;
-    if (lv2 && (St || pull2)) {
-      hn[0] = gB[0];
-      hn[1] = xch1[0][tc - 1];
-      hn[2] = gC[0];
-      hn[3] = xch1[1][tc + 1];
-      hn[4] = gA[4];
-      hn[5] = xch1[2][tc - 1];
-      hn[6] = xch1[3][tc + 1];
-      hn[7] = xch1[4][tc + 1];
-      hn[8] = xch1[5][tc - 1];
-      ring2[(q2 - yb) & 3][tid] = eval_psi<S>(hn, d, qh);
-    }
-    if (lv3 && (St || pull3)) {
-      hn3[0] = kB[0];
-      hn3[1] = xch2[0][tc - 1];
-      hn3[2] = kC[0];
-      hn3[3] = xch2[1][tc + 1];
-      hn3[4] = kA[4];
-      hn3[5] = xch2[2][tc - 1];
-      hn3[6] = xch2[3][tc + 1];
-      hn3[7] = xch2[4][tc + 1];
-      hn3[8] = xch2[5][tc - 1];
-      ring3[(q3 - yc) & 3][tid] = eval_psi<S>(hn3, d, qh3);
-    }
-    if (St || j >= 1) {  // rotate the kept step-one rows (gA was produced at j-1)
-      gC[0] = gB[3]; gC[1] = gB[4]; gC[2] = gB[5];
-      gB[0] = gA[0]; gB[1] = gA[1]; gB[2] = gA[3];
-      gB[3] = gA[2]; gB[4] = gA[5]; gB[5] = gA[6];
-    }
-    if ((St || j < n_one) && act0) {
-      if (act1) {
-        const bool chk = out && y1 >= y0 && y1 < y0 + nrows;
-        bad1 |= finish_node<S, MRT>(fc, qc, ring1[j & 3], ring1[(j + 1) & 3], ring1[(j + 2) & 3], tc, d) && chk;
-#pragma unroll
-        for (int a = 0; a < 9; ++a) gA[a] = T::round(fc[a]);
-      }
-#pragma unroll
-      for (int a = 0; a < 9; ++a) fc[a] = fn[a];
-      qc = qn;
-    }
-    __syncthreads();
-    // ---- phase 3: step-two collide of row r2 = q2-1; step-three collide of r3 = q3-1 and store
-    const int r2 = q2 - 1, r3 = q3 - 1;
-    if (St || (j >= 5 && j <= n_one)) {
-      // rotate the kept step-two rows (kA was produced at j-1)
-      kC[0] = kB[3]; kC[1] = kB[4]; kC[2] = kB[5];
-      kB[0] = kA[0]; kB[1] = kA[1]; kB[2] = kA[3];
-      kB[3] = kA[2]; kB[4] = kA[5]; kB[5] = kA[6];
-      if (act2) {
-        const bool chk = out && r2 >= y0 && r2 < y0 + nrows;
-        bad2 |= finish_node<S, MRT>(hp, qp, ring2[(r2 - 1 - yb) & 3], ring2[(r2 - yb) & 3],
-                                    ring2[(q2 - yb) & 3], tc, d) && chk;
-#pragma unroll
-        for (int a = 0; a < 9; ++a) kA[a] = T::round(hp[a]);
-      }
-    }
-    if (lv2) {
-#pragma unroll
-      for (int a = 0; a < 9; ++a) hp[a] = hn[a];
-      qp = qh;
-    }
-    if ((St || j >= 10) && out) {
-      bad3 |= finish_node<S, MRT>(hp3, qp3, ring3[(r3 - 1 - yc) & 3], ring3[(r3 - yc) & 3],
-                                  ring3[(q3 - yc) & 3], tc, d);
-      typename T::E* orow = dst + (int64_t)wrapy(r3) * d.rs;
-#pragma unroll
-      for (int a = 0; a < 9; ++a)
-        if (index_ok(orow + a * d.plane + cx.x - dst, d.elems)) T::st(orow + a * d.plane + cx.x, hp3[a]);
-    }
-    if (lv3) {
-#pragma unroll
-      for (int a = 0; a < 9; ++a) hp3[a] = hn3[a];
-      qp3 = qh3;
-    }
+      tile_pipe<S, NW, TS, MRT>(src, dst, d, x0, y, nc, n, step, flag, lds);
   };
-  // rows 0..9 fill the pipeline, 10 .. n_one-1 are steady (every row condition
-  // above holds), the last two drain it
-  using Edge = std::integral_constant<bool, false>;
-  using Steady = std::integral_constant<bool, true>;
-  for (int j = 0; j < 10; ++j) row(j, Edge{});
-  for (int j = 10; j < n_one; ++j) row(j, Steady{});
-  for (int j = max(10, n_one); j < n_one + 2; ++j) row(j, Edge{});
-  const auto b1 = __ballot(bad1), b2 = __ballot(bad2), b3 = __ballot(bad3);
-  if (__lane_id() == 0 && (b1 | b2 | b3) != 0)
-    atomicMin(flag, b1 != 0 ? step : (b2 != 0 ? step + 1 : step + 2));
-}
-
-// Three steps per launch over the single lattice (FP64 collision arithmetic):
-// strips of at most 64*NW - 10 columns spread evenly over nx, edges aligned as
-// for the two-step kernel; L > 0: one block per (strip, L-row chunk); L == 0:
-// the balanced schedule of k_step2.
-template <typename S, int NW, bool MRT = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void k_step3(const typename Store<S>::E* __restrict__ src,
-                                                   typename Store<S>::E* __restrict__ dst,
-                                                   RunDev d, int L, int nstrips,
-                                                   const unsigned long long* stepbase,
-                                                   unsigned long long steplocal,
-                                                   unsigned long long* flag) {
-  using R = typename Store<S>::R;
-  using P = typename Store<S>::P;
-  __shared__ P ring1[4][64 * NW];
-  __shared__ P ring2[4][64 * NW];
-  __shared__ P ring3[4][64 * NW];
-  __shared__ R xch1[6][64 * NW];
-  __shared__ R xch2[6][64 * NW];
-  const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
-  const bool frozen = *flag < step;  // diverged at an earlier step
-  const int t = xcd_remap(blockIdx.x, gridDim.x);
-  auto strip = [&](int sx, int& x0, int& nc) {
-    constexpr int A = Step2Align<S>::value;
-    auto edge = [&](int k) {
-      return k >= nstrips ? d.nx : (int)((int64_t)k * d.nx / nstrips) / A * A;
-    };
-    x0 = edge(sx);
-    nc = edge(sx + 1) - x0;
-  };
+  int64_t r, e;  // this block's share of the strip-major rows
   if (L > 0) {
-    const int sy = t / nstrips, sx = t - sy * nstrips;
-    int x0, nc;
-    strip(sx, x0, nc);
-    const int y0 = sy * L;
-    if (frozen)
-      copy_tile<S, 64 * NW>(src, dst, d, x0, y0, nc, min(L, d.ny - y0));
-    else
-      tile_step3<S, NW, MRT>(src, dst, d, x0, y0, nc, min(L, d.ny - y0), step, flag, ring1, ring2, ring3,
-                        xch1, xch2);
-    return;
+    const int sy = t / nstrips, s = t - sy * nstrips;
+    r = (int64_t)s * d.ny + (int64_t)sy * L;
+    e = min(r + L, (int64_t)(s + 1) * d.ny);
+  } else {
+    const int64_t total = (int64_t)nstrips * d.ny;
+    r = total * t / gridDim.x;
+    e = total * (t + 1) / gridDim.x;
   }
-  const int64_t total = (int64_t)nstrips * d.ny;
-  int64_t r = total * t / gridDim.x;
-  const int64_t e = total * (t + 1) / gridDim.x;
   while (r < e) {
     const int s = (int)(r / d.ny), y = (int)(r - (int64_t)s * d.ny);
     const int n = (int)min(e - r, (int64_t)(d.ny - y));
-    int x0, nc;
-    strip(s, x0, nc);
-    if (frozen)
-      copy_tile<S, 64 * NW>(src, dst, d, x0, y, nc, n);
-    else
-      tile_step3<S, NW, MRT>(src, dst, d, x0, y, nc, n, step, flag, ring1, ring2, ring3, xch1, xch2);
+    piece(s, y, n);
     r += n;
     __syncthreads();  // LDS is reused by the next piece
   }
@@ -1298,48 +1084,36 @@ __global__ __launch_bounds__(64 * NW) void k_batch_step(const typename Store<S>:
   }
 }
 
-// Persistent batched launch of two steps (tile_step2) over a work list whose
-// items are at most 64*NW - 6 columns wide.  A run frozen by divergence at an
-// earlier launch is copied unchanged; grid must be a multiple of 8.
-template <typename S, int NW, int PF, bool MRT = false>
-__global__ __launch_bounds__(64 * NW) void k_batch_step2(const typename Store<S>::E* __restrict__ src,
-                                                         typename Store<S>::E* __restrict__ dst,
-                                                         const RunDev* __restrict__ runs,
-                                                         const Item* __restrict__ items, int nitems,
-                                                         int total,
-                                                         const unsigned long long* stepbase,
-                                                         unsigned long long steplocal,
-                                                         unsigned long long* flags) {
-  using R = typename Store<S>::R;
-  __shared__ typename Store<S>::P ring1[4][64 * NW];
-  __shared__ typename Store<S>::P ring2[4][64 * NW];
-  __shared__ R xch[6][64 * NW];
+// Persistent batched launch of TS steps (tile_pipe) over a work list whose items are
+// at most W - 2H columns wide.  A run frozen by divergence at an earlier launch is
+// copied unchanged; grid must be a multiple of 8.
+template <typename S, int NW, int TS, bool MRT = false>
+__global__ __launch_bounds__(64 * NW * TS) void k_batch_pipe(const typename Store<S>::E* __restrict__ src,
+                                                             typename Store<S>::E* __restrict__ dst,
+                                                             const RunDev* __restrict__ runs,
+                                                             const Item* __restrict__ items, int nitems,
+                                                             int total,
+                                                             const unsigned long long* stepbase,
+                                                             unsigned long long steplocal,
+                                                             unsigned long long* flags) {
+  __shared__ PipeLds<S, 64 * NW, TS> lds;
   const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
+  auto piece = [&](const Item& it, int y, int n) {
+    const RunDev d = runs[it.run];
+    if (flags[it.run] < step)  // frozen run
+      copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n);
+    else
+      tile_pipe<S, NW, TS, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n, step,
+                                &flags[it.run], lds);
+  };
   if (total > 0) {  // balanced schedule over whole-strip items (no row cap: no per-row arrays)
-    balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), 1 << 30,
-                    [&](const Item& it, int y, int n) {
-                      const RunDev d = runs[it.run];
-                      if (flags[it.run] < step)
-                        copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n);
-                      else
-                        tile_step2<S, NW, PF, kBatchSteadyMode, MRT>(src + d.off, dst + d.off, d,
-                                                                     it.x0, it.y0 + y, it.ncols, n,
-                                                                     step, &flags[it.run], ring1,
-                                                                     ring2, xch);
-                    });
+    balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), 1 << 30, piece);
     return;
   }
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nb = gridDim.x >> 3;
   const int lo = (int)((int64_t)nitems * xcd / 8), hi = (int)((int64_t)nitems * (xcd + 1) / 8);
   for (int i = lo + slot; i < hi; i += nb) {
-    const Item it = items[i];
-    const RunDev d = runs[it.run];
-    if (flags[it.run] < step)  // frozen run
-      copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0, it.ncols, it.nrows);
-    else
-      tile_step2<S, NW, PF, kBatchSteadyMode, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0,
-                                                   it.ncols, it.nrows, step, &flags[it.run], ring1,
-                                                   ring2, xch);
+    piece(items[i], 0, items[i].nrows);
     __syncthreads();  // LDS is reused by the next item
   }
 }

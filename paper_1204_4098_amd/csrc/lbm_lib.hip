@@ -32,10 +32,10 @@ constexpr unsigned long long kNoDiv = ~0ull;
     if ((x) != hipSuccess) return LBM_EHIP; \
   } while (0)
 
-// Launch shape of the step kernels: waves per block (strip of 64*nw columns),
-// rows per block (0 = balanced schedule over the resident grid), the row
-// prefetch depth (1 or 2) and the time steps per launch (1, or 2 for the
-// two-step kernel of the single lattice).
+// Launch shape of the step kernels: waves per block (one-step kernels: a strip of
+// 64*nw columns; multi-step kernels: strip class, see pipe_nw), rows per block (0 =
+// balanced schedule over the resident grid), the row prefetch depth of the one-step
+// kernels (1 or 2) and the time steps per launch.
 struct Tile {
   int nw, L, pf;
   int ts = 1;
@@ -127,6 +127,7 @@ RunDev make_rundev(const lbm_params& p, const EosConst& k, double rho_ref, int64
   }
   d.c_d = c_f - d.c_eq;
   d.om1 = 1.0 - d.inv_tau;
+  d.om1_2 = d.om1 / 2.0;
   d.om_2 = d.inv_tau / 2.0;
   d.om_9 = d.inv_tau / 9.0;
   d.om_3 = d.inv_tau / 3.0;
@@ -252,97 +253,78 @@ hipError_t launch_step_s(const Tile& t, const void* src, void* dst, const RunDev
   }
 }
 
-template <typename S, int NW, int PF, bool MRT = false>
-hipError_t launch_step2_t(const void* src, void* dst, const RunDev& d, int L,
-                          const unsigned long long* base, unsigned long long local,
-                          unsigned long long* flag, hipStream_t st) {
-  const int SW = 64 * NW;
-  // strips of at most SW - 6 columns after their edges are aligned down to A columns
-  constexpr int A = Step2Align<S>::value;
-  const int nstrips = (d.nx + SW - 7 - (A - 1)) / (SW - 6 - (A - 1));
+// Strips of a multi-step launch: at most W - 2H columns after their edges are aligned
+// down to A columns (one strip needs no alignment).
+template <typename S, int NW, int TS> int pipe_strips(int nx) {
+  constexpr int M = 64 * NW - 2 * (2 * TS - 1), A = StripAlign<S>::value;
+  return nx <= M ? 1 : (nx + M - A) / (M - A + 1);
+}
+
+template <typename S, int NW, int TS, bool MRT>
+hipError_t launch_pipe_t(const void* src, void* dst, const RunDev& d, int L,
+                         const unsigned long long* base, unsigned long long local,
+                         unsigned long long* flag, hipStream_t st) {
+  const int threads = 64 * NW * TS;
+  const int nstrips = pipe_strips<S, NW, TS>(d.nx);
   int grid;
   if (L > 0) {
     grid = nstrips * ((d.ny + L - 1) / L);
   } else {
     const int64_t rows = (int64_t)nstrips * d.ny;
-    grid = resident_blocks((const void*)k_step2<S, NW, PF, MRT>, SW);
+    grid = resident_blocks((const void*)k_pipe<S, NW, TS, MRT>, threads);
     grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, rows / 8));
   }
   using E = typename Store<S>::E;
-  hipLaunchKernelGGL((k_step2<S, NW, PF, MRT>), dim3(grid), dim3(SW), 0, st,
+  hipLaunchKernelGGL((k_pipe<S, NW, TS, MRT>), dim3(grid), dim3(threads), 0, st,
                      static_cast<const E*>(src), static_cast<E*>(dst), d, L, nstrips, base, local, flag);
   return hipGetLastError();
 }
 
-template <typename S, bool MRT = false>
-hipError_t launch_step2_s(const Tile& t, const void* src, void* dst, const RunDev& d,
-                          const unsigned long long* base, unsigned long long local,
-                          unsigned long long* flag, hipStream_t st) {
-  switch (t.nw * 10 + t.pf) {
-    case 41: return launch_step2_t<S, 4, 1, MRT>(src, dst, d, t.L, base, local, flag, st);
-    case 42: return launch_step2_t<S, 4, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
-    case 81: return launch_step2_t<S, 8, 1, MRT>(src, dst, d, t.L, base, local, flag, st);
-    default: return launch_step2_t<S, 8, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
-  }
-}
-
-template <typename S, int NW, bool MRT = false>
-hipError_t launch_step3_t(const void* src, void* dst, const RunDev& d, int L,
-                          const unsigned long long* base, unsigned long long local,
-                          unsigned long long* flag, hipStream_t st) {
-  const int SW = 64 * NW;
-  // strips of at most SW - 10 columns after their edges are aligned down to A columns
-  constexpr int A = Step2Align<S>::value;
-  const int nstrips = (d.nx + SW - 11 - (A - 1)) / (SW - 10 - (A - 1));
-  int grid;
-  if (L > 0) {
-    grid = nstrips * ((d.ny + L - 1) / L);
-  } else {
-    const int64_t rows = (int64_t)nstrips * d.ny;
-    grid = resident_blocks((const void*)k_step3<S, NW, MRT>, SW);
-    grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, rows / 8));
-  }
-  using E = typename Store<S>::E;
-  hipLaunchKernelGGL((k_step3<S, NW, MRT>), dim3(grid), dim3(SW), 0, st, static_cast<const E*>(src),
-                     static_cast<E*>(dst), d, L, nstrips, base, local, flag);
-  return hipGetLastError();
-}
-
-// Storage types with a three-step kernel: those with FP64 collision arithmetic
-// (the FP32 and FP16 arithmetic paths are bound by instruction issue, where
-// the recomputed halo of a third step costs more than the traffic it saves).
+// Storage types with three steps per launch as a tile: those with FP64 collision
+// arithmetic.
 bool has_step3(int prec) { return prec == LBM_PREC_F64 || prec == LBM_PREC_F32DEV_F64; }
 
-// One launch of the tile: t.ts time steps (1, 2 or 3) from src into dst.
+template <typename S, bool MRT = false>
+hipError_t launch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev& d,
+                         const unsigned long long* base, unsigned long long local,
+                         unsigned long long* flag, hipStream_t st) {
+  constexpr int NW = pipe_nw<S>(4);
+  if (t.ts == 2) return launch_pipe_t<S, NW, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
+  if (t.ts == 4)
+    return t.nw == 2 ? launch_pipe_t<S, 2, 4, MRT>(src, dst, d, t.L, base, local, flag, st)
+                     : launch_pipe_t<S, NW, 4, MRT>(src, dst, d, t.L, base, local, flag, st);
+  if constexpr (std::is_same<typename Store<S>::R, double>::value)
+    if (t.ts == 3) return launch_pipe_t<S, NW, 3, MRT>(src, dst, d, t.L, base, local, flag, st);
+  return hipErrorInvalidValue;
+}
+
+// Steps of the next launch of tile t with `left` steps to go: the tile's, or what is
+// left (three only where that kernel exists).  Rows of 2^32 bytes and more take single
+// steps: the multi-step kernels address a row with 32-bit byte offsets.
+int next_ts(int prec, int nx, const Tile& t, int64_t left) {
+  int ts = (int)std::min<int64_t>(t.ts, left);
+  if (ts == 3 && !has_step3(prec)) ts = 2;
+  if (ts > 1 && (int64_t)nx * esize_of(prec) >= (1ll << 32)) ts = 1;
+  return ts;
+}
+
+// One launch of the tile: t.ts time steps from src into dst.
 hipError_t launch_step(int prec, const Tile& t, const void* src, void* dst, const RunDev& d,
                        const unsigned long long* base, unsigned long long local,
                        unsigned long long* flag, hipStream_t st) {
-  if (t.ts == 3 && d.mrt)  // FP64 only: the one precision with both MRT and three steps
-    return t.nw == 8 ? launch_step3_t<double, 8, true>(src, dst, d, t.L, base, local, flag, st)
-                     : launch_step3_t<double, 4, true>(src, dst, d, t.L, base, local, flag, st);
-  if (t.ts == 3) {
-    if (prec == LBM_PREC_F64)
-      return t.nw == 8 ? launch_step3_t<double, 8>(src, dst, d, t.L, base, local, flag, st)
-                       : launch_step3_t<double, 4>(src, dst, d, t.L, base, local, flag, st);
-    if (prec == LBM_PREC_F32DEV_F64)
-      return t.nw == 8 ? launch_step3_t<f32s_f64a, 8>(src, dst, d, t.L, base, local, flag, st)
-                       : launch_step3_t<f32s_f64a, 4>(src, dst, d, t.L, base, local, flag, st);
-    return hipErrorInvalidValue;
-  }
-  if (t.ts == 2 && d.mrt) {  // FP64 or FP32 deviation storage (checked by lbm_set_mrt)
-    if (prec == LBM_PREC_F64) return launch_step2_s<double, true>(t, src, dst, d, base, local, flag, st);
-    return launch_step2_s<float, true>(t, src, dst, d, base, local, flag, st);
-  }
-  if (t.ts == 2) {
-    if (prec == LBM_PREC_F64) return launch_step2_s<double>(t, src, dst, d, base, local, flag, st);
-    if (prec == LBM_PREC_F32DEV) return launch_step2_s<float>(t, src, dst, d, base, local, flag, st);
-    if (prec == LBM_PREC_F32DEV_F64)
-      return launch_step2_s<f32s_f64a>(t, src, dst, d, base, local, flag, st);
-    return launch_step2_s<__half>(t, src, dst, d, base, local, flag, st);
-  }
-  if (d.mrt) {  // one step per launch; FP64 or FP32 deviation storage (checked by lbm_set_mrt)
+  if (d.mrt) {  // FP64 or FP32 deviation storage (checked by lbm_set_mrt)
+    if (t.ts > 1)
+      return prec == LBM_PREC_F64 ? launch_pipe_s<double, true>(t, src, dst, d, base, local, flag, st)
+                                  : launch_pipe_s<float, true>(t, src, dst, d, base, local, flag, st);
     if (prec == LBM_PREC_F64) return launch_step_s<double, true>(t, src, dst, d, base, local, flag, st);
     return launch_step_s<float, true>(t, src, dst, d, base, local, flag, st);
+  }
+  if (t.ts > 1) {
+    if (prec == LBM_PREC_F64) return launch_pipe_s<double>(t, src, dst, d, base, local, flag, st);
+    if (prec == LBM_PREC_F32DEV) return launch_pipe_s<float>(t, src, dst, d, base, local, flag, st);
+    if (prec == LBM_PREC_F32DEV_F64)
+      return launch_pipe_s<f32s_f64a>(t, src, dst, d, base, local, flag, st);
+    return launch_pipe_s<__half>(t, src, dst, d, base, local, flag, st);
   }
   if (prec == LBM_PREC_F64) return launch_step_s<double>(t, src, dst, d, base, local, flag, st);
   if (prec == LBM_PREC_F32DEV) return launch_step_s<float>(t, src, dst, d, base, local, flag, st);
@@ -388,33 +370,34 @@ hipError_t launch_batch_s(const Tile& t, const void* src, void* dst, const RunDe
   }
 }
 
-template <typename S, int NW, int PF, bool MRT>
-hipError_t launch_batch2_t(const void* src, void* dst, const RunDev* runs, const Item* items,
-                           int nitems, int total, const unsigned long long* base,
-                           unsigned long long local, unsigned long long* flags, hipStream_t st) {
-  const int g = batch_grid((const void*)k_batch_step2<S, NW, PF, MRT>, 64 * NW, nitems, total);
+template <typename S, int NW, int TS, bool MRT>
+hipError_t launch_batch_pipe_t(const void* src, void* dst, const RunDev* runs, const Item* items,
+                               int nitems, int total, const unsigned long long* base,
+                               unsigned long long local, unsigned long long* flags, hipStream_t st) {
+  const int threads = 64 * NW * TS;
+  const int g = batch_grid((const void*)k_batch_pipe<S, NW, TS, MRT>, threads, nitems, total);
   using E = typename Store<S>::E;
-  hipLaunchKernelGGL((k_batch_step2<S, NW, PF, MRT>), dim3(g), dim3(64 * NW), 0, st,
+  hipLaunchKernelGGL((k_batch_pipe<S, NW, TS, MRT>), dim3(g), dim3(threads), 0, st,
                      static_cast<const E*>(src), static_cast<E*>(dst), runs, items, nitems, total,
                      base, local, flags);
   return hipGetLastError();
 }
 
 template <typename S, bool MRT = false>
-hipError_t launch_batch2_s(const Tile& t, const void* src, void* dst, const RunDev* runs,
-                           const Item* items, int nitems, int total, const unsigned long long* base,
-                           unsigned long long local, unsigned long long* flags, hipStream_t st) {
-  switch (t.nw * 10 + t.pf) {
-    case 21: return launch_batch2_t<S, 2, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 22: return launch_batch2_t<S, 2, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 41: return launch_batch2_t<S, 4, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 42: return launch_batch2_t<S, 4, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 81: return launch_batch2_t<S, 8, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    default: return launch_batch2_t<S, 8, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-  }
+hipError_t launch_batch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev* runs,
+                               const Item* items, int nitems, int total, const unsigned long long* base,
+                               unsigned long long local, unsigned long long* flags, hipStream_t st) {
+  constexpr int NW = pipe_nw<S>(4);
+  if (t.ts == 4)
+    return t.nw == 2
+               ? launch_batch_pipe_t<S, 2, 4, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st)
+               : launch_batch_pipe_t<S, NW, 4, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
+  return t.nw == 2
+             ? launch_batch_pipe_t<S, 2, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st)
+             : launch_batch_pipe_t<S, NW, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
 }
 
-// One launch of the batch tile: t.ts time steps (1 or 2) of every active run;
+// One launch of the batch tile: t.ts time steps of every active run;
 // mrt: the runs' descriptors carry the MRT collision (FP64 or FP32 deviation
 // storage, checked by lbm_batch_set_mrt).
 hipError_t launch_batch(int prec, bool mrt, const Tile& t, const void* src, void* dst,
@@ -422,23 +405,23 @@ hipError_t launch_batch(int prec, bool mrt, const Tile& t, const void* src, void
                         const unsigned long long* base, unsigned long long local,
                         unsigned long long* flags, hipStream_t st) {
   if (mrt) {
-    if (t.ts == 2) {
+    if (t.ts > 1) {
       if (prec == LBM_PREC_F64)
-        return launch_batch2_s<double, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-      return launch_batch2_s<float, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+        return launch_batch_pipe_s<double, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+      return launch_batch_pipe_s<float, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
     }
     if (prec == LBM_PREC_F64)
       return launch_batch_s<double, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
     return launch_batch_s<float, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
   }
-  if (t.ts == 2) {
+  if (t.ts > 1) {
     if (prec == LBM_PREC_F64)
-      return launch_batch2_s<double>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+      return launch_batch_pipe_s<double>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
     if (prec == LBM_PREC_F32DEV)
-      return launch_batch2_s<float>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+      return launch_batch_pipe_s<float>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
     if (prec == LBM_PREC_F32DEV_F64)
-      return launch_batch2_s<f32s_f64a>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-    return launch_batch2_s<__half>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+      return launch_batch_pipe_s<f32s_f64a>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+    return launch_batch_pipe_s<__half>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
   }
   if (prec == LBM_PREC_F64)
     return launch_batch_s<double>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
@@ -609,33 +592,29 @@ bool same_tile(const Tile& a, const Tile& b) {
 // columns wide).
 constexpr int kStepWaves[] = {1, 2, 4, 8, 16};
 constexpr int kBatchWaves[] = {1, 2, 4, 8};
-constexpr int kStep2Waves[] = {4, 8};  // two-step kernel: 250- and 506-column strips
-// The batched two-step kernel also has 2-wave blocks (122-column strips): the
-// lattices of a sweep are 64 to 512 columns wide, and a 250-column strip of a
-// narrow one leaves most lanes of its block idle.
-constexpr int kBatchStep2Waves[] = {2, 4, 8};
 
-// A launch shape; ts2_min_nw is the smallest wave count of the two-step kernel
-// (2 for the batched launch, 4 for a single lattice).
-// The three-step kernel (single lattice only) has 4- and 8-wave blocks and
-// row prefetch depth 1.
-bool valid_tile(int nw, int L, int pf, int maxnw, int ts = 1, int ts2_min_nw = 4) {
-  if (ts == 2 && (nw < ts2_min_nw || (nw != 2 && nw != 4 && nw != 8))) return false;
-  if (ts == 3 && (ts2_min_nw != 4 || (nw != 4 && nw != 8) || pf != 1)) return false;
+// A launch shape.  Multi-step tiles: strip class nw 4 (8 is the same) or 2 (narrow
+// strips: batches, and single lattices at four steps); three steps only for single
+// lattices, with depth 1.
+bool valid_tile(int nw, int L, int pf, int maxnw, int ts = 1, bool batch = false) {
+  if (ts > 1 && nw != 4 && nw != 8 && !(nw == 2 && (batch || ts == 4))) return false;
+  if (ts == 3 && batch) return false;
+  if (ts > 2 && pf != 1) return false;
   return (nw == 1 || nw == 2 || nw == 4 || nw == 8 || nw == 16) && nw <= maxnw && L >= 0 &&
-         L <= LMAX && (pf == 1 || pf == 2) && ts >= 1 && ts <= 3;
+         L <= LMAX && (pf == 1 || pf == 2) && ts >= 1 && ts <= 4;
 }
 
-// A remainder of r < t.ts steps of a multi-step tile: one launch of r steps
-// (the two-step kernel for two, with the same waves, rows and depth, which
-// every three-step tile also suits).
-Tile remainder_tile(Tile t, int r) {
-  t.ts = r;
+Tile with_steps(Tile t, int ts) {
+  t.ts = ts;
   return t;
 }
 
-// Launches in a graph of k steps: k / ts full launches and one for the remainder.
-int graph_launches(int k, int ts) { return k / ts + (k % ts != 0 ? 1 : 0); }
+// Launches that k steps take.
+int launches_of(int prec, int nx, const Tile& t, int k) {
+  int n = 0;
+  for (; k > 0; ++n) k -= next_ts(prec, nx, t, k);
+  return n;
+}
 
 void drop_graphs(lbm_ctx* c) {
   for (int i = 0; i < 2; ++i)
@@ -660,12 +639,11 @@ int capture_graph(lbm_ctx* c, int parity) {
   hipGraph_t g;
   HIPCHK(hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  const int full = c->graph_k / c->tile.ts, rest = c->graph_k % c->tile.ts;
-  for (int i = 0; i < graph_launches(c->graph_k, c->tile.ts) && e == hipSuccess; ++i) {
-    const int s = (parity + i) & 1;
-    const Tile t = i < full ? c->tile : remainder_tile(c->tile, rest);
-    e = launch_step(c->p.precision, t, c->buf[s], c->buf[s ^ 1], c->d, c->ctr,
-                    (unsigned long long)i * c->tile.ts, c->flag, c->st);
+  for (int s = parity, done = 0; done < c->graph_k && e == hipSuccess; s ^= 1) {
+    const int ts = next_ts(c->p.precision, c->p.nx, c->tile, c->graph_k - done);
+    e = launch_step(c->p.precision, with_steps(c->tile, ts), c->buf[s], c->buf[s ^ 1], c->d, c->ctr,
+                    (unsigned long long)done, c->flag, c->st);
+    done += ts;
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_counter_add, dim3(1), dim3(1), 0, c->st, c->ctr,
@@ -846,13 +824,12 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       HIPCHK(hipGraphLaunch(c->gexec[c->cur], c->st));
       done += c->graph_k;
       c->step += c->graph_k;
-      c->cur ^= graph_launches(c->graph_k, c->tile.ts) & 1;  // one buffer swap per launch
+      c->cur ^= launches_of(c->p.precision, c->p.nx, c->tile, c->graph_k) & 1;  // a buffer swap each
     }
   }
   while (done < n) {
     const int s = c->cur;
-    Tile t = c->tile;
-    if (n - done < t.ts) t = remainder_tile(t, (int)(n - done));  // fewer steps than the tile's
+    const Tile t = with_steps(c->tile, next_ts(c->p.precision, c->p.nx, c->tile, n - done));
     HIPCHK(launch_step(c->p.precision, t, c->buf[s], c->buf[s ^ 1], c->d, nullptr,
                        (unsigned long long)c->step, c->flag, c->st));
     c->cur ^= 1;
@@ -1068,18 +1045,11 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
         if (L <= 2 * c->p.ny && (L == 0 || L > 2 || nodes < (1 << 20)))  // 1-2 rows: small lattices
           cand.push_back(Tile{nw, L, pf, 1});
   }
-  for (int nw : kStep2Waves) {
-    if (nw > 4 && 64 * (nw / 2) >= c->p.nx) continue;
-    for (int pf : {1, 2})
-      for (int L : {0, 32, 64, 128})
-        if (L <= 2 * c->p.ny) cand.push_back(Tile{nw, L, pf, 2});
-  }
-  if (has_step3(c->p.precision) && c->p.nx >= 16 && c->p.ny >= 16)
-    for (int nw : {4, 8}) {
-      if (nw > 4 && 64 * (nw / 2) >= c->p.nx) continue;
-      for (int L : {0, 64, 128})
-        if (L <= 2 * c->p.ny) cand.push_back(Tile{nw, L, 1, 3});
-    }
+  for (int L : {0, 16, 32, 64, 128})
+    if (L <= 2 * c->p.ny)
+      for (const Tile& t : {Tile{4, L, 1, 4}, Tile{2, L, 1, 4}, Tile{4, L, 1, 2}})
+        if (next_ts(c->p.precision, c->p.nx, t, t.ts) == t.ts && (t.ts == 4 || L == 0 || L == 32))
+          cand.push_back(t);
   const int pst = pick_tile(
       cand,
       [&](const Tile& t) {
@@ -1253,9 +1223,11 @@ int batch_items(lbm_batch* b, const Tile& t) {
     nx[r] = b->p[r].nx;
     ny[r] = b->p[r].ny;
   }
-  // two-step strips of FP64 lattices start on 64-byte boundaries, as for a single lattice
-  const int64_t rows = layout::build_items(b->nruns, nx.data(), ny.data(), t.nw, t.L, t.ts, items,
-                                           b->prec == LBM_PREC_F64 ? Step2Align<double>::value : 1);
+  // multi-step strips: as wide as their kernel takes; those of FP64 lattices start on
+  // 64-byte boundaries, as for a single lattice
+  const int nw = t.ts == 1 ? t.nw : b->prec == LBM_PREC_F16DEV ? pipe_nw<__half>(t.nw) : pipe_nw<double>(t.nw);
+  const int64_t rows = layout::build_items(b->nruns, nx.data(), ny.data(), nw, t.L, t.ts, items,
+                                           b->prec == LBM_PREC_F64 ? StripAlign<double>::value : 1);
   if ((int)items.size() > b->items_cap) return LBM_ENOSPACE;
   if (rows >= INT32_MAX) return LBM_EINVAL;
   b->total_rows = t.L > 0 ? 0 : (int)rows;
@@ -1274,15 +1246,21 @@ void batch_drop_graphs(lbm_batch* b) {
     }
 }
 
+// Steps of the next launch with `left` steps to go: the tile's, or fewer at the end
+// (the items of a tile suit every kernel of fewer steps: their strips are no wider).
+int batch_next_ts(const Tile& t, int64_t left) {
+  return left >= t.ts ? t.ts : left >= 2 ? 2 : 1;
+}
+
 int batch_capture(lbm_batch* b, int parity) {
   hipGraph_t g;
   HIPCHK(hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  const int launches = b->graph_k / b->tile.ts;  // graph_k is even
-  for (int i = 0; i < launches && e == hipSuccess; ++i) {
-    const int s = (parity + i) & 1;
-    e = launch_batch(b->prec, b->mrt != 0, b->tile, b->buf[s], b->buf[s ^ 1], b->d_runs, b->d_items, b->nitems, b->total_rows,
-                     b->ctr, (unsigned long long)i * b->tile.ts, b->flags, b->st);
+  for (int s = parity, done = 0; done < b->graph_k && e == hipSuccess; s ^= 1) {
+    const int ts = batch_next_ts(b->tile, b->graph_k - done);
+    e = launch_batch(b->prec, b->mrt != 0, with_steps(b->tile, ts), b->buf[s], b->buf[s ^ 1], b->d_runs,
+                     b->d_items, b->nitems, b->total_rows, b->ctr, (unsigned long long)done, b->flags, b->st);
+    done += ts;
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_counter_add, dim3(1), dim3(1), 0, b->st, b->ctr, (unsigned long long)b->graph_k);
@@ -1447,13 +1425,12 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
       HIPCHK(hipGraphLaunch(b->gexec[b->cur], b->st));
       done += b->graph_k;
       b->step += b->graph_k;
-      b->cur ^= (b->graph_k / b->tile.ts) & 1;  // one buffer swap per launch
+      for (int k = b->graph_k; k > 0; k -= batch_next_ts(b->tile, k)) b->cur ^= 1;  // a swap per launch
     }
   }
   while (done < n) {
     const int s = b->cur;
-    Tile t = b->tile;
-    if (n - done < t.ts) t.ts = 1;  // odd remainder of a two-step tile (its items suit both)
+    const Tile t = with_steps(b->tile, batch_next_ts(b->tile, n - done));
     HIPCHK(launch_batch(b->prec, b->mrt != 0, t, b->buf[s], b->buf[s ^ 1], b->d_runs, b->d_items, b->nitems, b->total_rows,
                         nullptr, (unsigned long long)b->step, b->flags, b->st));
     b->cur ^= 1;
@@ -1464,7 +1441,7 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
 }
 
 int lbm_batch_set_tile(lbm_batch* b, int32_t nw, int32_t L, int32_t depth, int32_t steps) {
-  if (!b || !valid_tile(nw, L, depth, 8, steps, 2) || (L > 0 && L < 4)) return LBM_EINVAL;
+  if (!b || !valid_tile(nw, L, depth, 8, steps, true) || (L > 0 && L < 4)) return LBM_EINVAL;
   batch_drop_graphs(b);
   const int st = batch_items(b, Tile{nw, L, depth, steps});
   return st != LBM_OK ? st : batch_prepare_graphs(b);
@@ -1528,11 +1505,9 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
     for (int pf : {1, 2})
       for (int L : {0, 4, 8, 16, 32, 64}) cand.push_back(Tile{nw, L, pf, 1});
   }
-  for (int nw : kBatchStep2Waves) {
-    if (nw > 4 && 64 * (nw / 2) >= maxnx) continue;
-    for (int pf : {1, 2})
-      for (int L : {0, 32, 64}) cand.push_back(Tile{nw, L, pf, 2});
-  }
+  for (int nw : {2, 4})
+    for (int ts : {2, 4})
+      for (int L : {0, 16, 32, 64}) cand.push_back(Tile{nw, L, 1, ts});
   int ist = LBM_OK;
   const int pst = pick_tile(
       cand,
