@@ -432,29 +432,34 @@ hipError_t launch_batch(int prec, bool mrt, const Tile& t, const void* src, void
   return launch_batch_s<__half>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
 }
 
+// Rows per block (two more are pulled for psi): 2048 blocks or more, so that every CU
+// has 8, but 2 to 16 rows.  Measured: 700 x 300 FP64 7.0 us with 4 rows, 10.3 with 8, 31
+// with 32; 2048 x 2048 FP64 101, 98, 101, 120 us with 8, 16, 32, 64; FP16 39, 43, 53 with
+// 8, 16, 32; 4096 x 4096 FP64 417, 404, 408 with 8, 16, 32.
 template <typename S>
-hipError_t launch_moments_s(const void* src, const RunDev& d, double* rho, double* vx, double* vy,
-                            double* p, double* psi, hipStream_t st) {
-  // rows beyond the grid's y extent (at most 65535 here) are looped in the kernels
-  dim3 blk(64), grd((d.nx + 63) / 64, std::min(d.ny, 65535));
-  hipLaunchKernelGGL(k_moments1<S>, grd, blk, 0, st, static_cast<const typename Store<S>::E*>(src), d, rho,
-                     vx, vy, psi);
-  hipLaunchKernelGGL(k_moments2, grd, blk, 0, st, d, (const double*)psi, (const double*)rho, vx, vy, p);
+hipError_t launch_fields_s(const void* src, const RunDev& d, double* rho, double* vx, double* vy, double* p,
+                           hipStream_t st) {
+  const int threads = d.nx <= 62 ? 64 : d.nx <= 126 ? 128 : 256;
+  const int64_t nstrips = (d.nx + threads - 3) / (threads - 2);
+  const int64_t L = std::min<int64_t>(d.ny, std::min<int64_t>(16, std::max<int64_t>(2, nstrips * d.ny / 2048)));
+  const int64_t grid = nstrips * ((d.ny + L - 1) / L);
+  hipLaunchKernelGGL(k_fields<S>, dim3((unsigned)grid), dim3(threads), 0, st,
+                     static_cast<const typename Store<S>::E*>(src), d, (int)L, (int)nstrips, rho, vx, vy, p);
   return hipGetLastError();
 }
 
 hipError_t launch_moments(int prec, const void* src, const RunDev& d, double* rho, double* vx,
-                          double* vy, double* p, double* psi, hipStream_t st) {
-  if (prec == LBM_PREC_F64) return launch_moments_s<double>(src, d, rho, vx, vy, p, psi, st);
-  if (prec == LBM_PREC_F32DEV) return launch_moments_s<float>(src, d, rho, vx, vy, p, psi, st);
-  if (prec == LBM_PREC_F32DEV_F64) return launch_moments_s<f32s_f64a>(src, d, rho, vx, vy, p, psi, st);
-  return launch_moments_s<__half>(src, d, rho, vx, vy, p, psi, st);
+                          double* vy, double* p, hipStream_t st) {
+  if (prec == LBM_PREC_F64) return launch_fields_s<double>(src, d, rho, vx, vy, p, st);
+  if (prec == LBM_PREC_F32DEV) return launch_fields_s<float>(src, d, rho, vx, vy, p, st);
+  if (prec == LBM_PREC_F32DEV_F64) return launch_fields_s<f32s_f64a>(src, d, rho, vx, vy, p, st);
+  return launch_fields_s<__half>(src, d, rho, vx, vy, p, st);
 }
 
 // Mass partials of kMassBlocks work-groups into part_i/part_d, then the final
-// sums into out[0..2] (see k_mass_final).
+// sums into out[0..2] and *flag (nullable) into out[3] (see k_mass_final).
 hipError_t launch_mass(int prec, const void* src, const RunDev& d, __int128* pi, double* pd,
-                       unsigned long long* out, hipStream_t st) {
+                       const unsigned long long* flag, unsigned long long* out, hipStream_t st) {
   if (prec == LBM_PREC_F64)
     hipLaunchKernelGGL(k_mass<double>, dim3(kMassBlocks), dim3(256), 0, st, (const double*)src, d, pi, pd);
   else if (prec == LBM_PREC_F32DEV)
@@ -463,8 +468,8 @@ hipError_t launch_mass(int prec, const void* src, const RunDev& d, __int128* pi,
     hipLaunchKernelGGL(k_mass<f32s_f64a>, dim3(kMassBlocks), dim3(256), 0, st, (const float*)src, d, pi, pd);
   else
     hipLaunchKernelGGL(k_mass<__half>, dim3(kMassBlocks), dim3(256), 0, st, (const __half*)src, d, pi, pd);
-  hipLaunchKernelGGL(k_mass_final, dim3(1), dim3(1), 0, st, (const __int128*)pi, (const double*)pd,
-                     kMassBlocks, out);
+  hipLaunchKernelGGL(k_mass_final, dim3(1), dim3(256), 0, st, (const __int128*)pi, (const double*)pd,
+                     kMassBlocks, flag, out);
   return hipGetLastError();
 }
 
@@ -553,7 +558,7 @@ struct lbm_ctx {
   size_t ws_bytes;
   void* buf[2];
   int cur;
-  double* aux;  // 5 planes of nx*ny doubles: rho, vx, vy, p, psi
+  double* aux;  // 5 planes of nx*ny doubles: rho, vx, vy, p and one spare
   __int128* part_i;   // mass scratch: partials and the result words
   double* part_d;
   unsigned long long* mass_out;
@@ -852,7 +857,7 @@ int lbm_status(lbm_ctx* c, int64_t* step, int64_t* diverged_at) {
 int lbm_moments_device(lbm_ctx* c, double* rho, double* vx, double* vy, double* p) {
   if (!c || !rho || !vx || !vy || !p) return LBM_EINVAL;
   const size_t n = (size_t)c->p.nx * c->p.ny;
-  HIPCHK(launch_moments(c->p.precision, c->buf[c->cur], c->d, rho, vx, vy, p, c->aux + 4 * n, c->st));
+  HIPCHK(launch_moments(c->p.precision, c->buf[c->cur], c->d, rho, vx, vy, p, c->st));
   return LBM_OK;
 }
 
@@ -878,7 +883,7 @@ int lbm_flat_profile(lbm_ctx* c, double* rho_bar, double* p_n) {
   double* rb = a + n;
   double* pn = rb + c->p.nx;
   HIPCHK(launch_moments(c->p.precision, c->buf[c->cur], c->d, a, a + n, a + 2 * n, a + 3 * n,
-                        a + 4 * n, c->st));
+                        c->st));
   const dim3 blk(256), grd((c->p.nx + 255) / 256);
   hipLaunchKernelGGL(k_colmean, grd, blk, 0, c->st, (const double*)a, c->p.nx, c->p.ny, rb);
   if (p_n)
@@ -891,7 +896,7 @@ int lbm_flat_profile(lbm_ctx* c, double* rho_bar, double* p_n) {
 }
 
 // The three result words of the mass kernels into the caller's outputs.
-static void mass_words(const unsigned long long w[3], int64_t* fixed, double* mass) {
+static void mass_words(const unsigned long long* w, int64_t* fixed, double* mass) {
   if (fixed) {
     fixed[0] = (int64_t)w[0];
     fixed[1] = (int64_t)w[1];
@@ -907,7 +912,7 @@ int lbm_surface_tension(lbm_ctx* c, double* gamma) {
   double* rb = a + n;  // column means and the result reuse the velocity plane
   double* g = rb + c->p.nx;
   HIPCHK(launch_moments(c->p.precision, c->buf[c->cur], c->d, a, a + n, a + 2 * n, a + 3 * n,
-                        a + 4 * n, c->st));
+                        c->st));
   hipLaunchKernelGGL(k_colmean, dim3((c->p.nx + 255) / 256), dim3(256), 0, c->st, (const double*)a,
                      c->p.nx, c->p.ny, rb);
   hipLaunchKernelGGL(k_surface_tension, dim3(1), dim3(256), 0, c->st, (const double*)rb, c->d,
@@ -920,12 +925,12 @@ int lbm_surface_tension(lbm_ctx* c, double* gamma) {
 
 int lbm_mass(lbm_ctx* c, int64_t* fixed, double* mass) {
   if (!c) return LBM_EINVAL;
-  HIPCHK(launch_mass(c->p.precision, c->buf[c->cur], c->d, c->part_i, c->part_d, c->mass_out, c->st));
-  unsigned long long w[3];
+  HIPCHK(launch_mass(c->p.precision, c->buf[c->cur], c->d, c->part_i, c->part_d, c->flag, c->mass_out, c->st));
+  unsigned long long w[4];
   HIPCHK(hipMemcpyAsync(w, c->mass_out, sizeof w, hipMemcpyDeviceToHost, c->st));
   HIPCHK(hipStreamSynchronize(c->st));
   mass_words(w, fixed, mass);
-  return lbm_status(c, nullptr, nullptr);
+  return w[3] == kNoDiv ? LBM_OK : LBM_EDIVERGED;
 }
 
 int lbm_mass_noalloc(const void* dev_populations, int32_t nx, int32_t ny, int32_t precision,
@@ -948,7 +953,7 @@ int lbm_mass_noalloc(const void* dev_populations, int32_t nx, int32_t ny, int32_
   double* pd = reinterpret_cast<double*>(pi + kMassBlocks);
   unsigned long long* out = reinterpret_cast<unsigned long long*>(pd + kMassBlocks);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  HIPCHK(launch_mass(precision, dev_populations, d, pi, pd, out, st));
+  HIPCHK(launch_mass(precision, dev_populations, d, pi, pd, nullptr, out, st));
   unsigned long long w[3];
   HIPCHK(hipMemcpyAsync(w, out, sizeof w, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
@@ -1569,7 +1574,7 @@ int lbm_batch_moments(lbm_batch* b, int32_t run, double* rho, double* vx, double
   const size_t n = (size_t)d.nx * d.ny;
   double* a = b->aux;
   const char* src = static_cast<const char*>(b->buf[b->cur]) + d.off * b->esize;
-  HIPCHK(launch_moments(b->prec, src, d, a, a + n, a + 2 * n, a + 3 * n, a + 4 * n, b->st));
+  HIPCHK(launch_moments(b->prec, src, d, a, a + n, a + 2 * n, a + 3 * n, b->st));
   double* outs[4] = {rho, vx, vy, p};
   for (int i = 0; i < 4; ++i)
     if (outs[i]) HIPCHK(hipMemcpyAsync(outs[i], a + i * n, n * sizeof(double), hipMemcpyDeviceToHost, b->st));
