@@ -56,6 +56,11 @@ int mlp_set_norm(mlp_ctx* c, const mlp_norm* norm);
 /* Y = network(X) in output units (log rho_l, log rho_g); 1 <= B <= max_batch. */
 int mlp_forward(mlp_ctx* c, const float* dev_X, float* dev_Y, int32_t B);
 
+/* The same for host arrays (synchronous): the rows go through a pinned staging buffer
+ * of the context that the kernel reads and writes directly (80 KB of host memory,
+ * allocated by the first call, freed by mlp_destroy). */
+int mlp_forward_host(mlp_ctx* c, const float* host_X, float* host_Y, int32_t B);
+
 /* Gradient of the loss for targets dev_T (log rho) into dev_grad (MLP_NPARAMS
  * floats) and the loss into dev_loss (1 float); deterministic (fixed-order
  * reductions, no atomics). */
@@ -68,6 +73,13 @@ int mlp_adam(mlp_ctx* c, const float* dev_grad, float lr, float beta1, float bet
 /* Gradient + Adam (beta1 0.9, beta2 0.999, eps 1e-8); loss to dev_loss (nullable). */
 int mlp_train_step(mlp_ctx* c, const float* dev_X, const float* dev_T, int32_t B, float lr,
                    float* dev_loss);
+
+/* n steps of mlp_train_step on minibatches of B rows gathered from X and T: step i takes
+ * the rows dev_idx[i*B .. i*B + B-1] (device, 64-bit, each a valid row) with the
+ * learning rate lr[i] (host, n values, each > 0); loss of the last step to dev_loss
+ * (nullable).  Asynchronous. */
+int mlp_train_steps(mlp_ctx* c, const float* dev_X, const float* dev_T, const int64_t* dev_idx, int32_t B,
+                    int32_t n, const float* lr, float* dev_loss);
 
 int mlp_destroy(mlp_ctx* c);
 

@@ -32,6 +32,9 @@ _SIGS = {
     "mlp_gradient": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
     "mlp_adam": (C.c_int, [C.c_void_p, C.c_void_p, C.c_float, C.c_float, C.c_float, C.c_float]),
     "mlp_train_step": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_float, C.c_void_p]),
+    "mlp_forward_host": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32]),
+    "mlp_train_steps": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
+                                  C.c_void_p, C.c_void_p]),
     "mlp_destroy": (C.c_int, [C.c_void_p]),
 }
 _ready = False
@@ -96,11 +99,19 @@ class Mlp:
         _check(lib().mlp_set_params(self.ctx, p.ctypes.data), "mlp_set_params")
 
     def forward(self, X) -> np.ndarray:
-        Xd = X if isinstance(X, torch.Tensor) else _dev(X, 3, self.device)
-        B = Xd.shape[0]
+        if not isinstance(X, torch.Tensor):
+            Xh = np.ascontiguousarray(X, dtype=np.float32)
+            if Xh.ndim != 2 or Xh.shape[1] != 3:
+                raise ValueError("expected an (n, 3) array")
+            Yh = np.empty((Xh.shape[0], 2), dtype=np.float32)
+            torch.cuda.current_stream(self.device).synchronize()
+            _check(lib().mlp_forward_host(self.ctx, Xh.ctypes.data, Yh.ctypes.data, Xh.shape[0]),
+                   "mlp_forward_host")
+            return Yh
+        B = X.shape[0]
         Y = torch.empty((B, 2), dtype=torch.float32, device=self.device)
         torch.cuda.current_stream(self.device).synchronize()
-        _check(lib().mlp_forward(self.ctx, Xd.data_ptr(), Y.data_ptr(), B), "mlp_forward")
+        _check(lib().mlp_forward(self.ctx, X.data_ptr(), Y.data_ptr(), B), "mlp_forward")
         self.stream.synchronize()
         return Y.cpu().numpy()
 
@@ -129,23 +140,28 @@ class Mlp:
         hist = []
         torch.cuda.current_stream(self.device).synchronize()
         nb = max(1, n // batch)
-        perm = None
-        for s in range(steps):
+        rates = [lr * 0.5 * (1.0 + math.cos(math.pi * s / steps)) if cosine else lr for s in range(steps)]
+        rates = (C.c_float * max(steps, 1))(*rates)
+        perm, s = None, 0
+        while s < steps:
             k = s % nb
+            # steps of this call: to the end of the epoch, or to the next logged step
+            m = min(nb - k, steps - s)
+            if log_every:
+                m = min(m, -s % log_every + 1, steps - s)
             with torch.cuda.stream(self.stream):
                 if k == 0:
                     # each epoch's permutation is copied on the training stream, so
-                    # the minibatch gathers below are ordered after the copy
+                    # the minibatches gathered from it are ordered after the copy
                     perm = torch.randperm(n, generator=g).to(self.device)
-                idx = perm[k * batch:(k + 1) * batch]
-                xb = Xd.index_select(0, idx).contiguous()
-                tb = Td.index_select(0, idx).contiguous()
-                lr_s = lr * 0.5 * (1.0 + math.cos(math.pi * s / steps)) if cosine else lr
-                _check(lib().mlp_train_step(self.ctx, xb.data_ptr(), tb.data_ptr(), xb.shape[0], lr_s,
-                                            self.loss.data_ptr()), "mlp_train_step")
-            if log_every and (s % log_every == 0 or s == steps - 1):
+                _check(lib().mlp_train_steps(self.ctx, Xd.data_ptr(), Td.data_ptr(),
+                                             perm.data_ptr() + 8 * k * batch, batch, m,
+                                             C.addressof(rates) + 4 * s, self.loss.data_ptr()),
+                       "mlp_train_steps")
+            s += m
+            if log_every and ((s - 1) % log_every == 0 or s == steps):
                 self.stream.synchronize()
-                hist.append((s, float(self.loss.cpu()[0])))
+                hist.append((s - 1, float(self.loss.cpu()[0])))
         self.stream.synchronize()
         return hist
 
