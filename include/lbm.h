@@ -218,10 +218,12 @@ int lbm_load_state(lbm_ctx* c, const void* host_buf, size_t bytes);
  * waves selects the strip width, 4 or 8 for at most 64*k - (4*steps - 2)
  * columns (k = 4 with FP16 storage, else 3; the 4*steps - 2 extra columns are
  * recomputed), and with steps = 4 also 2 for k = 2; strips are spread evenly
- * over nx (FP64: strip edges on 64-byte boundaries).  steps = 2: depth 1 or 2
+ * over nx (FP64: strip edges on 64-byte boundaries).  waves = 1 with steps > 1
+ * (rows 0, depth 1, any storage type and size) takes square patches, one node
+ * per thread, for small lattices.  steps = 2: depth 1 or 2
  * (the same); steps = 3 and 4: depth 1; steps = 3: FP64 and
  * FP32-storage-FP64-collision lattices of at least 5 x 5 only (else
- * LBM_ENOTSUP or LBM_EINVAL).  rows = 0 selects the balanced schedule, in which
+ * LBM_ENOTSUP or LBM_EINVAL; patches: all).  rows = 0 selects the balanced schedule, in which
  * a grid sized to the GPU's resident capacity splits all strip rows evenly;
  * rows in [0, 128].  A remainder of lbm_step(n) smaller than `steps` runs as
  * one or two launches of fewer steps.  lbm_tune times the candidates

@@ -1044,6 +1044,96 @@ __global__ __launch_bounds__(64 * NW * TS) void k_pipe(const typename Store<S>::
   }
 }
 
+// ---- small lattices: several steps of a patch, one node per thread ------------------
+
+// A block holds a patch of RX x RY nodes, a thread a node, and advances it TS steps on
+// chip: every node pulls from global memory once, psi and the eight moving populations
+// of each step go to the neighbours through LDS (two barriers per step), and the inner
+// (RX - 2H) x (RY - 2H) nodes, H = 2 TS - 1, which the halo's wrong edge has not
+// reached, are stored.  For lattices that leave most of the chip idle: a step there is
+// latency (a launch, a load, two exchanges), and the march of the other kernels puts
+// rows one after the other.  The recomputed halo costs 7.6 (22 x 22, four steps), 2.1 or
+// 1.5 (32 x 32, three, two) times the work, so lattices that fill the chip take the pipe.
+// us per step in a graph, FP64, best other tile -> patch: 64 x 32 4.3 -> 1.6, 128 x 64 4.4
+// -> 1.7, 200 x 150 5.0 -> 2.6, 300 x 300 6.3 -> 3.5, 512 x 512 7.4 -> 7.4, 777 x 643 9.5
+// -> 12.8.  Same arithmetic in the same order as single steps: bitwise equal.
+template <typename S, int RX, int RY, int TS, bool MRT = false>
+__global__ __launch_bounds__((RX * RY + 63) / 64 * 64) void k_patch(
+    const typename Store<S>::E* __restrict__ src, typename Store<S>::E* __restrict__ dst, RunDev d, int ntx,
+    const unsigned long long* stepbase, unsigned long long steplocal, unsigned long long* flag) {
+  using T = Store<S>;
+  using R = typename T::R;
+  constexpr int H = 2 * TS - 1, TX = RX - 2 * H, TY = RY - 2 * H, N = RX * RY, PAD = RX + 1;
+  __shared__ double psi[N + 2 * PAD];
+  __shared__ R ex[TS > 1 ? 8 : 1][N + 2 * PAD];
+  const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
+  const bool frozen = *flag < step;
+  const int ty = blockIdx.x / ntx, tx = blockIdx.x - ty * ntx;
+  const int i = min((int)threadIdx.x, N - 1);  // the last wave's idle lanes repeat a node
+  const int ry = i / RX, rx = i - ry * RX;
+  const int gx = tx * TX + rx - H, gy = ty * TY + ry - H;
+  const bool out = threadIdx.x < N && rx >= H && rx < RX - H && ry >= H && ry < RY - H && gx < d.nx && gy < d.ny;
+  int x = gx % d.nx, y = gy % d.ny;
+  x = x < 0 ? x + d.nx : x;
+  y = y < 0 ? y + d.ny : y;
+  R f[9];
+  if (frozen) {
+    if (!out) return;
+#pragma unroll
+    for (int a = 0; a < 9; ++a) {
+      const int64_t o = (int64_t)y * d.rs + a * d.plane + x;
+      if (index_ok(o, d.elems)) dst[o] = src[o];
+    }
+    return;
+  }
+  const Cols cx = cols_of(x, d.nx);
+  const int ym = y == 0 ? d.ny - 1 : y - 1, yp = y == d.ny - 1 ? 0 : y + 1;
+  {
+    const int64_t P = d.plane, r0 = (int64_t)y * d.rs, rm = (int64_t)ym * d.rs, rp = (int64_t)yp * d.rs;
+    const int64_t o[9] = {r0 + cx.x,          r0 + P + cx.xm,     rm + 2 * P + cx.x,
+                          r0 + 3 * P + cx.xp, rp + 4 * P + cx.x,  rm + 5 * P + cx.xm,
+                          rm + 6 * P + cx.xp, rp + 7 * P + cx.xp, rp + 8 * P + cx.xm};
+#pragma unroll
+    for (int a = 0; a < 9; ++a) f[a] = index_ok(o[a], d.elems) ? T::ld(src + o[a]) : R(0);
+  }
+  double* ps = psi + PAD + i;
+  bool bad = false;
+  int first = TS;
+#pragma unroll
+  for (int l = 0; l < TS; ++l) {
+    NodeQ<S> q;
+    *ps = eval_psi<S>(f, d, q);
+    lds_barrier();
+    const bool b = finish_node<S, MRT>(f, q, ps - RX, ps, ps + RX, 0, d);
+    if (b && out && !bad) first = l;
+    bad |= b && out;
+    if (l < TS - 1) {
+      R(*e)[N + 2 * PAD] = ex;
+      const int k = PAD + i;
+#pragma unroll
+      for (int a = 1; a < 9; ++a) e[a - 1][k] = T::round(f[a]);
+      f[0] = T::round(f[0]);
+      lds_barrier();
+      f[1] = e[0][k - 1];
+      f[2] = e[1][k - RX];
+      f[3] = e[2][k + 1];
+      f[4] = e[3][k + RX];
+      f[5] = e[4][k - RX - 1];
+      f[6] = e[5][k - RX + 1];
+      f[7] = e[6][k + RX + 1];
+      f[8] = e[7][k + RX - 1];
+    }
+  }
+  if (out) {
+#pragma unroll
+    for (int a = 0; a < 9; ++a) {
+      const int64_t o = (int64_t)y * d.rs + a * d.plane + x;
+      if (index_ok(o, d.elems)) T::st(dst + o, f[a]);
+    }
+  }
+  if (bad) atomicMin(flag, step + first);
+}
+
 // Persistent batched step: blocks of XCD k walk the k-th contiguous eighth of
 // the work list.  Grid must be a multiple of 8.
 template <typename S, int NW, int PF, bool MRT = false>

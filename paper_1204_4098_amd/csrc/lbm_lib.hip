@@ -284,11 +284,28 @@ hipError_t launch_pipe_t(const void* src, void* dst, const RunDev& d, int L,
 // arithmetic.
 bool has_step3(int prec) { return prec == LBM_PREC_F64 || prec == LBM_PREC_F32DEV_F64; }
 
+template <typename S, int RX, int RY, int TS, bool MRT>
+hipError_t launch_patch_t(const void* src, void* dst, const RunDev& d, const unsigned long long* base,
+                          unsigned long long local, unsigned long long* flag, hipStream_t st) {
+  constexpr int H = 2 * TS - 1, TX = RX - 2 * H, TY = RY - 2 * H;
+  const int ntx = (d.nx + TX - 1) / TX;
+  const int64_t grid = (int64_t)ntx * ((d.ny + TY - 1) / TY);
+  using E = typename Store<S>::E;
+  hipLaunchKernelGGL((k_patch<S, RX, RY, TS, MRT>), dim3((unsigned)grid), dim3((RX * RY + 63) / 64 * 64), 0, st,
+                     static_cast<const E*>(src), static_cast<E*>(dst), d, ntx, base, local, flag);
+  return hipGetLastError();
+}
+
 template <typename S, bool MRT = false>
 hipError_t launch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev& d,
                          const unsigned long long* base, unsigned long long local,
                          unsigned long long* flag, hipStream_t st) {
   constexpr int NW = pipe_nw<S>(4);
+  if (t.nw == 1) {  // patches (see k_patch)
+    if (t.ts == 2) return launch_patch_t<S, 32, 32, 2, MRT>(src, dst, d, base, local, flag, st);
+    if (t.ts == 3) return launch_patch_t<S, 32, 32, 3, MRT>(src, dst, d, base, local, flag, st);
+    return launch_patch_t<S, 22, 22, 4, MRT>(src, dst, d, base, local, flag, st);
+  }
   if (t.ts == 2) return launch_pipe_t<S, NW, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
   if (t.ts == 4)
     return t.nw == 2 ? launch_pipe_t<S, 2, 4, MRT>(src, dst, d, t.L, base, local, flag, st)
@@ -299,11 +316,11 @@ hipError_t launch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev
 }
 
 // Steps of the next launch of tile t with `left` steps to go: the tile's, or what is
-// left (three only where that kernel exists).  Rows of 2^32 bytes and more take single
-// steps: the multi-step kernels address a row with 32-bit byte offsets.
+// left (three only where that kernel exists: patches, FP64 arithmetic).  Rows of 2^32
+// bytes and more take single steps: the pipe addresses a row with 32-bit byte offsets.
 int next_ts(int prec, int nx, const Tile& t, int64_t left) {
   int ts = (int)std::min<int64_t>(t.ts, left);
-  if (ts == 3 && !has_step3(prec)) ts = 2;
+  if (ts == 3 && t.nw != 1 && !has_step3(prec)) ts = 2;
   if (ts > 1 && (int64_t)nx * esize_of(prec) >= (1ll << 32)) ts = 1;
   return ts;
 }
@@ -599,17 +616,21 @@ constexpr int kStepWaves[] = {1, 2, 4, 8, 16};
 constexpr int kBatchWaves[] = {1, 2, 4, 8};
 
 // A launch shape.  Multi-step tiles: strip class nw 4 (8 is the same) or 2 (narrow
-// strips: batches, and single lattices at four steps); three steps only for single
-// lattices, with depth 1.
+// strips: batches, and single lattices at four steps), or patches (nw 1, no rows; single
+// lattices); three steps only for single lattices.  More than two steps and patches: depth 1.
 bool valid_tile(int nw, int L, int pf, int maxnw, int ts = 1, bool batch = false) {
-  if (ts > 1 && nw != 4 && nw != 8 && !(nw == 2 && (batch || ts == 4))) return false;
+  const bool patch = nw == 1 && L == 0 && pf == 1 && !batch;
+  if (ts > 1 && nw != 4 && nw != 8 && !(nw == 2 && (batch || ts == 4)) && !patch) return false;
   if (ts == 3 && batch) return false;
   if (ts > 2 && pf != 1) return false;
   return (nw == 1 || nw == 2 || nw == 4 || nw == 8 || nw == 16) && nw <= maxnw && L >= 0 &&
          L <= LMAX && (pf == 1 || pf == 2) && ts >= 1 && ts <= 4;
 }
 
+// Tile t with ts steps per launch (a remainder; a patch's single step takes one-row
+// chunks, which give a small lattice the most blocks).
 Tile with_steps(Tile t, int ts) {
+  if (t.nw == 1 && t.ts > 1 && ts == 1) t.L = 1;
   t.ts = ts;
   return t;
 }
@@ -1021,8 +1042,8 @@ int lbm_load_state(lbm_ctx* c, const void* host, size_t bytes) {
 
 int lbm_set_tile(lbm_ctx* c, int32_t nw, int32_t L, int32_t depth, int32_t steps) {
   if (!c || !valid_tile(nw, L, depth, 16, steps)) return LBM_EINVAL;
-  if (steps == 3 && !has_step3(c->p.precision)) return LBM_ENOTSUP;
-  if (steps == 3 && (c->p.nx < 5 || c->p.ny < 5)) return LBM_EINVAL;  // halo of 5 wraps once
+  if (steps == 3 && nw != 1 && !has_step3(c->p.precision)) return LBM_ENOTSUP;
+  if (steps == 3 && nw != 1 && (c->p.nx < 5 || c->p.ny < 5)) return LBM_EINVAL;
   c->tile = Tile{nw, L, depth, steps};
   return prepare_graphs(c);
 }
@@ -1043,17 +1064,25 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
   const int64_t nodes = (int64_t)c->p.nx * c->p.ny;
   const int reps = nodes >= (1 << 22) ? 3 : 10;
   std::vector<Tile> cand;
+  // Below 2^16 nodes the patches have been at least 1.8 times as fast as anything else, so
+  // of the other families only the likeliest are timed there (tuning is most of the time
+  // it takes to set such a lattice up); above 2^18 they lose to the pipe and are left out.
+  const bool tiny = nodes < (1 << 16);
+  if (nodes <= (1 << 18))
+    for (int ts : {2, 3, 4}) cand.push_back(Tile{1, 0, 1, ts});
   for (int nw : kStepWaves) {
-    if (nw > 1 && 64 * (nw / 2) >= c->p.nx) continue;
+    if ((nw > 1 && 64 * (nw / 2) >= c->p.nx) || (tiny && nw > 2)) continue;
     for (int pf : {1, 2})
       for (int L : {0, 1, 2, 4, 8, 16, 32, 64, 128})
-        if (L <= 2 * c->p.ny && (L == 0 || L > 2 || nodes < (1 << 20)))  // 1-2 rows: small lattices
+        if (L <= 2 * c->p.ny && (L == 0 || L > 2 || nodes < (1 << 20)) &&  // 1-2 rows: small lattices
+            (!tiny || (pf == 1 && L <= 8)))
           cand.push_back(Tile{nw, L, pf, 1});
   }
   for (int L : {0, 16, 32, 64, 128})
     if (L <= 2 * c->p.ny)
       for (const Tile& t : {Tile{4, L, 1, 4}, Tile{2, L, 1, 4}, Tile{4, L, 1, 2}})
-        if (next_ts(c->p.precision, c->p.nx, t, t.ts) == t.ts && (t.ts == 4 || L == 0 || L == 32))
+        if (next_ts(c->p.precision, c->p.nx, t, t.ts) == t.ts && (t.ts == 4 || L == 0 || L == 32) &&
+            (!tiny || L == 16))
           cand.push_back(t);
   const int pst = pick_tile(
       cand,

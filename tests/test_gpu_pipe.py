@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
 # widest strip of a tile: 64 k - (4 steps - 2) columns, k = 4 (FP16 storage) or 3, 2 for
 # the narrow class; FP64 strip edges are rounded down to 8 columns
 FOUR = [(4, 0, 1, 4), (2, 0, 1, 4), (4, 5, 1, 4), (2, 1, 1, 4), (8, 16, 1, 4)]
+# patches of 22 x 22 (four steps: 8 x 8 stored) and 32 x 32 nodes (26 and 22 square)
+PATCH = [(1, 0, 1, 4), (1, 0, 1, 3), (1, 0, 1, 2)]
 
 
 @pytest.fixture(scope="module")
@@ -58,6 +60,17 @@ def test_four_steps_bitwise_at_strip_edges(L, nx, ny, prec):
         assert np.array_equal(_run(L, gp, rho0, tile, 11), ref), tile
 
 
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+@pytest.mark.parametrize("nx,ny", [(3, 3), (5, 4), (8, 8), (9, 7), (22, 23), (26, 27), (64, 32), (130, 45)])
+def test_patches_bitwise(L, nx, ny, prec):
+    gp, _ = pair(L, nx, ny, t=0.9, tau=0.9, scheme=2, sigma=0.05, precision=prec)
+    rho0 = _rho(nx, ny, nx + ny)
+    ref = _run(L, gp, rho0, (2, 8, 1), 23)
+    for tile in PATCH:
+        assert np.array_equal(_run(L, gp, rho0, tile, 23), ref), tile
+        assert np.array_equal(_run(L, gp, rho0, tile, 23, graph=10), ref), tile
+
+
 @pytest.mark.parametrize("prec,rates", [(0, None), (0, (1.3, 1.1, 1.2)), (1, (1.3, 1.1, 1.2)), (2, None)])
 @pytest.mark.parametrize("k", [6, 10, 12])
 def test_four_step_graphs_bitwise(L, k, prec, rates):
@@ -65,7 +78,7 @@ def test_four_step_graphs_bitwise(L, k, prec, rates):
     gp, _ = pair(L, 300, 70, t=0.8, tau=0.8, scheme=2, sigma=0.105, precision=prec)
     rho0 = slab_rho(300, 70, CS, 0.8, seed=6)
     ref = _run(L, gp, rho0, (2, 8, 1), 5 * k + 7, rates=rates)
-    for tile in [(4, 0, 1, 4), (2, 0, 1, 4)]:
+    for tile in [(4, 0, 1, 4), (2, 0, 1, 4), (1, 0, 1, 4), (1, 0, 1, 3)]:
         assert np.array_equal(_run(L, gp, rho0, tile, 5 * k + 7, graph=k, rates=rates), ref), tile
 
 
@@ -75,10 +88,11 @@ def test_four_step_schemes_bitwise(L, scheme, eos, t):
     gp, _ = pair(L, 300, 70, t=t, tau=0.7, scheme=scheme, sigma=0.105, eos=eos)
     rho0 = slab_rho(300, 70, eos, t, seed=8)
     ref = _run(L, gp, rho0, (2, 8, 1), 41)
-    assert np.array_equal(_run(L, gp, rho0, (4, 0, 1, 4), 41), ref)
+    for tile in [(4, 0, 1, 4), (1, 0, 1, 4)]:
+        assert np.array_equal(_run(L, gp, rho0, tile, 41), ref), tile
 
 
-@pytest.mark.parametrize("tile", [(4, 0, 1, 4), (2, 16, 1, 4), (4, 0, 1, 3)])
+@pytest.mark.parametrize("tile", [(4, 0, 1, 4), (2, 16, 1, 4), (4, 0, 1, 3), (1, 0, 1, 4), (1, 0, 1, 3)])
 def test_multi_step_divergence_step_and_freeze(L, tile):
     # the step reported is the first with a bad node, whichever step of a launch it is,
     # and the state stays what the diverging launch wrote
@@ -136,7 +150,7 @@ def test_four_steps_in_bounds(monkeypatch, prec):
         gp, _ = pair(L, nx, ny, t=0.9, tau=0.9, scheme=2, sigma=0.05, precision=prec)
         gps.append(gp)
         rhos.append(_rho(nx, ny, nx + ny))
-        for tile in FOUR:
+        for tile in FOUR + PATCH:
             lat = L.Lattice(gp, rhos[-1])
             lat.set_tile(*tile)
             lat.step(9)
@@ -152,7 +166,8 @@ def test_four_steps_in_bounds(monkeypatch, prec):
 def test_four_step_tiles_rejected_where_unsupported(L):
     gp, _ = pair(L, 64, 32, t=0.8, tau=0.8, scheme=2, sigma=0.1)
     lat = L.Lattice(gp, slab_rho(64, 32, CS, 0.8, seed=1))
-    for tile in [(1, 0, 1, 4), (16, 0, 1, 4), (4, 0, 2, 4), (4, 0, 1, 5), (2, 0, 1, 3), (2, 0, 1, 2)]:
+    for tile in [(1, 4, 1, 4), (1, 0, 2, 2), (16, 0, 1, 4), (4, 0, 2, 4), (4, 0, 1, 5), (2, 0, 1, 3),
+                 (2, 0, 1, 2)]:
         with pytest.raises(L.LbmError):
             lat.set_tile(*tile)
     lat.set_tile(2, 0, 1, 4)
