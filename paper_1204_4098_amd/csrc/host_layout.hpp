@@ -5,6 +5,8 @@
 #include <algorithm>
 #include <cstddef>
 #include <cstdint>
+#include <functional>
+#include <queue>
 #include <utility>
 #include <vector>
 
@@ -12,7 +14,8 @@ namespace lbm {
 
 // A tile of the batched launch.  In the balanced schedule an item is a whole
 // strip of one run and row0 is its first row in the concatenated row space of
-// all items (rows of earlier items summed); item lists leave it 0.
+// all items (rows of earlier items summed); in item lists entry b's row0 is the first
+// item of block b (deal).
 struct Item {
   int32_t run, x0, y0, ncols, nrows, row0;
 };
@@ -100,6 +103,38 @@ inline int64_t build_items(int nruns, const int* nx, const int* ny, int nw, int 
       }
   }
   return rows;
+}
+
+// Deal a list of items (chunks) to nblocks blocks of about equal cost, an item's cost
+// being its rows plus `fill` (what starting it costs in rows): longest first, each to the
+// block with the least so far.  The list is reordered block by block and row0 of entry b
+// (b < nblocks <= items) becomes the index of block b's first item.  (Dealt in turn, 838
+// chunks of 32 rows of a sweep over 256 blocks left the fullest with 212 rows of cost for
+// a mean of 155.)
+inline void deal(std::vector<Item>& items, int nblocks, int fill) {
+  const int n = (int)items.size();
+  std::vector<int> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return items[a].nrows > items[b].nrows; });
+  using Load = std::pair<int64_t, int>;  // cost so far, block
+  std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
+  for (int b = 0; b < nblocks; ++b) least.push({0, b});
+  std::vector<std::vector<int>> mine(nblocks);
+  for (int i : order) {
+    const Load l = least.top();
+    least.pop();
+    mine[l.second].push_back(i);
+    least.push({l.first + items[i].nrows + fill, l.second});
+  }
+  std::vector<Item> out;
+  out.reserve(n);
+  std::vector<int> first(nblocks);
+  for (int b = 0; b < nblocks; ++b) {
+    first[b] = (int)out.size();
+    for (int i : mine[b]) out.push_back(items[i]);
+  }
+  for (int b = 0; b < nblocks; ++b) out[b].row0 = first[b];
+  items.swap(out);
 }
 
 }  // namespace layout

@@ -76,31 +76,50 @@ struct RunDev {
 };
 
 
-// Balanced schedule of a batch: the concatenated rows of all strips, [0,
-// total), are split evenly over the grid; block t (XCD-remapped) marches its
-// share, one piece per item it overlaps (at most `cap` rows per piece), and
-// calls piece(item, first row in the item, rows).
+// Balanced schedule of a batch: the rows of all strips laid end to end, every strip
+// but the first preceded by `fill` units (what starting a piece costs in rows), are split
+// evenly over the grid; block t (XCD-remapped) marches its share, one piece per item it
+// overlaps (at most `cap` rows per piece), and calls piece(item, first row in the item,
+// rows).
 template <class Piece>
 __device__ __forceinline__ void balanced_pieces(const Item* __restrict__ items, int nitems, int total,
-                                                int t, int cap, Piece&& piece) {
-  int64_t r = (int64_t)total * t / gridDim.x;
-  const int64_t e = (int64_t)total * (t + 1) / gridDim.x;
-  if (r >= e) return;
-  int lo = 0, hi = nitems - 1;  // last item whose row0 <= r
+                                                int t, int cap, int fill, Piece&& piece) {
+  const int64_t len = (int64_t)total + (int64_t)fill * (nitems - 1);
+  int64_t v = len * t / gridDim.x + fill;
+  const int64_t e = len * (t + 1) / gridDim.x + fill;
+  // item k: its fill units begin at row0 + k fill, its rows `fill` later
+  auto start = [&](int k) { return (int64_t)items[k].row0 + (int64_t)k * fill; };
+  int lo = 0, hi = nitems - 1;  // last item that begins at or before v
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (items[mid].row0 <= r) lo = mid;
+    if (start(mid) <= v) lo = mid;
     else hi = mid - 1;
   }
-  int i = lo;
-  while (r < e) {
+  for (int i = lo; v < e && i < nitems;) {
     const Item it = items[i];
-    const int y = (int)(r - it.row0);
-    const int n = (int)min(min(e - r, (int64_t)(it.nrows - y)), (int64_t)cap);
-    piece(it, y, n);
-    r += n;
-    if (y + n >= it.nrows) ++i;
-    __syncthreads();  // LDS is reused by the next piece
+    const int64_t base = start(i) + fill;
+    v = max(v, base);
+    const int y = (int)(v - base);
+    const int n = (int)min(min(e - v, (int64_t)(it.nrows - y)), (int64_t)cap);
+    if (n > 0) {
+      piece(it, y, n);
+      __syncthreads();  // LDS is reused by the next piece
+      v += n;
+    }
+    if (v >= base + it.nrows) ++i;
+  }
+}
+
+// List schedule of a batch: block b's items are items[row0 of b] .. items[row0 of b + 1] - 1
+// (layout::deal).
+template <class Piece>
+__device__ __forceinline__ void listed_pieces(const Item* __restrict__ items, int nitems, Piece&& piece) {
+  const int b = blockIdx.x;
+  const int hi = b + 1 < (int)gridDim.x ? items[b + 1].row0 : nitems;
+  for (int i = items[b].row0; i < hi; ++i) {
+    const Item it = items[i];
+    piece(it, 0, it.nrows);
+    __syncthreads();  // LDS is reused by the next item
   }
 }
 
@@ -999,9 +1018,14 @@ template <typename S> constexpr int pipe_nw(int waves) {
   return waves == 2 ? 2 : std::is_same<S, __half>::value ? 4 : 3;
 }
 
+// What starting a piece costs, in rows: march rows before the first and after the last
+// row is stored (pipe), psi rows and the prologue (one-step kernels).
+constexpr int pipe_fill(int ts) { return 6 * (ts - 1) + 3; }
+constexpr int kStepFill = 3;
+
 // Single lattice: strips of at most W - 2H columns spread evenly over nx.  L > 0: one
 // block per (strip, L-row chunk).  L == 0: balanced schedule, every block marches one
-// contiguous share of the strip-major row space; a share is split where it crosses a
+// contiguous share of the strips laid end to end; a share is split where it crosses a
 // strip boundary.
 template <typename S, int NW, int TS, bool MRT = false>
 __global__ __launch_bounds__(64 * NW * TS) void k_pipe(const typename Store<S>::E* __restrict__ src,
@@ -1025,21 +1049,29 @@ __global__ __launch_bounds__(64 * NW * TS) void k_pipe(const typename Store<S>::
     else
       tile_pipe<S, NW, TS, MRT>(src, dst, d, x0, y, nc, n, step, flag, lds);
   };
-  int64_t r, e;  // this block's share of the strip-major rows
   if (L > 0) {
     const int sy = t / nstrips, s = t - sy * nstrips;
-    r = (int64_t)s * d.ny + (int64_t)sy * L;
-    e = min(r + L, (int64_t)(s + 1) * d.ny);
-  } else {
-    const int64_t total = (int64_t)nstrips * d.ny;
-    r = total * t / gridDim.x;
-    e = total * (t + 1) / gridDim.x;
+    piece(s, sy * L, min(L, d.ny - sy * L));
+    return;
   }
-  while (r < e) {
-    const int s = (int)(r / d.ny), y = (int)(r - (int64_t)s * d.ny);
-    const int n = (int)min(e - r, (int64_t)(d.ny - y));
-    piece(s, y, n);
-    r += n;
+  // Rows cost one each and every piece kFill more (the march rows that fill and drain
+  // the pipeline), so shares are equal on a line on which every strip but the first is
+  // preceded by kFill units, not in rows alone: a share that crosses into the next strip
+  // pays for the second fill with fewer rows.  us per launch of four steps, equal rows ->
+  // equal cost: 4096 x 4096 FP64 534 -> 529, 3000 x 2501 FP32 218 -> 207, 1500 x 1001 FP32
+  // with FP64 collide 75 -> 63, 1024 x 1024 FP64 68 -> 55, 777 x 643 53 -> 39.
+  constexpr int kFill = pipe_fill(TS);
+  const int64_t per = (int64_t)d.ny + kFill, total = nstrips * per - kFill;
+  auto at = [&](int k, int& s, int& y) {  // strip and row where share k begins
+    const int64_t v = total * k / gridDim.x + kFill;
+    s = (int)(v / per);
+    y = max(0, (int)(v - s * per) - kFill);
+  };
+  int s, y, se, ye;
+  at(t, s, y);
+  at(t + 1, se, ye);  // the last share ends at (nstrips, 0)
+  for (; s < se || (s == se && y < ye); ++s, y = 0) {
+    piece(s, y, (s < se ? d.ny : ye) - y);
     __syncthreads();  // LDS is reused by the next piece
   }
 }
@@ -1134,8 +1166,8 @@ __global__ __launch_bounds__((RX * RY + 63) / 64 * 64) void k_patch(
   if (bad) atomicMin(flag, step + first);
 }
 
-// Persistent batched step: blocks of XCD k walk the k-th contiguous eighth of
-// the work list.  Grid must be a multiple of 8.
+// Persistent batched step over a work list (listed_pieces, or balanced_pieces where
+// total > 0).  A run frozen by divergence at an earlier launch is copied unchanged.
 template <typename S, int NW, int PF, bool MRT = false>
 __global__ __launch_bounds__(64 * NW) void k_batch_step(const typename Store<S>::E* __restrict__ src,
                                                         typename Store<S>::E* __restrict__ dst,
@@ -1148,35 +1180,22 @@ __global__ __launch_bounds__(64 * NW) void k_batch_step(const typename Store<S>:
   __shared__ typename Store<S>::P ring[4][64 * NW + 2];
   __shared__ typename Store<S>::P haloL[LMAX + 2], haloR[LMAX + 2];
   const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
-  if (total > 0) {  // balanced schedule over whole-strip items
-    balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), LMAX,
-                    [&](const Item& it, int y, int n) {
-                      const RunDev d = runs[it.run];
-                      if (flags[it.run] < step)
-                        copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n);
-                      else
-                        tile_step<S, NW, PF, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols,
-                                                  n, step, &flags[it.run], ring, haloL, haloR);
-                    });
-    return;
-  }
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nb = gridDim.x >> 3;
-  const int lo = (int)((int64_t)nitems * xcd / 8), hi = (int)((int64_t)nitems * (xcd + 1) / 8);
-  for (int i = lo + slot; i < hi; i += nb) {
-    const Item it = items[i];
+  auto piece = [&](const Item& it, int y, int n) {
     const RunDev d = runs[it.run];
     if (flags[it.run] < step)  // frozen run
-      copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0, it.ncols, it.nrows);
+      copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n);
     else
-      tile_step<S, NW, PF, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0, it.ncols, it.nrows, step,
-                           &flags[it.run], ring, haloL, haloR);
-    __syncthreads();  // LDS is reused by the next item
-  }
+      tile_step<S, NW, PF, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n, step,
+                                &flags[it.run], ring, haloL, haloR);
+  };
+  if (total > 0)
+    balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), LMAX, kStepFill, piece);
+  else
+    listed_pieces(items, nitems, piece);
 }
 
-// Persistent batched launch of TS steps (tile_pipe) over a work list whose items are
-// at most W - 2H columns wide.  A run frozen by divergence at an earlier launch is
-// copied unchanged; grid must be a multiple of 8.
+// Persistent batched launch of TS steps (tile_pipe); the items are at most W - 2H columns
+// wide.
 template <typename S, int NW, int TS, bool MRT = false>
 __global__ __launch_bounds__(64 * NW * TS) void k_batch_pipe(const typename Store<S>::E* __restrict__ src,
                                                              typename Store<S>::E* __restrict__ dst,
@@ -1196,16 +1215,10 @@ __global__ __launch_bounds__(64 * NW * TS) void k_batch_pipe(const typename Stor
       tile_pipe<S, NW, TS, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n, step,
                                 &flags[it.run], lds);
   };
-  if (total > 0) {  // balanced schedule over whole-strip items (no row cap: no per-row arrays)
-    balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), 1 << 30, piece);
-    return;
-  }
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nb = gridDim.x >> 3;
-  const int lo = (int)((int64_t)nitems * xcd / 8), hi = (int)((int64_t)nitems * (xcd + 1) / 8);
-  for (int i = lo + slot; i < hi; i += nb) {
-    piece(items[i], 0, items[i].nrows);
-    __syncthreads();  // LDS is reused by the next item
-  }
+  if (total > 0)  // no row cap: no per-row arrays
+    balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), 1 << 30, pipe_fill(TS), piece);
+  else
+    listed_pieces(items, nitems, piece);
 }
 
 // Coexistence densities of flat interfaces with normal x, for every run of a

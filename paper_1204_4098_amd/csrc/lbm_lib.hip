@@ -349,104 +349,81 @@ hipError_t launch_step(int prec, const Tile& t, const void* src, void* dst, cons
   return launch_step_s<__half>(t, src, dst, d, base, local, flag, st);
 }
 
-// Grid of a batch launch: item lists take at most one block per item (a
-// multiple of 8, one eighth of the list per XCD); the balanced schedule
-// (total > 0 rows) the resident capacity, at least 8 rows per block.
-int batch_grid(const void* fn, int threads, int nitems, int total) {
-  int g = resident_blocks(fn, threads);
-  if (total > 0) return (int)std::max<int64_t>(1, std::min<int64_t>(g, total / 8));
-  g = std::min(g, (nitems + 7) / 8 * 8);
-  return std::max(8, g / 8 * 8);
+// A batch launch.  grid 0: only report the resident blocks of the tile's kernel.
+struct BatchArgs {
+  const void* src;
+  void* dst;
+  const RunDev* runs;
+  const Item* items;
+  int nitems, total, grid;
+  const unsigned long long* base;
+  unsigned long long local;
+  unsigned long long* flags;
+  hipStream_t st;
+  int* resident;
+};
+
+// Grid of a batch schedule with `resident` blocks of its kernel: item lists take at most
+// one block per item; the balanced schedule (total > 0 rows) at least 8 rows per block.
+int batch_grid(int resident, int nitems, int total) {
+  return std::max(1, std::min(resident, total > 0 ? total / 8 : nitems));
 }
 
-template <typename S, int NW, int PF, bool MRT>
-hipError_t launch_batch_t(const void* src, void* dst, const RunDev* runs, const Item* items,
-                          int nitems, int total, const unsigned long long* base,
-                          unsigned long long local, unsigned long long* flags, hipStream_t st) {
-  const int g = batch_grid((const void*)k_batch_step<S, NW, PF, MRT>, 64 * NW, nitems, total);
+template <typename S, class Kernel>
+hipError_t launch_batch_k(Kernel k, int threads, const BatchArgs& a) {
+  if (a.resident) {
+    *a.resident = resident_blocks((const void*)k, threads);
+    return hipSuccess;
+  }
   using E = typename Store<S>::E;
-  hipLaunchKernelGGL((k_batch_step<S, NW, PF, MRT>), dim3(g), dim3(64 * NW), 0, st,
-                     static_cast<const E*>(src), static_cast<E*>(dst), runs, items, nitems, total,
-                     base, local, flags);
+  hipLaunchKernelGGL(k, dim3(a.grid), dim3(threads), 0, a.st, static_cast<const E*>(a.src),
+                     static_cast<E*>(a.dst), a.runs, a.items, a.nitems, a.total, a.base, a.local, a.flags);
   return hipGetLastError();
 }
 
 template <typename S, bool MRT = false>
-hipError_t launch_batch_s(const Tile& t, const void* src, void* dst, const RunDev* runs,
-                          const Item* items, int nitems, int total, const unsigned long long* base,
-                          unsigned long long local, unsigned long long* flags, hipStream_t st) {
+hipError_t launch_batch_s(const Tile& t, const BatchArgs& a) {
   switch (t.nw * 10 + t.pf) {
-    case 11: return launch_batch_t<S, 1, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 12: return launch_batch_t<S, 1, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 21: return launch_batch_t<S, 2, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 22: return launch_batch_t<S, 2, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 41: return launch_batch_t<S, 4, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 42: return launch_batch_t<S, 4, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    case 81: return launch_batch_t<S, 8, 1, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-    default: return launch_batch_t<S, 8, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
+    case 11: return launch_batch_k<S>(k_batch_step<S, 1, 1, MRT>, 64, a);
+    case 12: return launch_batch_k<S>(k_batch_step<S, 1, 2, MRT>, 64, a);
+    case 21: return launch_batch_k<S>(k_batch_step<S, 2, 1, MRT>, 128, a);
+    case 22: return launch_batch_k<S>(k_batch_step<S, 2, 2, MRT>, 128, a);
+    case 41: return launch_batch_k<S>(k_batch_step<S, 4, 1, MRT>, 256, a);
+    case 42: return launch_batch_k<S>(k_batch_step<S, 4, 2, MRT>, 256, a);
+    case 81: return launch_batch_k<S>(k_batch_step<S, 8, 1, MRT>, 512, a);
+    default: return launch_batch_k<S>(k_batch_step<S, 8, 2, MRT>, 512, a);
   }
 }
 
-template <typename S, int NW, int TS, bool MRT>
-hipError_t launch_batch_pipe_t(const void* src, void* dst, const RunDev* runs, const Item* items,
-                               int nitems, int total, const unsigned long long* base,
-                               unsigned long long local, unsigned long long* flags, hipStream_t st) {
-  const int threads = 64 * NW * TS;
-  const int g = batch_grid((const void*)k_batch_pipe<S, NW, TS, MRT>, threads, nitems, total);
-  using E = typename Store<S>::E;
-  hipLaunchKernelGGL((k_batch_pipe<S, NW, TS, MRT>), dim3(g), dim3(threads), 0, st,
-                     static_cast<const E*>(src), static_cast<E*>(dst), runs, items, nitems, total,
-                     base, local, flags);
-  return hipGetLastError();
-}
-
 template <typename S, bool MRT = false>
-hipError_t launch_batch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev* runs,
-                               const Item* items, int nitems, int total, const unsigned long long* base,
-                               unsigned long long local, unsigned long long* flags, hipStream_t st) {
+hipError_t launch_batch_pipe_s(const Tile& t, const BatchArgs& a) {
   constexpr int NW = pipe_nw<S>(4);
   if (t.ts == 4)
-    return t.nw == 2
-               ? launch_batch_pipe_t<S, 2, 4, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st)
-               : launch_batch_pipe_t<S, NW, 4, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
-  return t.nw == 2
-             ? launch_batch_pipe_t<S, 2, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st)
-             : launch_batch_pipe_t<S, NW, 2, MRT>(src, dst, runs, items, nitems, total, base, local, flags, st);
+    return t.nw == 2 ? launch_batch_k<S>(k_batch_pipe<S, 2, 4, MRT>, 512, a)
+                     : launch_batch_k<S>(k_batch_pipe<S, NW, 4, MRT>, 256 * NW, a);
+  return t.nw == 2 ? launch_batch_k<S>(k_batch_pipe<S, 2, 2, MRT>, 256, a)
+                   : launch_batch_k<S>(k_batch_pipe<S, NW, 2, MRT>, 128 * NW, a);
 }
 
 // One launch of the batch tile: t.ts time steps of every active run;
 // mrt: the runs' descriptors carry the MRT collision (FP64 or FP32 deviation
 // storage, checked by lbm_batch_set_mrt).
-hipError_t launch_batch(int prec, bool mrt, const Tile& t, const void* src, void* dst,
-                        const RunDev* runs, const Item* items, int nitems, int total,
-                        const unsigned long long* base, unsigned long long local,
-                        unsigned long long* flags, hipStream_t st) {
+hipError_t launch_batch(int prec, bool mrt, const Tile& t, const BatchArgs& a) {
   if (mrt) {
-    if (t.ts > 1) {
-      if (prec == LBM_PREC_F64)
-        return launch_batch_pipe_s<double, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-      return launch_batch_pipe_s<float, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-    }
-    if (prec == LBM_PREC_F64)
-      return launch_batch_s<double, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-    return launch_batch_s<float, true>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+    if (t.ts > 1)
+      return prec == LBM_PREC_F64 ? launch_batch_pipe_s<double, true>(t, a) : launch_batch_pipe_s<float, true>(t, a);
+    return prec == LBM_PREC_F64 ? launch_batch_s<double, true>(t, a) : launch_batch_s<float, true>(t, a);
   }
   if (t.ts > 1) {
-    if (prec == LBM_PREC_F64)
-      return launch_batch_pipe_s<double>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-    if (prec == LBM_PREC_F32DEV)
-      return launch_batch_pipe_s<float>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-    if (prec == LBM_PREC_F32DEV_F64)
-      return launch_batch_pipe_s<f32s_f64a>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-    return launch_batch_pipe_s<__half>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+    if (prec == LBM_PREC_F64) return launch_batch_pipe_s<double>(t, a);
+    if (prec == LBM_PREC_F32DEV) return launch_batch_pipe_s<float>(t, a);
+    if (prec == LBM_PREC_F32DEV_F64) return launch_batch_pipe_s<f32s_f64a>(t, a);
+    return launch_batch_pipe_s<__half>(t, a);
   }
-  if (prec == LBM_PREC_F64)
-    return launch_batch_s<double>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-  if (prec == LBM_PREC_F32DEV)
-    return launch_batch_s<float>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-  if (prec == LBM_PREC_F32DEV_F64)
-    return launch_batch_s<f32s_f64a>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
-  return launch_batch_s<__half>(t, src, dst, runs, items, nitems, total, base, local, flags, st);
+  if (prec == LBM_PREC_F64) return launch_batch_s<double>(t, a);
+  if (prec == LBM_PREC_F32DEV) return launch_batch_s<float>(t, a);
+  if (prec == LBM_PREC_F32DEV_F64) return launch_batch_s<f32s_f64a>(t, a);
+  return launch_batch_s<__half>(t, a);
 }
 
 // Rows per block (two more are pulled for psi): 2048 blocks or more, so that every CU
@@ -1202,6 +1179,7 @@ struct lbm_batch {
   Item* d_items;
   int nitems, items_cap;
   int total_rows;  // balanced schedule: rows of all strip items (0 for item lists)
+  int grid;        // blocks the work list was dealt to, or of the balanced schedule
   unsigned long long* flags;
   unsigned long long* ctr;
   double* aux;
@@ -1249,7 +1227,13 @@ BatchLayout batch_layout(int n, const lbm_params* p) {
   return L;
 }
 
-// Work list of a tile (layout::build_items), uploaded to the device.
+// A launch from buffer s into the other.
+BatchArgs batch_args(const lbm_batch* b, int s, const unsigned long long* base, unsigned long long local) {
+  return BatchArgs{b->buf[s], b->buf[s ^ 1], b->d_runs, b->d_items, b->nitems, b->total_rows,
+                   b->grid,   base,          local,     b->flags,   b->st,     nullptr};
+}
+
+// Work list of a tile (layout::build_items, dealt to its grid), uploaded to the device.
 int batch_items(lbm_batch* b, const Tile& t) {
   std::vector<Item> items;
   std::vector<int> nx(b->nruns), ny(b->nruns);
@@ -1264,7 +1248,13 @@ int batch_items(lbm_batch* b, const Tile& t) {
                                            b->prec == LBM_PREC_F64 ? StripAlign<double>::value : 1);
   if ((int)items.size() > b->items_cap) return LBM_ENOSPACE;
   if (rows >= INT32_MAX) return LBM_EINVAL;
+  int resident = 1;
+  BatchArgs q{};
+  q.resident = &resident;
+  HIPCHK(launch_batch(b->prec, b->mrt != 0, t, q));
   b->total_rows = t.L > 0 ? 0 : (int)rows;
+  b->grid = batch_grid(resident, (int)items.size(), b->total_rows);
+  if (t.L > 0) layout::deal(items, b->grid, t.ts > 1 ? pipe_fill(t.ts) : kStepFill);
   HIPCHK(hipMemcpyAsync(b->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, b->st));
   HIPCHK(hipStreamSynchronize(b->st));
   b->nitems = (int)items.size();
@@ -1292,8 +1282,8 @@ int batch_capture(lbm_batch* b, int parity) {
   hipError_t e = hipSuccess;
   for (int s = parity, done = 0; done < b->graph_k && e == hipSuccess; s ^= 1) {
     const int ts = batch_next_ts(b->tile, b->graph_k - done);
-    e = launch_batch(b->prec, b->mrt != 0, with_steps(b->tile, ts), b->buf[s], b->buf[s ^ 1], b->d_runs,
-                     b->d_items, b->nitems, b->total_rows, b->ctr, (unsigned long long)done, b->flags, b->st);
+    e = launch_batch(b->prec, b->mrt != 0, with_steps(b->tile, ts),
+                     batch_args(b, s, b->ctr, (unsigned long long)done));
     done += ts;
   }
   if (e == hipSuccess) {
@@ -1465,8 +1455,7 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
   while (done < n) {
     const int s = b->cur;
     const Tile t = with_steps(b->tile, batch_next_ts(b->tile, n - done));
-    HIPCHK(launch_batch(b->prec, b->mrt != 0, t, b->buf[s], b->buf[s ^ 1], b->d_runs, b->d_items, b->nitems, b->total_rows,
-                        nullptr, (unsigned long long)b->step, b->flags, b->st));
+    HIPCHK(launch_batch(b->prec, b->mrt != 0, t, batch_args(b, s, nullptr, (unsigned long long)b->step)));
     b->cur ^= 1;
     b->step += t.ts;
     done += t.ts;
@@ -1541,7 +1530,7 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
   }
   for (int nw : {2, 4})
     for (int ts : {2, 4})
-      for (int L : {0, 16, 32, 64}) cand.push_back(Tile{nw, L, 1, ts});
+      for (int L : {0, 16, 32, 64}) cand.push_back(Tile{nw, L, 1, ts});  // 64: whole runs of a sweep
   int ist = LBM_OK;
   const int pst = pick_tile(
       cand,
@@ -1552,9 +1541,8 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
         const float ms = time_launches(
             b->st,
             [&] {
-              return launch_batch(b->prec, b->mrt != 0, t, b->buf[s], b->buf[s ^ 1], b->d_runs, b->d_items,
-                                  b->nitems, b->total_rows, nullptr, (unsigned long long)b->step,
-                                  b->flags, b->st);
+              return launch_batch(b->prec, b->mrt != 0, t,
+                                  batch_args(b, s, nullptr, (unsigned long long)b->step));
             },
             5);
         return ms < 0 ? ms : ms / t.ts;  // time per lattice step

@@ -1,0 +1,60 @@
+"""Dealing of a batch work list to blocks (csrc/host_layout.hpp), compiled for the
+host: every item kept once, every block at least one, and the fullest block at most
+one item above the mean cost."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "host_layout.hpp"
+using namespace lbm;
+int main() {
+  unsigned seed = 1;
+  auto rnd = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+  for (int trial = 0; trial < 300; ++trial) {
+    std::vector<int> nx(1 + rnd(60)), ny(nx.size());
+    for (size_t i = 0; i < nx.size(); ++i) nx[i] = 3 + rnd(600), ny[i] = 3 + rnd(80);
+    const int ts[] = {1, 2, 4};
+    std::vector<Item> items;
+    layout::build_items((int)nx.size(), nx.data(), ny.data(), 2 + rnd(2), 4 + rnd(60), ts[rnd(3)], items, 8);
+    const std::vector<Item> before = items;
+    const int n = (int)items.size(), blocks = 1 + rnd(n < 256 ? n : 256), fill = rnd(22);
+    layout::deal(items, blocks, fill);
+    if ((int)items.size() != n) return 1;
+    std::vector<char> seen(n, 0);
+    long total = 0, most = 0, longest = 0;
+    for (int b = 0; b < blocks; ++b) {
+      const int lo = items[b].row0, hi = b + 1 < blocks ? items[b + 1].row0 : n;
+      if (lo < 0 || hi <= lo || hi > n) return 2;
+      long cost = 0;
+      for (int i = lo; i < hi; ++i) {
+        const Item& a = items[i];
+        int k = 0;
+        while (k < n && (seen[k] || a.run != before[k].run || a.x0 != before[k].x0 || a.y0 != before[k].y0 ||
+                         a.ncols != before[k].ncols || a.nrows != before[k].nrows)) ++k;
+        if (k == n) return 3;
+        seen[k] = 1;
+        cost += a.nrows + fill;
+        if (a.nrows + fill > longest) longest = a.nrows + fill;
+      }
+      total += cost;
+      if (cost > most) most = cost;
+    }
+    if (most > total / blocks + longest) return 4;
+  }
+  std::puts("ok");
+  return 0;
+}
+"""
+
+
+def test_deal_keeps_every_item_and_balances(tmp_path):
+    src, exe = tmp_path / "deal.cpp", tmp_path / "deal"
+    src.write_text(MAIN)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I",
+                    os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out
