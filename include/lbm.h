@@ -216,7 +216,7 @@ int lbm_load_state(lbm_ctx* c, const void* host_buf, size_t bytes);
  * the intermediate steps stay on chip (a work-group has one group of waves per
  * step, which hand them on through LDS), so they cross HBM once per launch;
  * waves selects the strip width, 4 or 8 for at most 64*k - (4*steps - 2)
- * columns (k = 4 with FP16 storage, else 3; the 4*steps - 2 extra columns are
+ * columns (k = 4 with FP32 arithmetic, 3 with FP64; the 4*steps - 2 extra columns are
  * recomputed), and with steps = 4 also 2 for k = 2; strips are spread evenly
  * over nx (FP64: strip edges on 64-byte boundaries).  waves = 1 with steps > 1
  * (rows 0, depth 1, any storage type and size) takes square patches, one node

@@ -492,13 +492,6 @@ __device__ __forceinline__ void exact_momentum(const double (&t)[9], double& jx,
   jx = ((t[1] - t[3]) + u) + v;
   jy = ((t[2] - t[4]) + u) - v;
 }
-// Mass of nine FP32 values, exactly (as exact_momentum).
-__device__ __forceinline__ double exact_mass(const float (&s)[9]) {
-#pragma clang fp contract(off)
-  return ((double(s[0]) + double(s[1])) + (double(s[2]) + double(s[3]))) +
-         ((double(s[4]) + double(s[5])) + (double(s[6]) + double(s[7]))) + double(s[8]);
-}
-
 // The collision conserves mass and changes the momentum by exactly F (every
 // forcing scheme here, BGK or MRT).  In FP32 arithmetic each updated
 // population carries its own rounding, and at a steady state the same
@@ -524,16 +517,14 @@ __device__ __forceinline__ void conserve(float (&s)[9], float hx, float hy, doub
 }
 
 // What a pulled row keeps for its collision: the summed stored values (the density
-// or its deviation; FP32 storage with FP32 arithmetic keeps the exact FP64 sum) and
-// 1/psi^2.
+// or its deviation) and 1/psi^2.
 template <typename S> struct NodeQ {
-  std::conditional_t<Store<S>::kConserve, double, typename Store<S>::R> drho = 0;
-  typename Store<S>::R ip2 = 0;
+  typename Store<S>::R drho = 0, ip2 = 0;
 };
 
 // Density from the summed stored values.
-template <typename S, typename Q>
-__device__ __forceinline__ double density(Q drho, const RunDev& d) {
+template <typename S>
+__device__ __forceinline__ double density(typename Store<S>::R drho, const RunDev& d) {
   if constexpr (Store<S>::kDev) return d.rho_ref + double(drho);
   return drho;
 }
@@ -542,10 +533,7 @@ __device__ __forceinline__ double density(Q drho, const RunDev& d) {
 template <typename S>
 __device__ __forceinline__ double eval_psi(const typename Store<S>::R (&f)[9], const RunDev& d,
                                            NodeQ<S>& q) {
-  if constexpr (Store<S>::kConserve)
-    q.drho = exact_mass(f);
-  else
-    q.drho = sum9(f);
+  q.drho = sum9(f);
   const PsiPair w = psi_pair(psi2_of(density<S>(q.drho, d), d));
   q.ip2 = typename Store<S>::R(w.ip2);
   return w.psi;
@@ -561,21 +549,24 @@ __device__ __forceinline__ bool update_node(typename Store<S>::R (&f)[9], const 
   const double rho = density<S>(q.drho, d);
   const R fx = R(Fx), fy = R(Fy);
   if constexpr (Store<S>::kConserve) {
+    // the exact mass is summed here, not kept from the density: carried through the two
+    // march rows in between it costs the pipe 21 registers, and with them 16 waves per CU
     double t[9], jx, jy;
 #pragma unroll
-    for (int a = 1; a < 9; ++a) t[a] = double(f[a]);
+    for (int a = 0; a < 9; ++a) t[a] = double(f[a]);
     exact_momentum(t, jx, jy);
+    const double mass = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])) + t[8];
     float hx, hy;
     if constexpr (MRT) {
-      collide_mrt<R>(f, R(q.drho), R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
+      collide_mrt<R>(f, q.drho, R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
       hx = 0.5f * (f[1] + f[3]);
       hy = 0.5f * (f[2] + f[4]);
     } else {
-      collide<true, R>(f, R(q.drho), R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
+      collide<true, R>(f, q.drho, R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
       hx = f[1];
       hy = f[2];
     }
-    conserve(f, hx, hy, q.drho, jx + Fx, jy + Fy);
+    conserve(f, hx, hy, mass, jx + Fx, jy + Fy);
   } else {
     R jx, jy;
     momentum(f, jx, jy);
@@ -1009,13 +1000,16 @@ template <typename S> struct StripAlign : std::integral_constant<int, 1> {};
 template <> struct StripAlign<double> : std::integral_constant<int, 8> {};
 
 // Waves per step of a multi-step tile: the strip class `waves` 4 (8 is the same) gives
-// strips of 64 k columns less the halo with k = 4, or 3 with FP64 arithmetic or FP32
-// storage (FP64: a CU's LDS holds four steps of 192 columns, not of 256, and three
-// waves per SIMD have the registers that four have not; FP32: 16 waves would spill 26
-// registers, 115 us per step either way on 4096 x 4096); 2 gives the narrow ones,
-// k = 2, for lattices that leave lanes of a wide strip idle.
+// strips of 64 k columns less the halo with k = 4, or 3 with FP64 arithmetic (a CU's LDS
+// holds four steps of 192 columns, not of 256, and three waves per SIMD have the registers
+// that four have not); 2 gives the narrow ones, k = 2, for lattices that leave lanes of a
+// wide strip idle.  FP32 arithmetic is held to the 128 registers of four waves per SIMD:
+// FP32 storage 4096 x 4096 with k = 4 103 us per step, with k = 3 and 148 registers 110.
 template <typename S> constexpr int pipe_nw(int waves) {
-  return waves == 2 ? 2 : std::is_same<S, __half>::value ? 4 : 3;
+  return waves == 2 ? 2 : std::is_same<typename Store<S>::R, float>::value ? 4 : 3;
+}
+template <typename S> constexpr int pipe_waves_per_simd() {
+  return std::is_same<typename Store<S>::R, float>::value ? 4 : 2;
 }
 
 // What starting a piece costs, in rows: march rows before the first and after the last
@@ -1028,7 +1022,8 @@ constexpr int kStepFill = 3;
 // contiguous share of the strips laid end to end; a share is split where it crosses a
 // strip boundary.
 template <typename S, int NW, int TS, bool MRT = false>
-__global__ __launch_bounds__(64 * NW * TS) void k_pipe(const typename Store<S>::E* __restrict__ src,
+__global__ __launch_bounds__(64 * NW * TS)
+__attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_pipe(const typename Store<S>::E* __restrict__ src,
                                                        typename Store<S>::E* __restrict__ dst, RunDev d,
                                                        int L, int nstrips,
                                                        const unsigned long long* stepbase,
@@ -1197,7 +1192,8 @@ __global__ __launch_bounds__(64 * NW) void k_batch_step(const typename Store<S>:
 // Persistent batched launch of TS steps (tile_pipe); the items are at most W - 2H columns
 // wide.
 template <typename S, int NW, int TS, bool MRT = false>
-__global__ __launch_bounds__(64 * NW * TS) void k_batch_pipe(const typename Store<S>::E* __restrict__ src,
+__global__ __launch_bounds__(64 * NW * TS)
+__attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_batch_pipe(const typename Store<S>::E* __restrict__ src,
                                                              typename Store<S>::E* __restrict__ dst,
                                                              const RunDev* __restrict__ runs,
                                                              const Item* __restrict__ items, int nitems,

@@ -198,10 +198,13 @@ void decode_any(int prec, const lbm_params& p, double rref, const char* raw, dou
 
 // ---- launches ---------------------------------------------------------------
 
-// Resident blocks per CU times the CU count for one kernel (cached per kernel).
-int resident_blocks(const void* fn, int threads) {
+// CUs, and resident blocks per CU, for one kernel (cached per kernel).
+struct Residency {
+  int ncu, per_cu;
+};
+Residency residency(const void* fn, int threads) {
   static std::mutex mu;
-  static std::map<const void*, int> cache;
+  static std::map<const void*, Residency> cache;
   std::lock_guard<std::mutex> lk(mu);
   auto it = cache.find(fn);
   if (it != cache.end()) return it->second;
@@ -212,7 +215,11 @@ int resident_blocks(const void* fn, int threads) {
   }
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, 0) != hipSuccess || occ < 1)
     occ = 1;
-  return cache[fn] = ncu * occ;
+  return cache[fn] = Residency{ncu, occ};
+}
+int resident_blocks(const void* fn, int threads) {
+  const Residency r = residency(fn, threads);
+  return r.ncu * r.per_cu;
 }
 
 template <typename S, int NW, int PF, bool MRT>
@@ -270,9 +277,15 @@ hipError_t launch_pipe_t(const void* src, void* dst, const RunDev& d, int L,
   if (L > 0) {
     grid = nstrips * ((d.ny + L - 1) / L);
   } else {
+    // A second block on a CU halves the rows of a share but not its fill, so it pays only
+    // while shares keep nearly a fill's rows (FP32, 128-column strips, us per step with one
+    // and two blocks per CU: 22 rows against 11 8.8 and 10.0, 36 against 18 11.9 and 11.7,
+    // 55 against 27 15.9 and 15.1).
     const int64_t rows = (int64_t)nstrips * d.ny;
-    grid = resident_blocks((const void*)k_pipe<S, NW, TS, MRT>, threads);
-    grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, rows / 8));
+    const Residency r = residency((const void*)k_pipe<S, NW, TS, MRT>, threads);
+    const int64_t least = std::max(8, pipe_fill(TS) * 17 / 20);
+    const int64_t k = std::max<int64_t>(1, std::min<int64_t>(r.per_cu, rows / (r.ncu * least)));
+    grid = (int)std::max<int64_t>(1, std::min<int64_t>(r.ncu * k, rows / 8));
   }
   using E = typename Store<S>::E;
   hipLaunchKernelGGL((k_pipe<S, NW, TS, MRT>), dim3(grid), dim3(threads), 0, st,
@@ -1243,7 +1256,8 @@ int batch_items(lbm_batch* b, const Tile& t) {
   }
   // multi-step strips: as wide as their kernel takes; those of FP64 lattices start on
   // 64-byte boundaries, as for a single lattice
-  const int nw = t.ts == 1 ? t.nw : b->prec == LBM_PREC_F16DEV ? pipe_nw<__half>(t.nw) : pipe_nw<double>(t.nw);
+  const bool f32 = b->prec == LBM_PREC_F32DEV || b->prec == LBM_PREC_F16DEV;  // FP32 arithmetic
+  const int nw = t.ts == 1 ? t.nw : f32 ? pipe_nw<float>(t.nw) : pipe_nw<double>(t.nw);
   const int64_t rows = layout::build_items(b->nruns, nx.data(), ny.data(), nw, t.L, t.ts, items,
                                            b->prec == LBM_PREC_F64 ? StripAlign<double>::value : 1);
   if ((int)items.size() > b->items_cap) return LBM_ENOSPACE;
