@@ -98,6 +98,20 @@ __global__ __launch_bounds__(NT) void k_mlp(const float* __restrict__ P, Norm nm
   __shared__ MlpLds s;
   const int t = threadIdx.x, l = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  // the row's index (an epoch's permutation) and then the row itself are dependent loads:
+  // the first tile's go out before the weights are staged, behind whose loads they hide
+  const int ntiles = (B + TR - 1) / TR;
+  float xin[3] = {0.f, 0.f, 0.f}, tgt = 0.f;  // input row l & 31 and its target of output l >> 5 (wave 0)
+  auto load_row = [&](int tile) {
+    const int r = tile * TR + (l & 31);
+    if (w != 0 || r >= B) return;
+    const int64_t rr = idx ? idx[r] : (int64_t)r;
+    if (TRAIN) tgt = T[2 * rr + (l >> 5)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) xin[i] = X[3 * rr + i];
+  };
+  load_row(blockIdx.x);
+#pragma unroll
   for (int i = t; i < NH * NH; i += NT) {
     const int n = i >> 6, k = i & 63;
     const unsigned short v = f2bf(P[OFF_W2 + i]);
@@ -120,18 +134,13 @@ __global__ __launch_bounds__(NT) void k_mlp(const float* __restrict__ P, Norm nm
   for (int i = 0; i < 16; ++i) gW2[i] = 0.f;
   float g1 = 0.f, gW3 = 0.f, gb = 0.f, lsum = 0.f;
 
-  const int ntiles = (B + TR - 1) / TR;
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int row0 = tile * TR;
-    float tgt = 0.f;  // target of row l & 31, output l >> 5 (wave 0)
-    if (w == 0) {  // standardised inputs; rows past B are zero and carry no gradient
-      const int m = l & 31, o = l >> 5, r = row0 + m;
-      const int64_t rr = r < B ? (idx ? idx[r] : (int64_t)r) : 0;
-      if (TRAIN && r < B) tgt = T[2 * rr + o];
-      if (o == 0)
+    if (tile != (int)blockIdx.x) load_row(tile);
+    if (w == 0 && l < TR) {  // standardised inputs; rows past B are zero and carry no gradient
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-          s.xs[m][i] = qbf(r < B ? (X[3 * rr + i] - nm.in_mean[i]) / nm.in_std[i] : 0.f);
+      for (int i = 0; i < 3; ++i)
+        s.xs[l][i] = qbf(row0 + l < B ? (xin[i] - nm.in_mean[i]) / nm.in_std[i] : 0.f);
     }
     __syncthreads();
     float d1[4];  // GELU'(z1)
@@ -209,6 +218,7 @@ __global__ __launch_bounds__(NT) void k_mlp(const float* __restrict__ P, Norm nm
         }
       }
       if (w >= 6) {  // W3: output w - 6, column l
+#pragma unroll
         for (int m = 0; m < TR; ++m) gW3 = fmaf(qbf(s.dy[m][w - 6]), bf2f(s.h2[m * SN + l]), gW3);
       }
       __syncthreads();
@@ -216,8 +226,10 @@ __global__ __launch_bounds__(NT) void k_mlp(const float* __restrict__ P, Norm nm
         mm32<TR>(s.dzt + (w >> 1) * 32 * SM, SM, s.h1t + (w & 1) * 32 * SM, SM, gW2);
       } else if (w == 4) {  // b3
         if (l < 2)
+#pragma unroll
           for (int m = 0; m < TR; ++m) gb += s.dy[m][l];
       } else if (w == 5) {  // b2
+#pragma unroll
         for (int m = 0; m < TR; ++m) gb += s.za[m][l];
       } else {  // dH1[m][k] = sum_n dZ2[m][n] W2[n][k], 32 columns a wave
         f16v c;
@@ -234,6 +246,7 @@ __global__ __launch_bounds__(NT) void k_mlp(const float* __restrict__ P, Norm nm
       __syncthreads();
       // chains of unit l: wave w sums rows 8 j + 4 (w & 1) + (0..3) of b1 (w < 2) or of
       // column (w >> 1) - 1 of W1
+#pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int m = 8 * (i >> 2) + 4 * (w & 1) + (i & 3);
         const float g = s.zb[m][l];
@@ -265,21 +278,22 @@ __global__ __launch_bounds__(NT) void k_mlp(const float* __restrict__ P, Norm nm
   __syncthreads();
   if (t == 0) {
     float sum = 0.f;
+#pragma unroll
     for (int i = 0; i < 64; ++i) sum += s.red[i];
     lpart[blockIdx.x] = sum;
   }
 }
 
-// Sum over the G work-groups in index order, eight loads in flight.
+// Sum over the G work-groups in index order, sixteen loads in flight.
 __device__ __forceinline__ float group_sum(const float* __restrict__ g, int stride, int G) {
   float s = 0.f;
   int b = 0;
-  for (; b + 8 <= G; b += 8) {
-    float v[8];
+  for (; b + 16 <= G; b += 16) {
+    float v[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = g[(size_t)(b + i) * stride];
+    for (int i = 0; i < 16; ++i) v[i] = g[(size_t)(b + i) * stride];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s += v[i];
+    for (int i = 0; i < 16; ++i) s += v[i];
   }
   for (; b < G; ++b) s += g[(size_t)b * stride];
   return s;

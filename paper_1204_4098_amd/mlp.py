@@ -152,8 +152,9 @@ class Mlp:
             with torch.cuda.stream(self.stream):
                 if k == 0:
                     # each epoch's permutation is copied on the training stream, so
-                    # the minibatches gathered from it are ordered after the copy
-                    perm = torch.randperm(n, generator=g).to(self.device)
+                    # the minibatches gathered from it are ordered after the copy; from
+                    # pinned memory, so that drawing it overlaps the steps enqueued before
+                    perm = torch.randperm(n, generator=g, pin_memory=True).to(self.device, non_blocking=True)
                 _check(lib().mlp_train_steps(self.ctx, Xd.data_ptr(), Td.data_ptr(),
                                              perm.data_ptr() + 8 * k * batch, batch, m,
                                              C.addressof(rates) + 4 * s, self.loss.data_ptr()),
