@@ -599,12 +599,6 @@ bool same_tile(const Tile& a, const Tile& b) {
   return a.nw == b.nw && a.L == b.L && a.pf == b.pf && a.ts == b.ts;
 }
 
-// Strip widths of the single-lattice kernel (64 to 1024 columns) and of the
-// batched one (64 to 512 columns; batched lattices are at most a few hundred
-// columns wide).
-constexpr int kStepWaves[] = {1, 2, 4, 8, 16};
-constexpr int kBatchWaves[] = {1, 2, 4, 8};
-
 // A launch shape.  Multi-step tiles: strip class nw 4 (8 is the same) or 2 (narrow
 // strips: batches, and single lattices at four steps), or patches (nw 1, no rows; single
 // lattices); three steps only for single lattices.  More than two steps and patches: depth 1.
@@ -867,7 +861,6 @@ int lbm_status(lbm_ctx* c, int64_t* step, int64_t* diverged_at) {
 
 int lbm_moments_device(lbm_ctx* c, double* rho, double* vx, double* vy, double* p) {
   if (!c || !rho || !vx || !vy || !p) return LBM_EINVAL;
-  const size_t n = (size_t)c->p.nx * c->p.ny;
   HIPCHK(launch_moments(c->p.precision, c->buf[c->cur], c->d, rho, vx, vy, p, c->st));
   return LBM_OK;
 }
@@ -1054,19 +1047,20 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
   const int64_t nodes = (int64_t)c->p.nx * c->p.ny;
   const int reps = nodes >= (1 << 22) ? 3 : 10;
   std::vector<Tile> cand;
-  // Below 2^16 nodes the patches have been at least 1.8 times as fast as anything else, so
-  // of the other families only the likeliest are timed there (tuning is most of the time
-  // it takes to set such a lattice up); above 2^18 they lose to the pipe and are left out.
+  // Tuning is most of the time it takes to set a lattice up, so of each family only the
+  // likeliest are timed.  One step per launch has lost to the multi-step kernels by 1.4
+  // times and more on every size measured (64 x 32 to 4096 x 4096); one-wave strips are
+  // there for narrow lattices.  Patches win below 2^16 nodes by 1.8 times and more and lose
+  // above 2^18.
   const bool tiny = nodes < (1 << 16);
   if (nodes <= (1 << 18))
     for (int ts : {2, 3, 4}) cand.push_back(Tile{1, 0, 1, ts});
-  for (int nw : kStepWaves) {
-    if ((nw > 1 && 64 * (nw / 2) >= c->p.nx) || (tiny && nw > 2)) continue;
-    for (int pf : {1, 2})
-      for (int L : {0, 1, 2, 4, 8, 16, 32, 64, 128})
-        if (L <= 2 * c->p.ny && (L == 0 || L > 2 || nodes < (1 << 20)) &&  // 1-2 rows: small lattices
-            (!tiny || (pf == 1 && L <= 8)))
-          cand.push_back(Tile{nw, L, pf, 1});
+  if (tiny) {
+    for (int L : {1, 2, 4, 8})
+      if (L <= 2 * c->p.ny) cand.push_back(Tile{1, L, 1, 1});
+  } else {
+    for (const Tile& t : {Tile{1, 0, 2, 1}, Tile{1, 64, 2, 1}, Tile{4, 0, 2, 1}, Tile{4, 8, 2, 1}, Tile{16, 0, 1, 1}})
+      if (t.L <= 2 * c->p.ny) cand.push_back(t);
   }
   for (int L : {0, 16, 32, 64, 128})
     if (L <= 2 * c->p.ny)
@@ -1534,14 +1528,10 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
   if (!b) return LBM_EINVAL;
   Tile bt = b->tile;
   const int s = b->cur;
-  int maxnx = 0;
-  for (int r = 0; r < b->nruns; ++r) maxnx = std::max(maxnx, b->p[r].nx);
+  // as in lbm_tune, only the likeliest of each family
   std::vector<Tile> cand;
-  for (int nw : kBatchWaves) {
-    if (nw > 1 && 64 * (nw / 2) >= maxnx) continue;
-    for (int pf : {1, 2})
-      for (int L : {0, 4, 8, 16, 32, 64}) cand.push_back(Tile{nw, L, pf, 1});
-  }
+  for (int nw : {1, 2, 4})
+    for (int L : {0, 8, 16}) cand.push_back(Tile{nw, L, 2, 1});
   for (int nw : {2, 4})
     for (int ts : {2, 4})
       for (int L : {0, 16, 32, 64}) cand.push_back(Tile{nw, L, 1, ts});  // 64: whole runs of a sweep
