@@ -1073,6 +1073,20 @@ __attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_pipe(const
 
 // ---- small lattices: several steps of a patch, one node per thread ------------------
 
+// pull9 of a row that differs from lane to lane.
+template <typename S>
+__device__ __forceinline__ void pull9_lane(const typename Store<S>::E* __restrict__ src, const RunDev& d,
+                                           const Cols& c, int y, typename Store<S>::R (&f)[9]) {
+  const int ym = y == 0 ? d.ny - 1 : y - 1, yp = y == d.ny - 1 ? 0 : y + 1;
+  const int64_t P = d.plane, r0 = (int64_t)y * d.rs, rm = (int64_t)ym * d.rs, rp = (int64_t)yp * d.rs;
+  const int64_t o[9] = {r0 + c.x,          r0 + P + c.xm,     rm + 2 * P + c.x,
+                        r0 + 3 * P + c.xp, rp + 4 * P + c.x,  rm + 5 * P + c.xm,
+                        rm + 6 * P + c.xp, rp + 7 * P + c.xp, rp + 8 * P + c.xm};
+#pragma unroll
+  for (int a = 0; a < 9; ++a)
+    f[a] = index_ok(o[a], d.elems) ? Store<S>::ld(src + o[a]) : typename Store<S>::R(0);
+}
+
 // A block holds a patch of RX x RY nodes, a thread a node, and advances it TS steps on
 // chip: every node pulls from global memory once, psi and the eight moving populations
 // of each step go to the neighbours through LDS (two barriers per step), and the inner
@@ -1081,6 +1095,8 @@ __attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_pipe(const
 // latency (a launch, a load, two exchanges), and the march of the other kernels puts
 // rows one after the other.  The recomputed halo costs 7.6 (22 x 22, four steps), 2.1 or
 // 1.5 (32 x 32, three, two) times the work, so lattices that fill the chip take the pipe.
+// The populations' loads go out before the divergence flag is waited for, which ends a
+// chain of two latencies: 100 steps of 64 x 32 went from 194 to 188 us.
 // us per step in a graph, FP64, best other tile -> patch: 64 x 32 4.3 -> 1.6, 128 x 64 4.4
 // -> 1.7, 200 x 150 5.0 -> 2.6, 300 x 300 6.3 -> 3.5, 512 x 512 7.4 -> 7.4, 777 x 643 9.5
 // -> 12.8.  Same arithmetic in the same order as single steps: bitwise equal.
@@ -1093,35 +1109,34 @@ __global__ __launch_bounds__((RX * RY + 63) / 64 * 64) void k_patch(
   constexpr int H = 2 * TS - 1, TX = RX - 2 * H, TY = RY - 2 * H, N = RX * RY, PAD = RX + 1;
   __shared__ double psi[N + 2 * PAD];
   __shared__ R ex[TS > 1 ? 8 : 1][N + 2 * PAD];
-  const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
-  const bool frozen = *flag < step;
   const int ty = blockIdx.x / ntx, tx = blockIdx.x - ty * ntx;
   const int i = min((int)threadIdx.x, N - 1);  // the last wave's idle lanes repeat a node
   const int ry = i / RX, rx = i - ry * RX;
   const int gx = tx * TX + rx - H, gy = ty * TY + ry - H;
   const bool out = threadIdx.x < N && rx >= H && rx < RX - H && ry >= H && ry < RY - H && gx < d.nx && gy < d.ny;
-  int x = gx % d.nx, y = gy % d.ny;
-  x = x < 0 ? x + d.nx : x;
-  y = y < 0 ? y + d.ny : y;
+  // periodic image of column or row g of n, for g in (-w, n + w)
+  auto wrap = [](int g, int n, int w) {
+    if (n < w) {  // a patch wider than the lattice
+      g %= n;
+      return g < 0 ? g + n : g;
+    }
+    return g < 0 ? g + n : (g >= n ? g - n : g);
+  };
+  const int x = wrap(gx, d.nx, RX), y = wrap(gy, d.ny, RY);
+  const Cols cx = cols_of(x, d.nx);
+  // the node's populations are under way before the divergence flag is waited for
   R f[9];
-  if (frozen) {
-    if (!out) return;
+  pull9_lane<S>(src, d, cx, y, f);
+  const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
+  if (*flag < step) {  // diverged at an earlier step: frozen
+    if (out) {
 #pragma unroll
-    for (int a = 0; a < 9; ++a) {
-      const int64_t o = (int64_t)y * d.rs + a * d.plane + x;
-      if (index_ok(o, d.elems)) dst[o] = src[o];
+      for (int a = 0; a < 9; ++a) {
+        const int64_t o = (int64_t)y * d.rs + a * d.plane + x;
+        if (index_ok(o, d.elems)) dst[o] = src[o];
+      }
     }
     return;
-  }
-  const Cols cx = cols_of(x, d.nx);
-  const int ym = y == 0 ? d.ny - 1 : y - 1, yp = y == d.ny - 1 ? 0 : y + 1;
-  {
-    const int64_t P = d.plane, r0 = (int64_t)y * d.rs, rm = (int64_t)ym * d.rs, rp = (int64_t)yp * d.rs;
-    const int64_t o[9] = {r0 + cx.x,          r0 + P + cx.xm,     rm + 2 * P + cx.x,
-                          r0 + 3 * P + cx.xp, rp + 4 * P + cx.x,  rm + 5 * P + cx.xm,
-                          rm + 6 * P + cx.xp, rp + 7 * P + cx.xp, rp + 8 * P + cx.xm};
-#pragma unroll
-    for (int a = 0; a < 9; ++a) f[a] = index_ok(o[a], d.elems) ? T::ld(src + o[a]) : R(0);
   }
   double* ps = psi + PAD + i;
   bool bad = false;
