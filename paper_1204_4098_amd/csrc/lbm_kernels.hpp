@@ -103,7 +103,6 @@ __device__ __forceinline__ void balanced_pieces(const Item* __restrict__ items, 
     const int n = (int)min(min(e - v, (int64_t)(it.nrows - y)), (int64_t)cap);
     if (n > 0) {
       piece(it, y, n);
-      __syncthreads();  // LDS is reused by the next piece
       v += n;
     }
     if (v >= base + it.nrows) ++i;
@@ -119,7 +118,6 @@ __device__ __forceinline__ void listed_pieces(const Item* __restrict__ items, in
   for (int i = items[b].row0; i < hi; ++i) {
     const Item it = items[i];
     piece(it, 0, it.nrows);
-    __syncthreads();  // LDS is reused by the next item
   }
 }
 
@@ -875,15 +873,32 @@ __device__ __forceinline__ void pipe_pull(const typename Store<S>::R* x, typenam
   f[6] = x[(a3 + 2) * W + 1];
 }
 
+// A block's pieces follow one another without draining the pipeline: a group that has
+// done its rows of a piece starts its rows of the next, while the groups behind it finish
+// the last one.  Group l has rows jf .. je-1 of a piece's march rows, and the next piece's
+// march row 0 is the one at which the first group is done, je of l = 0: no other group is
+// busy with both (je of group l is at most (2l + 3) & ~3 later, its jf (6l) & ~3), and
+// piece lengths are whole fours, so registers and LDS slots keep their rotation and a
+// hand-over is never more than the 1-3 march rows apart that it is inside a piece.
+// A sweep of 256 runs (3.1 million nodes, 2-3 pieces per block), us per launch of four
+// steps, drained after each piece -> not: FP64 162 -> 158, FP32 with FP64 collide 153 ->
+// 146, FP64 in chunks of 16 rows 216 -> 201.
+// `owed`: barriers the group has yet to pass to reach the next piece's march row 0
+// (negative: it is past it).
+template <int TS> __device__ __forceinline__ void pipe_drain(int owed) {
+  for (int k = -((2 * (TS - 1) + 3) & ~3); k < owed; ++k) lds_barrier();
+}
+
 // TS time steps of columns [x0, x0+ncols), rows [y0, y0+nrows); ncols <= W - 2H.  All
-// threads of the block call it.
+// threads of the block call it.  owed: 0 for a block's first piece, passed on from each
+// piece to the next and to pipe_drain after the last.
 template <typename S, int NW, int TS, bool MRT = false>
 __device__ __forceinline__ void tile_pipe(const typename Store<S>::E* __restrict__ src,
                                           typename Store<S>::E* __restrict__ dst,
                                           const RunDev& d, int x0, int y0, int ncols, int nrows,
                                           unsigned long long step,
                                           unsigned long long* __restrict__ flag,
-                                          PipeLds<S, 64 * NW, TS>& lds) {
+                                          PipeLds<S, 64 * NW, TS>& lds, int& owed) {
   using T = Store<S>;
   using E = typename T::E;
   using R = typename T::R;
@@ -898,10 +913,10 @@ __device__ __forceinline__ void tile_pipe(const typename Store<S>::E* __restrict
   if (c < 0) c += d.nx;
   double* const ud = &lds.ud[lv][0][0] + i;
   bool bad = false;
-  const int J = 6 * (TS - 1) + nrows + 3;              // march rows
-  // march rows of this step, widened to whole fours (the rows added compute values that
-  // nothing reads)
-  const int j4 = (J + 3) & ~3, jf = (6 * lv) & ~3, je = min(j4, (J - 2 * (TS - 1 - lv) + 3) & ~3);
+  // march rows of the first group, and of this step, widened to whole fours (the rows added
+  // compute values that nothing reads)
+  const int J = 4 * (TS - 1) + nrows + 3;
+  const int jn = (J + 3) & ~3, jf = (6 * lv) & ~3, je = (J + 2 * lv + 3) & ~3;
   const int yc = y0 - H - 2 - 4 * lv;                  // row collided at march row j: yc + j
   auto in_rows = [&](int j) { return yc + j >= y0 && yc + j < y0 + nrows; };
   // rows p, p-1, p-2 and (first group) the one being loaded: buffer K = j mod 4 holds p,
@@ -928,14 +943,14 @@ __device__ __forceinline__ void tile_pipe(const typename Store<S>::E* __restrict
   using K2 = std::integral_constant<int, 2>;
   using K3 = std::integral_constant<int, 3>;
   auto march = [&](auto&& row) __attribute__((always_inline)) {
-    for (int j = 0; j < jf; ++j) lds_barrier();
+    for (int j = -owed; j < jf; ++j) lds_barrier();
     for (int j = jf; j < je; j += 4) {
       row(j, K0{});
       row(j + 1, K1{});
       row(j + 2, K2{});
       row(j + 3, K3{});
     }
-    for (int j = je; j < j4; ++j) lds_barrier();
+    owed = jn - je;
   };
   if (lv == 0) {
     R* xo = &lds.ex[0][0][0] + i;
@@ -1012,9 +1027,11 @@ template <typename S> constexpr int pipe_waves_per_simd() {
   return std::is_same<typename Store<S>::R, float>::value ? 4 : 2;
 }
 
-// What starting a piece costs, in rows: march rows before the first and after the last
-// row is stored (pipe), psi rows and the prologue (one-step kernels).
-constexpr int pipe_fill(int ts) { return 6 * (ts - 1) + 3; }
+// What a piece costs besides its rows, in rows: the first group's halo rows (pipe; a
+// block's last piece takes pipe_drain_rows more), psi rows and the prologue (one-step
+// kernels).
+constexpr int pipe_fill(int ts) { return 4 * (ts - 1) + 3; }
+constexpr int pipe_drain_rows(int ts) { return 2 * (ts - 1); }
 constexpr int kStepFill = 3;
 
 // Single lattice: strips of at most W - 2H columns spread evenly over nx.  L > 0: one
@@ -1037,16 +1054,18 @@ __attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_pipe(const
     constexpr int A = StripAlign<S>::value;
     return k >= nstrips ? d.nx : (int)((int64_t)k * d.nx / nstrips) / A * A;
   };
+  int owed = 0;
   auto piece = [&](int s, int y, int n) {
     const int x0 = edge(s), nc = edge(s + 1) - x0;
     if (frozen)
       copy_tile<S, 64 * NW>(src, dst, d, x0, y, nc, n);
     else
-      tile_pipe<S, NW, TS, MRT>(src, dst, d, x0, y, nc, n, step, flag, lds);
+      tile_pipe<S, NW, TS, MRT>(src, dst, d, x0, y, nc, n, step, flag, lds, owed);
   };
   if (L > 0) {
     const int sy = t / nstrips, s = t - sy * nstrips;
     piece(s, sy * L, min(L, d.ny - sy * L));
+    pipe_drain<TS>(owed);
     return;
   }
   // Rows cost one each and every piece kFill more (the march rows that fill and drain
@@ -1065,10 +1084,8 @@ __attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_pipe(const
   int s, y, se, ye;
   at(t, s, y);
   at(t + 1, se, ye);  // the last share ends at (nstrips, 0)
-  for (; s < se || (s == se && y < ye); ++s, y = 0) {
-    piece(s, y, (s < se ? d.ny : ye) - y);
-    __syncthreads();  // LDS is reused by the next piece
-  }
+  for (; s < se || (s == se && y < ye); ++s, y = 0) piece(s, y, (s < se ? d.ny : ye) - y);
+  pipe_drain<TS>(owed);
 }
 
 // ---- small lattices: several steps of a patch, one node per thread ------------------
@@ -1197,6 +1214,7 @@ __global__ __launch_bounds__(64 * NW) void k_batch_step(const typename Store<S>:
     else
       tile_step<S, NW, PF, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n, step,
                                 &flags[it.run], ring, haloL, haloR);
+    __syncthreads();  // LDS is reused by the next piece
   };
   if (total > 0)
     balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), LMAX, kStepFill, piece);
@@ -1218,18 +1236,20 @@ __attribute__((amdgpu_waves_per_eu(pipe_waves_per_simd<S>()))) void k_batch_pipe
                                                              unsigned long long* flags) {
   __shared__ PipeLds<S, 64 * NW, TS> lds;
   const unsigned long long step = (stepbase ? *stepbase : 0ull) + steplocal;
+  int owed = 0;
   auto piece = [&](const Item& it, int y, int n) {
     const RunDev d = runs[it.run];
     if (flags[it.run] < step)  // frozen run
       copy_tile<S, 64 * NW>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n);
     else
       tile_pipe<S, NW, TS, MRT>(src + d.off, dst + d.off, d, it.x0, it.y0 + y, it.ncols, n, step,
-                                &flags[it.run], lds);
+                                &flags[it.run], lds, owed);
   };
   if (total > 0)  // no row cap: no per-row arrays
     balanced_pieces(items, nitems, total, xcd_remap(blockIdx.x, gridDim.x), 1 << 30, pipe_fill(TS), piece);
   else
     listed_pieces(items, nitems, piece);
+  pipe_drain<TS>(owed);
 }
 
 // Coexistence densities of flat interfaces with normal x, for every run of a

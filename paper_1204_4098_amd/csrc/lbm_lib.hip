@@ -283,7 +283,7 @@ hipError_t launch_pipe_t(const void* src, void* dst, const RunDev& d, int L,
     // 55 against 27 15.9 and 15.1).
     const int64_t rows = (int64_t)nstrips * d.ny;
     const Residency r = residency((const void*)k_pipe<S, NW, TS, MRT>, threads);
-    const int64_t least = std::max(8, pipe_fill(TS) * 17 / 20);
+    const int64_t least = std::max(8, (pipe_fill(TS) + pipe_drain_rows(TS)) * 17 / 20);
     const int64_t k = std::max<int64_t>(1, std::min<int64_t>(r.per_cu, rows / (r.ncu * least)));
     grid = (int)std::max<int64_t>(1, std::min<int64_t>(r.ncu * k, rows / 8));
   }

@@ -137,6 +137,33 @@ def test_batch_four_steps_bitwise(L, tile, prec):
     a.close(); b.close()
 
 
+@pytest.mark.parametrize("tile", [(2, 5, 1, 4), (4, 4, 1, 4), (4, 0, 1, 4), (2, 4, 1, 2), (4, 7, 1, 2)])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_blocks_with_many_pieces(L, tile, prec):
+    # up to 2,000 pieces of 1 to 7 rows (a block marches several without draining), or
+    # whole strips; a run in the middle diverges, so its pieces become copies
+    from oracle import thermo as th
+    gps, rhos = [], []
+    for i in range(28):
+        nx, ny = 64 + 37 * (i % 11), 80 + 13 * (i % 5)
+        gps.append(pair(L, nx, ny, t=0.85, tau=0.7 + 0.02 * i, scheme=2, sigma=0.1, precision=prec)[0])
+        rhos.append(slab_rho(nx, ny, CS, 0.85, stream=i))
+    c = th.maxwell_pr(0.6)
+    gps.insert(9, pair(L, 96, 80, t=0.6, tau=1.0, scheme=2, sigma=0.105, eos=PR, precision=prec)[0])
+    rhos.insert(9, synth.droplet(96, 80, c.rho_l, c.rho_g, 20, 4.0, 0.005))
+    a, b = L.Batch(gps, rhos), L.Batch(gps, rhos)
+    a.set_tile(1, 16, 2)
+    b.set_tile(*tile)
+    a.step(203)
+    b.step(203)
+    st = b.coexistence()[2]
+    assert st[9] == L.LBM_EDIVERGED and np.array_equal(a.coexistence()[2], st)
+    for i in range(len(gps)):
+        if i != 9:
+            assert np.array_equal(a.get_populations(i), b.get_populations(i)), i
+    a.close(); b.close()
+
+
 @pytest.mark.parametrize("prec", [0, 1, 2, 3])
 def test_four_steps_in_bounds(monkeypatch, prec):
     import torch
