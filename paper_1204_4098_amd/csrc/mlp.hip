@@ -22,6 +22,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "lbm.h"
@@ -346,6 +347,7 @@ struct mlp_ctx {
   hipStream_t st;
   int64_t t;  // Adam steps taken
   float* host;  // pinned staging of mlp_forward_host: kHostRows rows of inputs, then outputs
+  std::mutex host_lock;  // held while the staging is in use (callers on several threads)
 };
 
 namespace {
@@ -466,6 +468,7 @@ int mlp_forward(mlp_ctx* c, const float* X, float* Y, int32_t B) {
 
 int mlp_forward_host(mlp_ctx* c, const float* X, float* Y, int32_t B) {
   if (!c || !X || !Y || B < 1 || B > c->max_batch) return LBM_EINVAL;
+  const std::lock_guard<std::mutex> hold(c->host_lock);
   if (!c->host) {
     void* h = nullptr;
     if (hipHostMalloc(&h, kHostRows * 5 * sizeof(float), hipHostMallocDefault) != hipSuccess) return LBM_EHIP;

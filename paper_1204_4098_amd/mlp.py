@@ -135,6 +135,8 @@ class Mlp:
         cosine when `cosine`); returns the loss history (sampled)."""
         Xd, Td = _dev(X, 3, self.device), _dev(T, 2, self.device)
         n = Xd.shape[0]
+        if Td.shape[0] < n:  # the kernels read the targets of every row
+            raise IndexError(f"{n} rows of inputs but {Td.shape[0]} of targets")
         batch = min(batch, n, self.max_batch)
         g = torch.Generator(device="cpu").manual_seed(seed)
         hist = []

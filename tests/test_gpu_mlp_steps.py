@@ -54,3 +54,24 @@ def test_host_forward_equals_device_forward(M, B):  # noqa: F811
     assert np.array_equal(y, net.forward(torch.as_tensor(X, device="cuda")))
     assert np.array_equal(y, net.forward(X))
     net.close()
+
+
+def test_host_forward_from_two_threads(M):  # noqa: F811
+    from concurrent.futures import ThreadPoolExecutor
+    xs = [_data(4096, seed=s)[0] for s in (1, 2)]
+    nrm, _ = _norm(M, *_data(100))
+    net = M.Mlp(_params(5), nrm, max_batch=4096)
+    want = [net.forward(x) for x in xs]
+    with ThreadPoolExecutor(2) as pool:
+        for i, y in enumerate(pool.map(lambda i: net.forward(xs[i % 2]), range(200))):
+            assert np.array_equal(y, want[i % 2]), i
+    net.close()
+
+
+def test_train_refuses_fewer_targets_than_rows(M):  # noqa: F811
+    X, T = _data(64, seed=1)
+    nrm, _ = _norm(M, X, T)
+    net = M.Mlp(_params(2), nrm, max_batch=32)
+    with pytest.raises(IndexError):
+        net.train(X, T[:40], steps=2, lr=1e-3, batch=32)
+    net.close()
