@@ -1017,9 +1017,10 @@ template <> struct StripAlign<double> : std::integral_constant<int, 8> {};
 // Waves per step of a multi-step tile: the strip class `waves` 4 (8 is the same) gives
 // strips of 64 k columns less the halo with k = 4, or 3 with FP64 arithmetic (a CU's LDS
 // holds four steps of 192 columns, not of 256, and three waves per SIMD have the registers
-// that four have not); 2 gives the narrow ones, k = 2, for lattices that leave lanes of a
-// wide strip idle.  FP32 arithmetic is held to the 128 registers of four waves per SIMD:
-// FP32 storage 4096 x 4096 with k = 4 103 us per step, with k = 3 and 148 registers 110.
+// that four have not; two steps of a single lattice may take six, see launch_pipe_s); 2
+// gives the narrow ones, k = 2, for lattices that leave lanes of a wide strip idle.  FP32
+// arithmetic is held to the 128 registers of four waves per SIMD: FP32 storage 4096 x 4096
+// with k = 4 103 us per step, with k = 3 and 148 registers 110.
 template <typename S> constexpr int pipe_nw(int waves) {
   return waves == 2 ? 2 : std::is_same<typename Store<S>::R, float>::value ? 4 : 3;
 }

@@ -319,7 +319,18 @@ hipError_t launch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev
     if (t.ts == 3) return launch_patch_t<S, 32, 32, 3, MRT>(src, dst, d, base, local, flag, st);
     return launch_patch_t<S, 22, 22, 4, MRT>(src, dst, d, base, local, flag, st);
   }
-  if (t.ts == 2) return launch_pipe_t<S, NW, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
+  if (t.ts == 2) {
+    // FP64 arithmetic: two steps leave room in a CU for one block with twice the columns
+    // instead of two blocks; fewer columns are recomputed and fewer lines read twice.  Not
+    // where the wide strips leave a quarter more lanes idle.  us per launch of two steps,
+    // three waves per step and six: FP64 4096 x 4096 526 and 501, 1024 x 1024 49 and 43.5,
+    // 777 x 643 33 and 27.6, 400 x 400 16.7 and 21; FP32 storage 4096 x 4096 378 and 302,
+    // 1500 x 1001 49 and 38.  (FP32 arithmetic, four and eight: 304 and 301, 27 and 30.)
+    if constexpr (std::is_same<typename Store<S>::R, double>::value)
+      if (4 * 6 * pipe_strips<S, 6, 2>(d.nx) <= 5 * NW * pipe_strips<S, NW, 2>(d.nx))
+        return launch_pipe_t<S, 6, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
+    return launch_pipe_t<S, NW, 2, MRT>(src, dst, d, t.L, base, local, flag, st);
+  }
   if (t.ts == 4)
     return t.nw == 2 ? launch_pipe_t<S, 2, 4, MRT>(src, dst, d, t.L, base, local, flag, st)
                      : launch_pipe_t<S, NW, 4, MRT>(src, dst, d, t.L, base, local, flag, st);

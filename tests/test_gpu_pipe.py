@@ -60,6 +60,17 @@ def test_four_steps_bitwise_at_strip_edges(L, nx, ny, prec):
         assert np.array_equal(_run(L, gp, rho0, tile, 11), ref), tile
 
 
+@pytest.mark.parametrize("prec", [0, 3])
+@pytest.mark.parametrize("nx,ny", [(371, 9), (378, 7), (379, 7), (756, 6), (757, 40), (1100, 5)])
+def test_two_steps_with_six_waves(L, nx, ny, prec):
+    # strips of up to 378 columns (FP64 arithmetic); 2 + 2 + 2 + 1 steps
+    gp, _ = pair(L, nx, ny, t=0.9, tau=0.9, scheme=2, sigma=0.05, precision=prec)
+    rho0 = _rho(nx, ny, nx + ny)
+    ref = _run(L, gp, rho0, (2, 8, 1), 7)
+    for tile in [(4, 0, 1, 2), (4, 5, 1, 2), (8, 0, 2, 2)]:
+        assert np.array_equal(_run(L, gp, rho0, tile, 7), ref), tile
+
+
 @pytest.mark.parametrize("prec", [0, 1, 2, 3])
 @pytest.mark.parametrize("nx,ny", [(3, 3), (5, 4), (8, 8), (9, 7), (22, 23), (26, 27), (64, 32), (130, 45)])
 def test_patches_bitwise(L, nx, ny, prec):
