@@ -110,7 +110,7 @@ __device__ __forceinline__ void balanced_pieces(const Item* __restrict__ items, 
 }
 
 // List schedule of a batch: block b's items are items[row0 of b] .. items[row0 of b + 1] - 1
-// (layout::deal).
+// (layout::deal, layout::walk).
 template <class Piece>
 __device__ __forceinline__ void listed_pieces(const Item* __restrict__ items, int nitems, Piece&& piece) {
   const int b = blockIdx.x;

@@ -1251,7 +1251,8 @@ BatchArgs batch_args(const lbm_batch* b, int s, const unsigned long long* base, 
                    b->grid,   base,          local,     b->flags,   b->st,     nullptr};
 }
 
-// Work list of a tile (layout::build_items, dealt to its grid), uploaded to the device.
+// Work list of a tile (layout::build_items, dealt to its grid or walked), uploaded to the
+// device.
 int batch_items(lbm_batch* b, const Tile& t) {
   std::vector<Item> items;
   std::vector<int> nx(b->nruns), ny(b->nruns);
@@ -1273,7 +1274,8 @@ int batch_items(lbm_batch* b, const Tile& t) {
   HIPCHK(launch_batch(b->prec, b->mrt != 0, t, q));
   b->total_rows = t.L > 0 ? 0 : (int)rows;
   b->grid = batch_grid(resident, (int)items.size(), b->total_rows);
-  if (t.L > 0) layout::deal(items, b->grid, t.ts > 1 ? pipe_fill(t.ts) : kStepFill);
+  if (t.ts == 1 && t.L > 0 && t.L < layout::kWalkRows) layout::walk(items, b->grid);
+  else if (t.L > 0) layout::deal(items, b->grid, t.ts > 1 ? pipe_fill(t.ts) : kStepFill);
   HIPCHK(hipMemcpyAsync(b->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, b->st));
   HIPCHK(hipStreamSynchronize(b->st));
   b->nitems = (int)items.size();
