@@ -12,7 +12,7 @@ from tests.gpu_common import CS, PR, pair, slab_rho
 
 pytestmark = pytest.mark.gpu
 
-# widest strip of a tile: 64 k - (4 steps - 2) columns, k = 4 (FP16 storage) or 3, 2 for
+# widest strip of a tile: 64 k - (4 steps - 2) columns, k = 4 (FP32 arithmetic) or 3, 2 for
 # the narrow class; FP64 strip edges are rounded down to 8 columns
 FOUR = [(4, 0, 1, 4), (2, 0, 1, 4), (4, 5, 1, 4), (2, 1, 1, 4), (8, 16, 1, 4)]
 # patches of 22 x 22 (four steps: 8 x 8 stored) and 32 x 32 nodes (26 and 22 square)
