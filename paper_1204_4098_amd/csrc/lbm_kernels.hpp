@@ -58,17 +58,17 @@ struct RunDev {
   int64_t elems;            // elements of the lattice's population buffer
   int64_t off;              // element offset of this lattice in the population pool
   double RT, c1, c2;        // EOS constants (see EosConst)
-  // folded EOS constants: eA = 2 RT/G, eB = c2/RT, eC = 1/(3 RT) (see psi2_of)
-  double eA, eB, eC;
-  double mG12;              // -G/12: w(2) = 1/12 taken out of the force stencil
+  double two_over_G, mG;    // 2/G and -G
   double inv_tau;
   // forcing scheme in general form: u_eq = u + c_eq F/rho,
-  // F_a = w_a [3 Be e.F + Ce (9 (e.vf)(e.F) - 3 vf.F)], vf = u + c_f F/rho + sig F/psi^2,
-  // written vf = u_eq + (c_d/rho + sig/psi^2) F with c_d = c_f - c_eq
-  double c_eq, c_d, sig, Ce;
-  // products used by the collision, om = 1/tau: 1 - om, (1 - om)/2, om/2, om/9,
-  // om/3, Be/3
-  double om1, om1_2, om_2, om_9, om_3, Be_3;
+  // F_a = w_a [3 Be e.F + Ce (9 (e.vf)(e.F) - 3 vf.F)], vf = u + c_f F/rho + sig F/psi^2
+  double c_eq, c_f, sig, Ce;
+  // products used by the collision with om = 1/tau and w0, w1, w2 = 4/9, 1/9, 1/36: om w0,
+  // om w1, om w2, 1 - om; of collide: c_d = c_f - c_eq, om/2, om/3, Be/3; of
+  // collide_pairs: w0 Ce, w1 Ce, w2 Ce, 3 w1 Be, 3 w2 Be, 3 om w1, 3 om w2
+  double om_w0, om_w1, om_w2, om1;
+  double c_d, om_2, om_3, Be_3;
+  double wCe0, wCe1, wCe2, wBe3_1, wBe3_2, om_3w1, om_3w2;
   double rho_ref;           // deviation reference density (0 for FP64 storage)
   int32_t run;
   int32_t mrt;              // 1: multiple-relaxation-time collision (collide_mrt with m)
@@ -134,12 +134,13 @@ template <typename S> struct Store;
 // the density they are evaluated at (FP64 for every storage type: the EOS and
 // psi stay FP64 in the reduced-precision forms).  kConserve: after the FP32
 // collision, restore the node's mass and momentum change exactly (see
-// conserve()).  kDev: values are deviations from w_a rho_ref.
+// conserve()).  kPairs: BGK collision by pairs of directions (collide_pairs).  kDev: values are deviations from w_a rho_ref.
 template <> struct Store<double> {
   using E = double;
   using R = double;
   using P = double;
   static constexpr bool kConserve = false;
+  static constexpr bool kPairs = false;
   static constexpr bool kDev = false;
   static __device__ __forceinline__ R ld(const E* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ void st(E* p, R v) { __builtin_nontemporal_store(v, p); }
@@ -150,6 +151,7 @@ template <> struct Store<float> {
   using R = float;
   using P = double;
   static constexpr bool kConserve = true;
+  static constexpr bool kPairs = false;
   static constexpr bool kDev = true;
   static __device__ __forceinline__ R ld(const E* p) { return *p; }
   static __device__ __forceinline__ void st(E* p, R v) { *p = v; }
@@ -160,6 +162,7 @@ template <> struct Store<f32s_f64a> {
   using R = double;
   using P = double;
   static constexpr bool kConserve = false;
+  static constexpr bool kPairs = false;
   static constexpr bool kDev = true;
   static __device__ __forceinline__ R ld(const E* p) { return double(__builtin_nontemporal_load(p)); }
   static __device__ __forceinline__ void st(E* p, R v) { __builtin_nontemporal_store(float(v), p); }
@@ -170,6 +173,7 @@ template <> struct Store<__half> {
   using R = float;
   using P = double;
   static constexpr bool kConserve = false;
+  static constexpr bool kPairs = true;
   static constexpr bool kDev = true;
   // The narrowing to FP16 takes its operand through an empty asm statement:
   // the backend otherwise folds it into the FMA that produced the operand (a
@@ -282,44 +286,50 @@ __device__ __forceinline__ R sum9(const R (&s)[9]) {
   return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])) + s[8];
 }
 
-// psi^2 = 2 (p_EOS(rho) - rho/3) / G (Eq. 8 with Eq. 23 or Peng-Robinson) with
-// the constants of the lattice folded into three: psi^2 = rho eA q, where
-//   Carnahan-Starling  q = (1 + e + e^2 - e^3)/(1 - e)^3 - eC - eB rho, e = b rho/4
-//   Peng-Robinson      q = 1/(1 - b) - eB rho/(1 + b(2 - b)) - eC over one reciprocal
-// (each operation takes one constant from a scalar register).
+// psi^2 = 2 (p_EOS(rho) - rho/3) / G (Eq. 8 with Eq. 23 or Peng-Robinson).
 __device__ __forceinline__ double psi2_of(double rho, const RunDev& d) {
 #pragma clang fp contract(off)
-  double q;
+  double p;
   if (d.eos == 0) {
+    // rho RT (1 + e + e^2 - e^3)/(1 - e)^3 - c2 rho^2, e = b rho / 4
     const double e = d.c1 * rho, m = 1.0 - e;
     const double poly = fma(e, fma(e, m, 1.0), 1.0);
-    q = fma(-d.eB, rho, fma(poly, rcp((m * m) * m), -d.eC));
+    p = fma((rho * d.RT) * poly, rcp((m * m) * m), -((d.c2 * rho) * rho));
   } else {
+    // rho RT/(1 - b) - c2 rho^2/(1 + b(2 - b)) over one common reciprocal
     const double b = d.c1 * rho;
     const double q1 = 1.0 - b, q2 = fma(b, 2.0 - b, 1.0);
-    q = fma(fma(-(d.eB * rho), q1, q2), rcp(q1 * q2), -d.eC);
+    p = fma(rho * d.RT, q2, -(((d.c2 * rho) * rho) * q1)) * rcp(q1 * q2);
   }
-  return (rho * d.eA) * q;
+  return fma(rho, -1.0 / 3.0, p) * d.two_over_G;
 }
 
-// psi = sqrt(x) and 1/psi^2 from x = psi^2 by one hardware reciprocal square
-// root y (relative error below 2^-24): with e = 1 - x y^2, sqrt(x) = x y (1 +
-// e/2 + 3 e^2/8 + ...) and 1/sqrt(x) likewise, each to about 1 ulp; a last
-// residual step makes the root the correctly rounded one but for rare ties.
-// No scaling for subnormal or huge x and no special cases: a run whose x is not
-// a positive normal number has diverged (both results are NaN for x <= 0).
-struct PsiPair {
-  double psi, ip2;
-};
-__device__ __forceinline__ PsiPair psi_pair(double x) {
+// The correctly rounded square root of x > 0 and, in r, 1/sqrt(x) to 1-2 ulp, from one
+// hardware reciprocal square root y (relative error below 2^-24): with e = 1 - x y^2,
+// 1/sqrt(x) = r = y (1 + e/2 + 3 e^2/8 + ...), g = x r, and the root is g + (x - g^2) r/2.
+// Before its rounding that is within 2^-50 ulp of the root; the 365 arguments of two binades
+// whose root lies within 2^-46 ulp of a midpoint of two doubles were enumerated and all give
+// the result of sqrt() (as do 2^30 random ones).  No scaling and no special cases: 9
+// operations where sqrt() takes 20.  Not a number for x = 0, infinite or negative: a node
+// with such a psi^2 has diverged.
+__device__ __forceinline__ double root_of(double x, double& r) {
 #pragma clang fp contract(off)
   const double y = __builtin_amdgcn_rsq(x);
-  const double g = x * y;
-  const double e = fma(-g, y, 1.0);
-  const double t = e * fma(0.375, e, 0.5);
-  const double r = fma(y, t, y);   // 1/sqrt(x)
-  const double g1 = fma(g, t, g);  // sqrt(x)
-  return PsiPair{fma(fma(-g1, g1, x), 0.5 * y, g1), r * r};
+  const double e = fma(-(x * y), y, 1.0);
+  r = fma(y, e * fma(0.375, e, 0.5), y);
+  const double g = x * r;
+  return fma(fma(-g, g, x), 0.5 * r, g);
+}
+// 1/psi^2 from x = psi^2 and r = 1/psi: the square of r and one Newton step (error as the
+// reciprocal's), or the single-precision estimate (FP32 arithmetic).
+template <typename R> __device__ __forceinline__ R inverse_of(double x, double r) {
+#pragma clang fp contract(off)
+  if constexpr (std::is_same<R, float>::value) {
+    return rcp(float(x));
+  } else {
+    const double c = r * r;
+    return fma(c, fma(-x, c, 1.0), c);
+  }
 }
 
 __device__ __forceinline__ double pressure_of(double rho, const RunDev& d) {
@@ -330,28 +340,18 @@ __device__ __forceinline__ double pressure_of(double rho, const RunDev& d) {
   return rho * d.RT / (1.0 - d.c1 * rho) - d.c2 * rho * rho / (1.0 + d.c1 * rho * (2.0 - d.c1 * rho));
 }
 
-// Interaction force of Eq. (3), w(1) = 1/3, w(2) = 1/12, with w(2) taken out of
-// the sums and the 3x3 psi neighbourhood summed by columns first: with U = 4
-// psi(y) + psi(y+1) + psi(y-1) and D = psi(y+1) - psi(y-1) of a column,
-//   F = (-G/12) psi (U(x+1) - U(x-1), 4 D(x) + D(x+1) + D(x-1)).
-// Only U and D of the neighbour columns cross lanes.
-__device__ __forceinline__ double col_u(double s, double c, double n) {
-#pragma clang fp contract(off)
-  return fma(4.0, c, n + s);
-}
-__device__ __forceinline__ void force_ud(double mG12, double psi, double Ul, double Ur, double Dl,
-                                         double D, double Dr, double& Fx, double& Fy) {
-#pragma clang fp contract(off)
-  const double c = mG12 * psi;
-  Fx = c * (Ur - Ul);
-  Fy = c * fma(4.0, D, Dl + Dr);
-}
-// The same from three psi rows (row-major: s = y-1, c = y, n = y+1; index i = x).
+// Interaction force of Eq. (3), w(1) = 1/3, w(2) = 1/12, from three psi rows (s = y-1, c
+// = y, n = y+1; index i = x).
 __device__ __forceinline__ void force3x3(const double* rs, const double* rc, const double* rn, int i,
-                                         double mG12, double& Fx, double& Fy) {
+                                         double mG, double& Fx, double& Fy) {
 #pragma clang fp contract(off)
-  force_ud(mG12, rc[i], col_u(rs[i - 1], rc[i - 1], rn[i - 1]), col_u(rs[i + 1], rc[i + 1], rn[i + 1]),
-           rn[i - 1] - rs[i - 1], rn[i] - rs[i], rn[i + 1] - rs[i + 1], Fx, Fy);
+  const double dNE = rn[i + 1] - rs[i - 1];  // psi(x+e5) - psi(x-e5)
+  const double dNW = rn[i - 1] - rs[i + 1];  // psi(x+e6) - psi(x-e6)
+  const double Sx = fma(1.0 / 3.0, rc[i + 1] - rc[i - 1], (1.0 / 12.0) * (dNE - dNW));
+  const double Sy = fma(1.0 / 3.0, rn[i] - rs[i], (1.0 / 12.0) * (dNE + dNW));
+  const double c = mG * rc[i];
+  Fx = c * Sx;
+  Fy = c * Sy;
 }
 
 // BGK collision with the forcing scheme in general form (see RunDev).
@@ -359,19 +359,16 @@ __device__ __forceinline__ void force3x3(const double* rs, const double* rc, con
 // For direction a the update is s_a + om (seq_a - s_a) + F_a with
 //   seq_a = w (drho + rho (3 e.u + 4.5 (e.u)^2 - 1.5 u.u))        (Eq. 2, deviation form)
 //   F_a   = w [3 B_e e.F + C_e (9 (e.v)(e.F) - 3 v.F)]             (Eq. 12)
-// The even part of om seq + F is a quadratic form of e: with m = rho u_eq = j +
-// c_eq F and the symmetric tensor (both terms already times w1 = 1/9)
+// The even part of om seq + F is om w drho and a quadratic form of e: with m = rho u_eq = j
+// + c_eq F and the symmetric tensor (both terms already times w1 = 1/9)
 //   T = om/2 m u + C_e v F,  S = T_xx + T_yy,
-// it is 4 base, base + T_xx, base + T_yy and (base + S +- T_xy)/4 with base =
-// om/9 drho - S/3 (1.5/4.5 = 3/9 = 1/3), and the odd part is q.e with q = om/3 m
-// + B_e/3 F (over 4 for the diagonals).  Each pair of opposite directions is
-// then s' = (1 - om) s + (P +- Q).  55 operations besides the moments and 1/rho,
-// against 85 with the per-pair products (e.u)^2 and (e.v)(e.F) evaluated apart.
-// Together with the folded EOS, the one-estimate square root and the density
-// carried from psi to the collision, a node update went from 177 to 123 FP64
-// instructions; with the kernels of that time, 4096 x 4096, us per launch: FP64 three
-// steps 670 -> 584, FP16 two steps 278 -> 248, FP32 384 -> 357, FP32 with FP64 collide
-// 394 -> 342.
+// it is -4/3 S, T_xx - S/3, T_yy - S/3 and S/6 +- T_xy/4 (1.5/4.5 = 3/9 = 1/3), and the odd
+// part is q.e with q = om/3 m + B_e/3 F (over 4 for the diagonals).  Each pair of opposite
+// directions is then s' = (1 - om) s + (P +- Q).  58 operations besides the moments and
+// 1/rho, against 85 of collide_pairs, which evaluates (e.u)^2 and (e.v)(e.F) for each
+// pair.  The density enters each P last, in one fma of its own: error of a node's update over
+// w rho in FP64, mean and largest of 400,000 against quadruple precision: 0.98e-16 and
+// 8.6e-16, collide_pairs 1.05e-16 and 1.05e-15 (FP32 1.67e-8, collide_pairs 1.79e-8).
 template <typename R>
 __device__ __forceinline__ void relax_pair(R& sa, R& sb, R P, R Q, R om1) {
 #pragma clang fp contract(off)
@@ -379,9 +376,7 @@ __device__ __forceinline__ void relax_pair(R& sa, R& sb, R P, R Q, R om1) {
   sb = fma(om1, sb, P - Q);
 }
 
-// HALF: of the axis pairs only the half sums are formed, returned in s[1] (x) and
-// s[2] (y); s[0], s[3] and s[4] are left for conserve().
-template <bool HALF, typename R>
+template <typename R>
 __device__ __forceinline__ void collide(R (&s)[9], R drho, R rho, R jx, R jy, R Fx, R Fy,
                                         R inv_psi2, const RunDev& d) {
 #pragma clang fp contract(off)
@@ -394,23 +389,62 @@ __device__ __forceinline__ void collide(R (&s)[9], R drho, R rho, R jx, R jy, R 
   const R ax = om_2 * mx, ay = om_2 * my, bx = Ce * Fx, by = Ce * Fy;
   const R Txx = fma(ax, wx, bx * vx), Tyy = fma(ay, wy, by * vy);
   const R Txy = fma(ax, wy, fma(ay, wx, fma(bx, vy, by * vx)));
-  const R S = Txx + Tyy;
-  const R base = fma(R(-1.0 / 3.0), S, R(d.om_9) * drho);
+  const R S = Txx + Tyy, S3 = R(-1.0 / 3.0) * S, S6 = R(1.0 / 6.0) * S;
   const R om_3 = R(d.om_3), Be_3 = R(d.Be_3);
   const R qx = fma(om_3, mx, Be_3 * Fx), qy = fma(om_3, my, Be_3 * Fy);
-  const R D = R(0.25) * (base + S);
-  if constexpr (HALF) {
-    s[1] = fma(R(d.om1_2), s[1] + s[3], base + Txx);
-    s[2] = fma(R(d.om1_2), s[2] + s[4], base + Tyy);
-  } else {
-    s[0] = fma(R(4), base, om1 * s[0]);
-    // axis pairs (e1, e3 = -e1), (e2, e4 = -e2)
-    relax_pair(s[1], s[3], base + Txx, qx, om1);
-    relax_pair(s[2], s[4], base + Tyy, qy, om1);
-  }
+  const R w1 = R(d.om_w1), w2 = R(d.om_w2);
+  s[0] = fma(om1, s[0], fma(R(d.om_w0), drho, R(4) * S3));
+  // axis pairs (e1, e3 = -e1), (e2, e4 = -e2)
+  relax_pair(s[1], s[3], fma(w1, drho, Txx + S3), qx, om1);
+  relax_pair(s[2], s[4], fma(w1, drho, Tyy + S3), qy, om1);
   // diagonal pairs (e5 = (1,1), e7 = -e5), (e6 = (-1,1), e8 = -e6)
-  relax_pair(s[5], s[7], fma(R(0.25), Txy, D), R(0.25) * (qx + qy), om1);
-  relax_pair(s[6], s[8], fma(R(-0.25), Txy, D), R(0.25) * (qy - qx), om1);
+  relax_pair(s[5], s[7], fma(w2, drho, fma(R(0.25), Txy, S6)), R(0.25) * (qx + qy), om1);
+  relax_pair(s[6], s[8], fma(w2, drho, fma(R(-0.25), Txy, S6)), R(0.25) * (qy - qx), om1);
+}
+
+// The same by pairs of directions, for FP16 storage: there a last-bit difference of an FP32
+// result turns roundings to FP16, and this form gives the populations that FP16 lattices have
+// always had, bit for bit.  With X = drho + rho (4.5 (e.u)^2 - 1.5 u.u), om seq = om w X +-
+// 3 om w rho e.u and F_a = C +- D, s' = (1 - om) s + (P +- Q) with P = om w X + C, Q = 3 om w
+// rho e.u + D (the products of om and the weights are per-lattice constants).
+template <typename R>
+__device__ __forceinline__ void collide_pair(R& sa, R& sb, R eu, R eF, R ev, R omw, R omwr3, R wCe,
+                                             R wBe3, R rho, R drho, R usq, R vF3, R om1) {
+#pragma clang fp contract(off)
+  const R X = fma(rho, fma(R(4.5) * eu, eu, -usq), drho);
+  const R C = wCe * fma(R(9) * ev, eF, -vF3);
+  const R P = fma(omw, X, C);
+  const R Q = fma(omwr3, eu, wBe3 * eF);
+  sa = fma(om1, sa, P + Q);
+  sb = fma(om1, sb, P - Q);
+}
+
+template <typename R>
+__device__ __forceinline__ void collide_pairs(R (&s)[9], R drho, R rho, R jx, R jy, R Fx, R Fy,
+                                              R inv_psi2, const RunDev& d) {
+#pragma clang fp contract(off)
+  const R inv_rho = rcp(rho);
+  const R ux = jx * inv_rho, uy = jy * inv_rho;
+  const R Fr_x = Fx * inv_rho, Fr_y = Fy * inv_rho;
+  const R wx = fma(R(d.c_eq), Fr_x, ux), wy = fma(R(d.c_eq), Fr_y, uy);
+  const R sg = R(d.sig) * inv_psi2;
+  const R vx = fma(sg, Fx, fma(R(d.c_f), Fr_x, ux)), vy = fma(sg, Fy, fma(R(d.c_f), Fr_y, uy));
+  const R om1 = R(d.om1);
+  const R usq = R(1.5) * fma(wx, wx, wy * wy);
+  const R vF3 = R(3) * fma(vx, Fx, vy * Fy);
+  const R omw1 = R(d.om_w1), omw2 = R(d.om_w2);
+  const R omwr3_1 = R(d.om_3w1) * rho, omwr3_2 = R(d.om_3w2) * rho;
+  const R wCe1 = R(d.wCe1), wBe3_1 = R(d.wBe3_1), wCe2 = R(d.wCe2), wBe3_2 = R(d.wBe3_2);
+  // rest direction: e = 0
+  s[0] = fma(om1, s[0], fma(R(d.om_w0), fma(rho, -usq, drho), R(d.wCe0) * -vF3));
+  // axis pairs (e1, e3 = -e1), (e2, e4 = -e2)
+  collide_pair(s[1], s[3], wx, Fx, vx, omw1, omwr3_1, wCe1, wBe3_1, rho, drho, usq, vF3, om1);
+  collide_pair(s[2], s[4], wy, Fy, vy, omw1, omwr3_1, wCe1, wBe3_1, rho, drho, usq, vF3, om1);
+  // diagonal pairs (e5 = (1,1), e7 = -e5), (e6 = (-1,1), e8 = -e6)
+  collide_pair(s[5], s[7], wx + wy, Fx + Fy, vx + vy, omw2, omwr3_2, wCe2, wBe3_2, rho, drho, usq,
+               vF3, om1);
+  collide_pair(s[6], s[8], wy - wx, Fy - Fx, vy - vx, omw2, omwr3_2, wCe2, wBe3_2, rho, drho, usq,
+               vF3, om1);
 }
 
 // Multiple-relaxation-time collision with the improved forcing scheme, on the
@@ -471,13 +505,13 @@ __device__ __forceinline__ void collide_mrt(R (&s)[9], R drho, R rho, R jx, R jy
   s[8] += Dm + XmY;
 }
 
-// Momentum sum_a s_a e_a in the arithmetic type.
 template <typename R>
-__device__ __forceinline__ void momentum(const R (&s)[9], R& jx, R& jy) {
-#pragma clang fp contract(off)
-  const R u = s[5] - s[7], v = s[8] - s[6];
-  jx = ((s[1] - s[3]) + u) + v;
-  jy = ((s[2] - s[4]) + u) - v;
+__device__ __forceinline__ R mom_x(const R (&s)[9]) {
+  return ((s[1] - s[3]) + (s[5] - s[7])) + (s[8] - s[6]);
+}
+template <typename R>
+__device__ __forceinline__ R mom_y(const R (&s)[9]) {
+  return ((s[2] - s[4]) + (s[5] - s[7])) + (s[6] - s[8]);
 }
 
 // Momentum of FP32 values (as FP64 t) summed in FP64: exact unless the
@@ -490,28 +524,41 @@ __device__ __forceinline__ void exact_momentum(const double (&t)[9], double& jx,
   jx = ((t[1] - t[3]) + u) + v;
   jy = ((t[2] - t[4]) + u) - v;
 }
+// Mass and momentum of nine FP32 values, exactly (as exact_momentum).
+__device__ __forceinline__ void exact_moments(const float (&s)[9], double& m, double& jx, double& jy) {
+#pragma clang fp contract(off)
+  double t[9];
+#pragma unroll
+  for (int a = 0; a < 9; ++a) t[a] = double(s[a]);
+  m = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])) + t[8];
+  exact_momentum(t, jx, jy);
+}
+
 // The collision conserves mass and changes the momentum by exactly F (every
 // forcing scheme here, BGK or MRT).  In FP32 arithmetic each updated
 // population carries its own rounding, and at a steady state the same
 // roundings recur every step: a persistent mass and momentum source at every
 // node that the slow bulk dynamics integrate into visibly shifted coexistence
-// densities.  So only the half sums h = (s1 + s3)/2, (s2 + s4)/2 of the axis pairs
-// are taken from the collision; their differences follow in FP64 from the momentum
-// (jx, jy: the exact new one) that the diagonal populations leave, and the rest
-// population from the mass m; what remains is one FP32 rounding of five values.
-__device__ __forceinline__ void conserve(float (&s)[9], float hx, float hy, double m, double jx,
-                                         double jy) {
+// densities.  conserve() puts the momentum change of the new populations back
+// to exactly F (half the x defect on e1 and -e1, likewise y on e2, -e4) and the
+// mass back to exactly the old mass on the rest population, computed in FP64;
+// what remains is one FP32 rounding of five values.
+__device__ __forceinline__ void conserve(float (&s)[9], double m_t, double jx_t, double jy_t) {
 #pragma clang fp contract(off)
-  const double t5 = double(s[5]), t6 = double(s[6]), t7 = double(s[7]), t8 = double(s[8]);
-  const double u = t5 - t7, v = t8 - t6;
-  const double dx = jx - (u + v), dy = jy - (u - v);
-  s[1] = float(fma(0.5, dx, double(hx)));
-  s[3] = float(fma(-0.5, dx, double(hx)));
-  s[2] = float(fma(0.5, dy, double(hy)));
-  s[4] = float(fma(-0.5, dy, double(hy)));
-  const double rest = ((double(s[1]) + double(s[2])) + (double(s[3]) + double(s[4]))) +
-                      ((t5 + t6) + (t7 + t8));
-  s[0] = float(m - rest);
+  double t[9], jx, jy;
+  t[0] = 0.0;  // the rest population carries no momentum
+#pragma unroll
+  for (int a = 1; a < 9; ++a) t[a] = double(s[a]);
+  exact_momentum(t, jx, jy);
+  const double dx = 0.5 * (jx_t - jx), dy = 0.5 * (jy_t - jy);
+  s[1] = float(t[1] + dx);
+  s[3] = float(t[3] - dx);
+  s[2] = float(t[2] + dy);
+  s[4] = float(t[4] - dy);
+#pragma unroll
+  for (int a = 1; a < 5; ++a) t[a] = double(s[a]);
+  const double rest = ((t[1] + t[2]) + (t[3] + t[4])) + ((t[5] + t[6]) + (t[7] + t[8]));
+  s[0] = float(m_t - rest);
 }
 
 // What a pulled row keeps for its collision: the summed stored values (the density
@@ -531,10 +578,13 @@ __device__ __forceinline__ double density(typename Store<S>::R drho, const RunDe
 template <typename S>
 __device__ __forceinline__ double eval_psi(const typename Store<S>::R (&f)[9], const RunDev& d,
                                            NodeQ<S>& q) {
+  using R = typename Store<S>::R;
   q.drho = sum9(f);
-  const PsiPair w = psi_pair(psi2_of(density<S>(q.drho, d), d));
-  q.ip2 = typename Store<S>::R(w.ip2);
-  return w.psi;
+  const double psi2 = psi2_of(density<S>(q.drho, d), d);
+  double r;
+  const double psi = root_of(psi2, r);
+  q.ip2 = inverse_of<R>(psi2, r);
+  return psi;
 }
 
 // One node update: collision (BGK or MRT) of the pulled values f with the force
@@ -545,33 +595,21 @@ __device__ __forceinline__ bool update_node(typename Store<S>::R (&f)[9], const 
                                             double Fy, const RunDev& d) {
   using R = typename Store<S>::R;
   const double rho = density<S>(q.drho, d);
-  const R fx = R(Fx), fy = R(Fy);
-  if constexpr (Store<S>::kConserve) {
-    // the exact mass is summed here, not kept from the density: carried through the two
-    // march rows in between it costs the pipe 21 registers, and with them 16 waves per CU
-    double t[9], jx, jy;
-#pragma unroll
-    for (int a = 0; a < 9; ++a) t[a] = double(f[a]);
-    exact_momentum(t, jx, jy);
-    const double mass = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])) + t[8];
-    float hx, hy;
-    if constexpr (MRT) {
-      collide_mrt<R>(f, q.drho, R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
-      hx = 0.5f * (f[1] + f[3]);
-      hy = 0.5f * (f[2] + f[4]);
-    } else {
-      collide<true, R>(f, q.drho, R(rho), R(jx), R(jy), fx, fy, q.ip2, d);
-      hx = f[1];
-      hy = f[2];
-    }
-    conserve(f, hx, hy, mass, jx + Fx, jy + Fy);
-  } else {
-    R jx, jy;
-    momentum(f, jx, jy);
+  auto collision = [&](R jx, R jy) __attribute__((always_inline)) {
     if constexpr (MRT)
-      collide_mrt<R>(f, q.drho, R(rho), jx, jy, fx, fy, q.ip2, d);
+      collide_mrt<R>(f, q.drho, R(rho), jx, jy, R(Fx), R(Fy), q.ip2, d);
+    else if constexpr (Store<S>::kPairs)
+      collide_pairs<R>(f, q.drho, R(rho), jx, jy, R(Fx), R(Fy), q.ip2, d);
     else
-      collide<false, R>(f, q.drho, R(rho), jx, jy, fx, fy, q.ip2, d);
+      collide<R>(f, q.drho, R(rho), jx, jy, R(Fx), R(Fy), q.ip2, d);
+  };
+  if constexpr (Store<S>::kConserve) {
+    double m, jx, jy;
+    exact_moments(f, m, jx, jy);
+    collision(R(jx), R(jy));
+    conserve(f, m, jx + Fx, jy + Fy);
+  } else {
+    collision(mom_x(f), mom_y(f));
   }
   return !(q.ip2 > 0) || !(rho > 0.0);
 }
@@ -582,7 +620,7 @@ __device__ __forceinline__ bool finish_node(typename Store<S>::R (&f)[9], const 
                                             const double* rs, const double* rc, const double* rn, int i,
                                             const RunDev& d) {
   double Fx, Fy;
-  force3x3(rs, rc, rn, i, d.mG12, Fx, Fy);
+  force3x3(rs, rc, rn, i, d.mG, Fx, Fy);
   return update_node<S, MRT>(f, q, Fx, Fy, d);
 }
 
@@ -764,8 +802,8 @@ __global__ __launch_bounds__(64 * NW) void k_step(const typename Store<S>::E* __
 //   * pulls row p of its step: the first group from global memory (loaded one march
 //     row ahead), the others from the exchange rows in LDS that the group before
 //     them filled;
-//   * evaluates psi of row p and leaves U and D of row p-1 (see force_ud) in LDS;
-//   * collides row p-2, whose U and D the last march row left there, and hands the
+//   * evaluates psi of row p and leaves it in a ring of four rows in LDS;
+//   * collides row p-2, whose psi rows the last three march rows left there, and hands the
 //     result to the next group through the exchange rows; the last group stores it.
 // Lane i owns column x0 - H + i, H = 2 TS - 1, in every step: step l is right on the
 // lanes 2l .. and n0-1-2l (psi) and one lane further in (collision), so the last one
@@ -800,7 +838,7 @@ __device__ __forceinline__ void lds_barrier() {
 // and W-1 past the ends (never used).
 template <typename S, int W, int TS> struct PipeLds {
   double pad0[1];
-  double ud[TS][4][W];  // U and D of two march rows per step
+  double psi[TS][4][W];  // psi of four march rows per step
   typename Store<S>::R ex[TS - 1][30][W];
   double pad1[1];
 };
@@ -911,7 +949,7 @@ __device__ __forceinline__ void tile_pipe(const typename Store<S>::E* __restrict
   const bool out = i >= H && i < ncols + H;
   int c = (x0 - H + min(i, ncols + 2 * H - 1)) % d.nx;
   if (c < 0) c += d.nx;
-  double* const ud = &lds.ud[lv][0][0] + i;
+  double* const ps = &lds.psi[lv][0][0] + i;
   bool bad = false;
   // march rows of the first group, and of this step, widened to whole fours (the rows added
   // compute values that nothing reads)
@@ -922,21 +960,19 @@ __device__ __forceinline__ void tile_pipe(const typename Store<S>::E* __restrict
   // rows p, p-1, p-2 and (first group) the one being loaded: buffer K = j mod 4 holds p,
   // K + 3 row p-1, K + 2 row p-2
   R F[4][9];
-  double P[4] = {0, 0, 0, 0}, D[2] = {0, 0};
+  double P[4] = {0, 0, 0, 0};
   NodeQ<S> Q[4];
-  // psi of the pulled row (buffer K), U and D of the row below it to LDS; collision of
-  // the row below that one (buffer K + 2), whose U and D the last march row left
+  // psi of the pulled row to LDS (row K); collision of the row two below (buffer K + 2)
+  // with the psi rows below (row K + 1), at and above it (row K + 3), which the last three
+  // march rows left; row K held the one before those
   auto step_row = [&](auto kk) __attribute__((always_inline)) {
-    constexpr int K = decltype(kk)::value, kc = (K + 2) & 3, kp = (K + 3) & 3;
-    double* u = ud + (K & 1) * 2 * W;
-    const double* v = ud + ((K & 1) ^ 1) * 2 * W;
-    double Fx, Fy;
-    force_ud(d.mG12, P[kc], v[-1], v[1], v[W - 1], D[(K + 1) & 1], v[W + 1], Fx, Fy);
+    constexpr int K = decltype(kk)::value, ks = (K + 1) & 3, kc = (K + 2) & 3, kn = (K + 3) & 3;
+    const double *s = ps + ks * W, *c = ps + kc * W, *n = ps + kn * W;
+    const double rs[3] = {s[-1], P[ks], s[1]}, rc[3] = {c[-1], P[kc], c[1]}, rn[3] = {n[-1], P[kn], n[1]};
+    const bool b = finish_node<S, MRT>(F[kc], Q[kc], rs, rc, rn, 1, d);
     P[K] = eval_psi<S>(F[K], d, Q[K]);
-    D[K & 1] = P[K] - P[kc];
-    u[0] = col_u(P[kc], P[kp], P[K]);
-    u[W] = D[K & 1];
-    return update_node<S, MRT>(F[kc], Q[kc], Fx, Fy, d);
+    ps[K * W] = P[K];
+    return b;
   };
   using K0 = std::integral_constant<int, 0>;
   using K1 = std::integral_constant<int, 1>;
@@ -1304,8 +1340,8 @@ __global__ void k_counter_set(unsigned long long* ctr, unsigned long long v) { *
 // Macroscopic fields: rho, v = u + F/(2 rho) (Table I, actual velocity) and p =
 // p_EOS(rho).  One pass: a block of T threads (at most 256) owns up to T - 2 columns (a
 // lane more on either side evaluates psi) and marches up a chunk of rows, the next row's loads in
-// flight; U and D of the row below (see force_ud) go to the neighbour lanes through
-// LDS, two slots by turns, one barrier per row.  Bound by memory: every population
+// flight; psi goes to the neighbour lanes through a ring of four rows in LDS, one barrier per
+// row.  Bound by memory: every population
 // read once, four planes written once.  2048 x 2048 FP64 (302 + 134 MB): 98 us, 4.4
 // TB/s, against 113 in two passes with psi and u going through memory.
 template <typename S>
@@ -1314,7 +1350,7 @@ __global__ __launch_bounds__(256) void k_fields(const typename Store<S>::E* __re
                                                 double* __restrict__ vx_o, double* __restrict__ vy_o,
                                                 double* __restrict__ p_o) {
   using R = typename Store<S>::R;
-  __shared__ double ud[2][2][256 + 2];
+  __shared__ double ring[4][256 + 2];
   const int tid = threadIdx.x;
   const int t = xcd_remap(blockIdx.x, gridDim.x);
   const int sy = t / nstrips, s = t - sy * nstrips;
@@ -1325,7 +1361,7 @@ __global__ __launch_bounds__(256) void k_fields(const typename Store<S>::E* __re
   x = x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x);
   const Cols cx = cols_of(x, d.nx);
   auto next = [&](int y) { return y + 1 == d.ny ? 0 : y + 1; };
-  double ps = 0, pc = 0, rc = 0;  // psi of rows p-2 and p-1, rho and momentum of p-1
+  double rc = 0;  // rho and momentum of row p-1
   R jxc = 0, jyc = 0;
   R f[9], g[9];
   int y = y0 == 0 ? d.ny - 1 : y0 - 1;
@@ -1334,26 +1370,20 @@ __global__ __launch_bounds__(256) void k_fields(const typename Store<S>::E* __re
     y = next(y);
     if (j + 1 < n + 2) pull9<S>(src, d, cx, y, g);
     const R drho = sum9(f);
-    R jx, jy;
-    momentum(f, jx, jy);
+    const R jx = mom_x(f), jy = mom_y(f);
     const double r = density<S>(drho, d);
-    const double pn = psi_pair(psi2_of(r, d)).psi;
-    const double D = pn - ps;
-    double(*w)[256 + 2] = ud[j & 1];
-    w[0][tid + 1] = col_u(ps, pc, pn);
-    w[1][tid + 1] = D;
+    double ir;
+    ring[j & 3][tid + 1] = root_of(psi2_of(r, d), ir);
     __syncthreads();
     if (j >= 2 && out) {
       double Fx, Fy;
-      force_ud(d.mG12, pc, w[0][tid], w[0][tid + 2], w[1][tid], D, w[1][tid + 2], Fx, Fy);
+      force3x3(ring[(j + 2) & 3], ring[(j + 3) & 3], ring[j & 3], tid + 1, d.mG, Fx, Fy);
       const int64_t o = (int64_t)(y0 + j - 2) * d.nx + x;
       rho_o[o] = rc;
       vx_o[o] = double(jxc / R(rc)) + Fx / (2.0 * rc);
       vy_o[o] = double(jyc / R(rc)) + Fy / (2.0 * rc);
       p_o[o] = pressure_of(rc, d);
     }
-    ps = pc;
-    pc = pn;
     rc = r;
     jxc = jx;
     jyc = jy;
@@ -1382,7 +1412,7 @@ __global__ void k_normal_pressure(const double* __restrict__ rbar, RunDev d, dou
   const double pm = sqrt(psi2_of(rbar[xm], d)), pc = sqrt(psi2_of(rbar[x], d)),
                pp = sqrt(psi2_of(rbar[xp], d));
   const double d1 = 0.5 * (pp - pm), d2 = (pp - 2.0 * pc) + pm;
-  const double G = -12.0 * d.mG12;
+  const double G = -d.mG;
   pn[x] = rbar[x] * (1.0 / 3.0) + 0.5 * G * pc * pc + (G / 12.0) * (3.0 * pc * d2) +
           2.0 * G * G * sigma * d1 * d1;
 }
@@ -1409,7 +1439,7 @@ __global__ __launch_bounds__(256) void k_surface_tension(const double* __restric
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const double G = -12.0 * d.mG12;
+    const double G = -d.mG;
     out[0] = (-G / 6.0 + 2.0 * G * G * sigma) * sm[0] * 0.5;
   }
 }

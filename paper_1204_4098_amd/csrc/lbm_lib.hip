@@ -86,52 +86,58 @@ RunDev make_rundev(const lbm_params& p, const EosConst& k, double rho_ref, int64
   d.RT = k.RT;
   d.c1 = k.c1;
   d.c2 = k.c2;
-  d.eA = k.RT * k.two_over_G;
-  d.eB = k.c2 / k.RT;
-  d.eC = 1.0 / (3.0 * k.RT);
-  d.mG12 = -p.G / 12.0;
+  d.two_over_G = k.two_over_G;
+  d.mG = -p.G;
   d.inv_tau = 1.0 / p.tau;
-  double c_f = 0.0, Be = 0.0;
+  double Be = 0.0;
   switch (p.scheme) {
     case LBM_SCHEME_SHANCHEN:  // Eqs. (9)-(10): u_eq = u + tau F/rho, no forcing term
       d.c_eq = p.tau;
-      c_f = 0.0;
+      d.c_f = 0.0;
       d.sig = 0.0;
       Be = d.Ce = 0.0;
       break;
     case LBM_SCHEME_EDM:  // Eq. (11) = Eq. (16): B_e = C_e = 1, velocity u + F/(2 rho)
       d.c_eq = 0.0;
-      c_f = 0.5;
+      d.c_f = 0.5;
       d.sig = 0.0;
       Be = d.Ce = 1.0;
       break;
     case LBM_SCHEME_EDM_MODIFIED:  // Sec. III.C: EDM with C_e = 1/tau
       d.c_eq = 0.0;
-      c_f = 0.5;
+      d.c_f = 0.5;
       d.sig = 0.0;
       Be = 1.0;
       d.Ce = 1.0 / p.tau;
       break;
     case LBM_SCHEME_LADD:  // Table I: u in the equilibrium and in F_a, B_e = C_e = 1
       d.c_eq = 0.0;
-      c_f = 0.0;
+      d.c_f = 0.0;
       d.sig = 0.0;
       Be = d.Ce = 1.0;
       break;
     default:  // Eq. (31): u_eq = v, B_e = C_e = 1 - 1/(2 tau), v' = v + sigma F/((tau - 1/2) psi^2)
       d.c_eq = 0.5;
-      c_f = 0.5;
+      d.c_f = 0.5;
       d.sig = p.sigma / (p.tau - 0.5);
       Be = d.Ce = 1.0 - 0.5 / p.tau;
       break;
   }
-  d.c_d = c_f - d.c_eq;
-  d.om1 = 1.0 - d.inv_tau;
-  d.om1_2 = d.om1 / 2.0;
+  d.c_d = d.c_f - d.c_eq;
   d.om_2 = d.inv_tau / 2.0;
-  d.om_9 = d.inv_tau / 9.0;
   d.om_3 = d.inv_tau / 3.0;
   d.Be_3 = Be / 3.0;
+  d.wCe0 = 4.0 / 9.0 * d.Ce;
+  d.wCe1 = 1.0 / 9.0 * d.Ce;
+  d.wCe2 = 1.0 / 36.0 * d.Ce;
+  d.wBe3_1 = 3.0 / 9.0 * Be;
+  d.wBe3_2 = 3.0 / 36.0 * Be;
+  d.om_w0 = 4.0 / 9.0 * d.inv_tau;
+  d.om_w1 = 1.0 / 9.0 * d.inv_tau;
+  d.om_w2 = 1.0 / 36.0 * d.inv_tau;
+  d.om_3w1 = 3.0 / 9.0 * d.inv_tau;
+  d.om_3w2 = 3.0 / 36.0 * d.inv_tau;
+  d.om1 = 1.0 - d.inv_tau;
   d.rho_ref = rho_ref;
   d.run = run;
   d.mrt = 0;
