@@ -584,15 +584,17 @@ __device__ __forceinline__ double eval_psi(const typename Store<S>::R (&f)[9], c
   double r;
   const double psi = root_of(psi2, r);
   q.ip2 = inverse_of<R>(psi2, r);
+  // sigma = 0 does not use it, and psi^2 may then lie outside the range of FP32
+  if constexpr (std::is_same<R, float>::value) q.ip2 = d.sig != 0.0 ? q.ip2 : 0.0f;
   return psi;
 }
 
 // One node update: collision (BGK or MRT) of the pulled values f with the force
-// (Fx, Fy) (FP64), for FP32 storage with conserve(); true if the node is bad
-// (density or psi^2 not positive, or not a number).
+// (Fx, Fy) (FP64), for FP32 storage with conserve(); psi: the node's own.  True if the
+// node is bad (density or psi^2 not positive, or not a number).
 template <typename S, bool MRT>
-__device__ __forceinline__ bool update_node(typename Store<S>::R (&f)[9], const NodeQ<S>& q, double Fx,
-                                            double Fy, const RunDev& d) {
+__device__ __forceinline__ bool update_node(typename Store<S>::R (&f)[9], const NodeQ<S>& q, double psi,
+                                            double Fx, double Fy, const RunDev& d) {
   using R = typename Store<S>::R;
   const double rho = density<S>(q.drho, d);
   auto collision = [&](R jx, R jy) __attribute__((always_inline)) {
@@ -611,7 +613,7 @@ __device__ __forceinline__ bool update_node(typename Store<S>::R (&f)[9], const 
   } else {
     collision(mom_x(f), mom_y(f));
   }
-  return !(q.ip2 > 0) || !(rho > 0.0);
+  return !(psi > 0.0) || !(rho > 0.0);
 }
 
 // Force and collision of a node from the psi rows around it; true if it is bad.
@@ -621,7 +623,7 @@ __device__ __forceinline__ bool finish_node(typename Store<S>::R (&f)[9], const 
                                             const RunDev& d) {
   double Fx, Fy;
   force3x3(rs, rc, rn, i, d.mG, Fx, Fy);
-  return update_node<S, MRT>(f, q, Fx, Fy, d);
+  return update_node<S, MRT>(f, q, rc[i], Fx, Fy, d);
 }
 
 // One tile: columns [x0, x0+ncols), rows [y0, y0+nrows), nrows <= LMAX.

@@ -1,4 +1,5 @@
-"""The node arithmetic: FP16 lattices keep their populations bit for bit."""
+"""The node arithmetic: FP16 lattices keep their populations bit for bit, and psi^2 outside
+the range of FP32 is no divergence."""
 import hashlib
 import json
 import os
@@ -40,3 +41,34 @@ def test_fp16_states_keep_their_bits(L, case):
         assert lat.status()[0] == L.LBM_OK
         assert hashlib.sha256(lat.save_state()[56:]).hexdigest() == case["sha256"], tile
         lat.close()
+
+
+@pytest.mark.parametrize("scheme,mrt", [(0, False), (1, False), (2, False), (2, True), (4, False)])
+@pytest.mark.parametrize("prec", [1, 2])
+@pytest.mark.parametrize("power", [150, -150])
+def test_psi2_outside_fp32_range(L, prec, scheme, mrt, power):
+    # psi^2 = 2 (p - rho/3)/G: with G times 2^150 it is below the least FP32 number, with G
+    # times 2^-150 above the largest.  psi scales by 2^(-+75), and the force G psi grad psi and
+    # all that follows keep their bits; sigma = 0, so 1/psi^2 is not used
+    if mrt and prec == 2:
+        pytest.skip("MRT has FP64 and FP32 storage")
+    nx, ny = 96, 40
+    rho0 = slab_rho(nx, ny, CS, 0.9, seed=3)
+    gp, _ = pair(L, nx, ny, t=0.9, tau=0.9, scheme=scheme, sigma=0.0, precision=prec)
+
+    def run(G, tile):
+        gp.G = G
+        lat = L.Lattice(gp, rho0)
+        if mrt:
+            lat.set_mrt((1.3, 1.1, 1.2))
+        lat.set_tile(*tile)
+        lat.step(22)
+        st = lat.status()
+        raw = lat.save_state()[56:]
+        lat.close()
+        assert st == (L.LBM_OK, 22, -1), (tile, st)
+        return raw
+
+    want = run(-1.0, (2, 8, 1, 1))
+    for tile in [(2, 8, 1, 1), (4, 0, 1, 2), (4, 0, 1, 4), (1, 0, 1, 3)]:
+        assert run(-2.0 ** power, tile) == want, tile
