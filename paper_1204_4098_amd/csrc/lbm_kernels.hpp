@@ -1374,8 +1374,7 @@ __global__ __launch_bounds__(256) void k_fields(const typename Store<S>::E* __re
     const R drho = sum9(f);
     const R jx = mom_x(f), jy = mom_y(f);
     const double r = density<S>(drho, d);
-    double ir;
-    ring[j & 3][tid + 1] = root_of(psi2_of(r, d), ir);
+    ring[j & 3][tid + 1] = sqrt(psi2_of(r, d));  // 0 at an empty node, unlike root_of
     __syncthreads();
     if (j >= 2 && out) {
       double Fx, Fy;

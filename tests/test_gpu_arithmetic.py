@@ -1,12 +1,13 @@
 """The node arithmetic: FP16 lattices keep their populations bit for bit, and psi^2 outside
-the range of FP32 is no divergence."""
+the range of FP32 or 0 spoils nothing else."""
 import hashlib
 import json
 import os
 
+import numpy as np
 import pytest
 
-from tests.gpu_common import CS, PR, pair, slab_rho
+from tests.gpu_common import CS, PR, pair, slab_rho, temperature
 
 pytestmark = pytest.mark.gpu
 GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "fp16_states.json")
@@ -72,3 +73,33 @@ def test_psi2_outside_fp32_range(L, prec, scheme, mrt, power):
     want = run(-1.0, (2, 8, 1, 1))
     for tile in [(2, 8, 1, 1), (4, 0, 1, 2), (4, 0, 1, 4), (1, 0, 1, 3)]:
         assert run(-2.0 ** power, tile) == want, tile
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+@pytest.mark.parametrize("nx,ny", [(9, 7), (130, 45)])
+def test_fields_around_a_node_of_no_density(L, nx, ny, prec):
+    # psi of an empty node is 0 (psi^2 = 2 (p - rho/3)/G = 0): its neighbours have a force and
+    # a velocity.  Equilibrium at rest elsewhere, so v = F/(2 rho), F of psi(rho)
+    T, _ = temperature(0, 0.9)
+    gp, _ = pair(L, nx, ny, t=0.9, tau=0.9, scheme=2, sigma=0.1, precision=prec, rho_ref=0.0)
+    rho0 = np.full((ny, nx), 0.125)
+    lat = L.Lattice(gp, rho0)
+    w = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)[:, None, None]
+    f = w * rho0
+    f[:, 3, 4] = 0.0
+    lat.set_populations(np.ascontiguousarray(f), 0)
+    rho, vx, vy, p = lat.moments()
+    lat.close()
+    e = rho
+    psi = np.sqrt(-2 * (rho * T * (1 + e + e * e - e ** 3) / (1 - e) ** 3 - rho * rho - rho / 3))
+    assert rho[3, 4] == 0 and p[3, 4] == 0 and psi[3, 4] == 0
+    F = np.zeros((2, ny, nx))
+    for ex, ey in [(1, 0), (0, 1), (-1, 0), (0, -1), (1, 1), (-1, 1), (-1, -1), (1, -1)]:
+        n = np.roll(psi, (-ey, -ex), (0, 1)) * (1 / 3 if ex * ey == 0 else 1 / 12)
+        F[0] += ex * n
+        F[1] += ey * n
+    v = psi * F / (2 * np.where(rho > 0, rho, 1.0))
+    full = rho > 0
+    # FP64 sums of at most 8 numbers of 0.1, F and psi to 1e-15 each
+    assert np.abs(vx - v[0])[full].max() < 1e-14 and np.abs(vy - v[1])[full].max() < 1e-14
+    assert np.abs(v[:, 3, 3]).max() > 0.01
