@@ -431,8 +431,10 @@ hipError_t launch_batch_pipe_s(const Tile& t, const BatchArgs& a) {
   if (t.ts == 4)
     return t.nw == 2 ? launch_batch_k<S>(k_batch_pipe<S, 2, 4, MRT>, 512, a)
                      : launch_batch_k<S>(k_batch_pipe<S, NW, 4, MRT>, 256 * NW, a);
-  return t.nw == 2 ? launch_batch_k<S>(k_batch_pipe<S, 2, 2, MRT>, 256, a)
-                   : launch_batch_k<S>(k_batch_pipe<S, NW, 2, MRT>, 128 * NW, a);
+  if (t.ts == 2)
+    return t.nw == 2 ? launch_batch_k<S>(k_batch_pipe<S, 2, 2, MRT>, 256, a)
+                     : launch_batch_k<S>(k_batch_pipe<S, NW, 2, MRT>, 128 * NW, a);
+  return hipErrorInvalidValue;
 }
 
 // One launch of the batch tile: t.ts time steps of every active run;
@@ -564,8 +566,11 @@ Tile default_tile(int nx, int ny) {
   return t;
 }
 
+// Tuned tiles by size and kind, for the life of the process.  Lattices and batches have a
+// map each: their keys are of one type, and a tile of the one is not always one of the other.
+using TuneKey = std::tuple<int, int, int, int>;
 std::mutex g_tune_mu;
-std::map<std::tuple<int, int, int, int>, Tile> g_tune;
+std::map<TuneKey, Tile> g_tune, g_batch_tune;
 
 }  // namespace
 }  // namespace lbm
@@ -1344,7 +1349,7 @@ int batch_prepare_graphs(lbm_batch* b) {
   return LBM_OK;
 }
 
-std::tuple<int, int, int, int> batch_key(const lbm_batch* b) {
+TuneKey batch_key(const lbm_batch* b) {
   int64_t tot = 0;
   int maxnx = 0;
   for (int r = 0; r < b->nruns; ++r) {
@@ -1449,8 +1454,8 @@ int lbm_batch_init(int32_t n, const lbm_params* p, const double* const* rho0, vo
   Tile t{1, 16, 2};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tune.find(batch_key(b));
-    if (it != g_tune.end()) t = it->second;
+    auto it = g_batch_tune.find(batch_key(b));
+    if (it != g_batch_tune.end()) t = it->second;
   }
   st = batch_items(b, t);
   if (st != LBM_OK) {
@@ -1577,7 +1582,7 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
   if (st != LBM_OK) return st;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[batch_key(b)] = bt;
+    g_batch_tune[batch_key(b)] = bt;
   }
   st = batch_prepare_graphs(b);
   if (st != LBM_OK) return st;
