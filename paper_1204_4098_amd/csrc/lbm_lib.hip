@@ -345,16 +345,6 @@ hipError_t launch_pipe_s(const Tile& t, const void* src, void* dst, const RunDev
   return hipErrorInvalidValue;
 }
 
-// Steps of the next launch of tile t with `left` steps to go: the tile's, or what is
-// left (three only where that kernel exists: patches, FP64 arithmetic).  Rows of 2^32
-// bytes and more take single steps: the pipe addresses a row with 32-bit byte offsets.
-int next_ts(int prec, int nx, const Tile& t, int64_t left) {
-  int ts = (int)std::min<int64_t>(t.ts, left);
-  if (ts == 3 && t.nw != 1 && !has_step3(prec)) ts = 2;
-  if (ts > 1 && (int64_t)nx * esize_of(prec) >= (1ll << 32)) ts = 1;
-  return ts;
-}
-
 // One launch of the tile: t.ts time steps from src into dst.
 hipError_t launch_step(int prec, const Tile& t, const void* src, void* dst, const RunDev& d,
                        const unsigned long long* base, unsigned long long local,
@@ -566,11 +556,20 @@ Tile default_tile(int nx, int ny) {
   return t;
 }
 
-// Tuned tiles by size and kind, for the life of the process.  Lattices and batches have a
+// A tile and what runs the steps that it leaves over: rem[r - 1] is the launch with r steps
+// to go, r < t.ts (of r steps or fewer).
+struct Plan {
+  Tile t;
+  Tile rem[3];
+  const Tile& next(int64_t left) const { return left >= t.ts ? t : rem[left - 1]; }
+};
+
+// Tuned plans by size and kind, for the life of the process.  Lattices and batches have a
 // map each: their keys are of one type, and a tile of the one is not always one of the other.
 using TuneKey = std::tuple<int, int, int, int>;
 std::mutex g_tune_mu;
-std::map<TuneKey, Tile> g_tune, g_batch_tune;
+std::map<TuneKey, Plan> g_tune;
+std::map<TuneKey, Tile> g_batch_tune;
 
 }  // namespace
 }  // namespace lbm
@@ -595,10 +594,10 @@ struct lbm_ctx {
   unsigned long long* ctr;
   hipStream_t st;
   int64_t step;
-  Tile tile;
+  Plan plan;
   int graph_k;
   hipGraphExec_t gexec[2];
-  Tile gtile;
+  Plan gplan;
   int64_t captures;  // graphs captured so far
 };
 
@@ -641,10 +640,31 @@ Tile with_steps(Tile t, int ts) {
   return t;
 }
 
+// The plan of a tile that was not tuned: its own shape with fewer steps (three only where
+// that kernel exists: patches, FP64 arithmetic).
+Plan plan_of(int prec, const Tile& t) {
+  Plan p{t, {t, t, t}};
+  for (int r = 1; r < t.ts; ++r) p.rem[r - 1] = with_steps(t, r == 3 && t.nw != 1 && !has_step3(prec) ? 2 : r);
+  return p;
+}
+
+bool same_plan(const Plan& a, const Plan& b) {
+  bool same = same_tile(a.t, b.t);
+  for (int r = 1; same && r < a.t.ts; ++r) same = same_tile(a.rem[r - 1], b.rem[r - 1]);
+  return same;
+}
+
+// The next launch of a lattice with `left` steps to go.  Rows of 2^32 bytes and more take
+// single steps: the pipe addresses a row with 32-bit byte offsets.
+Tile next_launch(const lbm_ctx* c, int64_t left) {
+  const Tile& t = c->plan.next(left);
+  return t.ts > 1 && (int64_t)c->p.nx * c->esize >= (1ll << 32) ? with_steps(t, 1) : t;
+}
+
 // Launches that k steps take.
-int launches_of(int prec, int nx, const Tile& t, int k) {
+int launches_of(const lbm_ctx* c, int k) {
   int n = 0;
-  for (; k > 0; ++n) k -= next_ts(prec, nx, t, k);
+  for (; k > 0; ++n) k -= next_launch(c, k).ts;
   return n;
 }
 
@@ -672,10 +692,10 @@ int capture_graph(lbm_ctx* c, int parity) {
   HIPCHK(hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   for (int s = parity, done = 0; done < c->graph_k && e == hipSuccess; s ^= 1) {
-    const int ts = next_ts(c->p.precision, c->p.nx, c->tile, c->graph_k - done);
-    e = launch_step(c->p.precision, with_steps(c->tile, ts), c->buf[s], c->buf[s ^ 1], c->d, c->ctr,
-                    (unsigned long long)done, c->flag, c->st);
-    done += ts;
+    const Tile t = next_launch(c, c->graph_k - done);
+    e = launch_step(c->p.precision, t, c->buf[s], c->buf[s ^ 1], c->d, c->ctr, (unsigned long long)done,
+                    c->flag, c->st);
+    done += t.ts;
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_counter_add, dim3(1), dim3(1), 0, c->st, c->ctr,
@@ -692,7 +712,7 @@ int capture_graph(lbm_ctx* c, int parity) {
     c->gexec[parity] = nullptr;
     return LBM_EHIP;
   }
-  c->gtile = c->tile;
+  c->gplan = c->plan;
   ++c->captures;
   return LBM_OK;
 }
@@ -701,7 +721,7 @@ int capture_graph(lbm_ctx* c, int parity) {
 // parities now, so that no later lbm_step call pays for a capture.
 int prepare_graphs(lbm_ctx* c) {
   if (c->graph_k <= 0) return LBM_OK;
-  if (!same_tile(c->gtile, c->tile)) drop_graphs(c);
+  if (!same_plan(c->gplan, c->plan)) drop_graphs(c);
   for (int parity = 0; parity < 2; ++parity)
     if (!c->gexec[parity]) {
       int st = capture_graph(c, parity);
@@ -734,14 +754,32 @@ float time_launches(hipStream_t st, Launch&& launch, int reps) {
   return e == hipSuccess ? ms : -1.f;
 }
 
-// Pick the fastest tile per lattice step (tuning::pick_best); time_one(t)
-// returns ms per lattice step, negative on a HIP error, +inf to skip the tile.
-// Returns LBM_OK (best_tile unchanged if every tile was skipped) or LBM_EHIP.
+// Pick the fastest tile per lattice step (tuning::pick_best), and for fewer steps than it
+// takes the launches whose times add up to the least.  time_one(t) returns ms per lattice
+// step, negative on a HIP error, +inf to skip the tile.  Returns LBM_OK (plan unchanged if
+// every tile was skipped) or LBM_EHIP.
 template <class TimeOne>
-int pick_tile(const std::vector<Tile>& cand, TimeOne&& time_one, Tile& best_tile) {
-  const int k = tuning::pick_best((int)cand.size(), [&](int i) { return time_one(cand[i]); });
+int pick_plan(int prec, const std::vector<Tile>& cand, TimeOne&& time_one, Plan& plan) {
+  const int n = (int)cand.size();
+  std::vector<float> least(n, 1e30f);
+  const int k = tuning::pick_best(n, [&](int i) {
+    const float ms = time_one(cand[i]);
+    if (ms >= 0) least[i] = std::min(least[i], ms);
+    return ms;
+  });
   if (k == -2) return LBM_EHIP;
-  if (k >= 0) best_tile = cand[k];
+  if (k < 0) return LBM_OK;
+  plan = plan_of(prec, cand[k]);
+  float cost[4] = {};  // of r steps
+  for (int r = 1; r < plan.t.ts; ++r) {
+    cost[r] = 1e30f;
+    for (int i = 0; i < n; ++i) {
+      const int ts = cand[i].ts;
+      if (ts > r || least[i] >= 1e30f || least[i] * ts + cost[r - ts] >= cost[r]) continue;
+      cost[r] = least[i] * ts + cost[r - ts];
+      plan.rem[r - 1] = cand[i];
+    }
+  }
   return LBM_OK;
 }
 
@@ -818,11 +856,11 @@ int lbm_init(const lbm_params* p, const double* rho0, const double* ux0, const d
   c->flag = reinterpret_cast<unsigned long long*>(c->ws + 2 * pop + aux + parts);
   c->ctr = c->flag + 1;
   c->st = static_cast<hipStream_t>(stream);
-  c->tile = default_tile(p->nx, p->ny);
+  c->plan = plan_of(p->precision, default_tile(p->nx, p->ny));
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find({p->nx, p->ny, p->precision, 0});
-    if (it != g_tune.end()) c->tile = it->second;
+    if (it != g_tune.end()) c->plan = it->second;
   }
   // the second buffer is written only at lattice nodes: clear its row padding once
   // so that checkpoints of either buffer are deterministic
@@ -845,7 +883,7 @@ int lbm_step(lbm_ctx* c, int64_t n) {
   if (!c || n < 0) return LBM_EINVAL;
   int64_t done = 0;
   if (c->graph_k > 0 && n >= c->graph_k) {
-    if (!same_tile(c->gtile, c->tile)) drop_graphs(c);
+    if (!same_plan(c->gplan, c->plan)) drop_graphs(c);
     hipLaunchKernelGGL(k_counter_set, dim3(1), dim3(1), 0, c->st, c->ctr, (unsigned long long)c->step);
     HIPCHK(hipGetLastError());
     while (n - done >= c->graph_k) {
@@ -856,12 +894,12 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       HIPCHK(hipGraphLaunch(c->gexec[c->cur], c->st));
       done += c->graph_k;
       c->step += c->graph_k;
-      c->cur ^= launches_of(c->p.precision, c->p.nx, c->tile, c->graph_k) & 1;  // a buffer swap each
+      c->cur ^= launches_of(c, c->graph_k) & 1;  // a buffer swap each
     }
   }
   while (done < n) {
     const int s = c->cur;
-    const Tile t = with_steps(c->tile, next_ts(c->p.precision, c->p.nx, c->tile, n - done));
+    const Tile t = next_launch(c, n - done);
     HIPCHK(launch_step(c->p.precision, t, c->buf[s], c->buf[s ^ 1], c->d, nullptr,
                        (unsigned long long)c->step, c->flag, c->st));
     c->cur ^= 1;
@@ -1049,49 +1087,56 @@ int lbm_set_tile(lbm_ctx* c, int32_t nw, int32_t L, int32_t depth, int32_t steps
   if (!c || !valid_tile(nw, L, depth, 16, steps)) return LBM_EINVAL;
   if (steps == 3 && nw != 1 && !has_step3(c->p.precision)) return LBM_ENOTSUP;
   if (steps == 3 && nw != 1 && (c->p.nx < 5 || c->p.ny < 5)) return LBM_EINVAL;
-  c->tile = Tile{nw, L, depth, steps};
+  c->plan = plan_of(c->p.precision, Tile{nw, L, depth, steps});
   return prepare_graphs(c);
 }
 
 int lbm_get_tile(lbm_ctx* c, int32_t* nw, int32_t* L, int32_t* depth, int32_t* steps) {
   if (!c) return LBM_EINVAL;
-  if (nw) *nw = c->tile.nw;
-  if (L) *L = c->tile.L;
-  if (depth) *depth = c->tile.pf;
-  if (steps) *steps = c->tile.ts;
+  if (nw) *nw = c->plan.t.nw;
+  if (L) *L = c->plan.t.L;
+  if (depth) *depth = c->plan.t.pf;
+  if (steps) *steps = c->plan.t.ts;
   return LBM_OK;
 }
 
 int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, int32_t* steps_out) {
   if (!c) return LBM_EINVAL;
-  Tile bt = c->tile;
+  Plan best = c->plan;
   const int s = c->cur;
   const int64_t nodes = (int64_t)c->p.nx * c->p.ny;
   const int reps = nodes >= (1 << 22) ? 3 : 10;
   std::vector<Tile> cand;
   // Tuning is most of the time it takes to set a lattice up, so of each family only the
-  // likeliest are timed.  One step per launch has lost to the multi-step kernels by 1.4
-  // times and more on every size measured (64 x 32 to 4096 x 4096); one-wave strips are
-  // there for narrow lattices.  Patches win below 2^16 nodes by 1.8 times and more and lose
-  // above 2^18.
-  const bool tiny = nodes < (1 << 16);
+  // likeliest are timed.  Patches win below 2^16 nodes by 1.8 times and more and lose
+  // above 2^18.  Single steps win on narrow lattices only, but are what a program takes that
+  // reads its lattice after every step: below 2^21 nodes strips of 1, 4 and 16 waves in chunks
+  // of about nodes / 2^17 rows (the fastest of all had 1 row below 2^17 nodes, 2 to 4 up to
+  // 2^20), above that the balanced ones.
+  const bool tiny = nodes < (1 << 16), large = nodes >= (1 << 21);
   if (nodes <= (1 << 18))
     for (int ts : {2, 3, 4}) cand.push_back(Tile{1, 0, 1, ts});
-  if (tiny) {
-    for (int L : {1, 2, 4, 8})
-      if (L <= 2 * c->p.ny) cand.push_back(Tile{1, L, 1, 1});
+  if (!large) {
+    int rows = 1;
+    while (rows < 16 && 2 * rows <= (nodes >> 17)) rows *= 2;
+    for (int nw : {1, 4, 16})
+      for (int L : {rows, 2 * rows})
+        if (nw == 1 || 32 * nw < c->p.nx) cand.push_back(Tile{nw, L, 1, 1});
   } else {
-    for (const Tile& t : {Tile{1, 0, 2, 1}, Tile{1, 64, 2, 1}, Tile{4, 0, 2, 1}, Tile{4, 8, 2, 1}, Tile{16, 0, 1, 1}})
+    for (const Tile& t : {Tile{1, 0, 2, 1}, Tile{1, 64, 2, 1}, Tile{4, 8, 2, 1}, Tile{16, 0, 1, 1}})
       if (t.L <= 2 * c->p.ny) cand.push_back(t);
   }
-  for (int L : {0, 16, 32, 64, 128})
-    if (L <= 2 * c->p.ny)
-      for (const Tile& t : {Tile{4, L, 1, 4}, Tile{2, L, 1, 4}, Tile{4, L, 1, 2}})
-        if (next_ts(c->p.precision, c->p.nx, t, t.ts) == t.ts && (t.ts == 4 || L == 0 || L == 32) &&
-            (!tiny || L == 16))
-          cand.push_back(t);
-  const int pst = pick_tile(
-      cand,
+  if (!tiny) cand.push_back(Tile{4, 0, 2, 1});
+  if ((int64_t)c->p.nx * c->esize < (1ll << 32))
+    for (int L : {0, 16, 32, 64, 128})
+      if (L <= 2 * c->p.ny && (!tiny || L == 16)) {
+        cand.push_back(Tile{4, L, 1, 4});
+        cand.push_back(Tile{2, L, 1, 4});
+        if (L == 0 || L == 32) cand.push_back(Tile{4, L, 1, 2});
+        if (L == 0 && has_step3(c->p.precision) && std::min(c->p.nx, c->p.ny) >= 5) cand.push_back(Tile{4, 0, 1, 3});
+      }
+  const int pst = pick_plan(
+      c->p.precision, cand,
       [&](const Tile& t) {
         const float ms = time_launches(
             c->st,
@@ -1102,19 +1147,19 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
             reps);
         return ms < 0 ? ms : ms / t.ts;  // time per lattice step
       },
-      bt);
+      best);
   if (pst != LBM_OK) return pst;
-  c->tile = bt;
+  c->plan = best;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[{c->p.nx, c->p.ny, c->p.precision, c->d.mrt}] = bt;
+    g_tune[{c->p.nx, c->p.ny, c->p.precision, c->d.mrt}] = best;
   }
   const int gst = prepare_graphs(c);
   if (gst != LBM_OK) return gst;
-  if (nw_out) *nw_out = bt.nw;
-  if (L_out) *L_out = bt.L;
-  if (depth_out) *depth_out = bt.pf;
-  if (steps_out) *steps_out = bt.ts;
+  if (nw_out) *nw_out = best.t.nw;
+  if (L_out) *L_out = best.t.L;
+  if (depth_out) *depth_out = best.t.pf;
+  if (steps_out) *steps_out = best.t.ts;
   return LBM_OK;
 }
 
@@ -1550,7 +1595,7 @@ int lbm_batch_graph_captures(lbm_batch* b, int64_t* n) {
 int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth_out,
                    int32_t* steps_out) {
   if (!b) return LBM_EINVAL;
-  Tile bt = b->tile;
+  Plan best{b->tile, {}};
   const int s = b->cur;
   // as in lbm_tune, only the likeliest of each family
   std::vector<Tile> cand;
@@ -1560,8 +1605,8 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
     for (int ts : {2, 4})
       for (int L : {0, 16, 32, 64}) cand.push_back(Tile{nw, L, 1, ts});  // 64: whole runs of a sweep
   int ist = LBM_OK;
-  const int pst = pick_tile(
-      cand,
+  const int pst = pick_plan(
+      b->prec, cand,
       [&](const Tile& t) {
         ist = batch_items(b, t);
         if (ist == LBM_ENOSPACE) return 1e30f;  // too many items for the work list: skipped
@@ -1575,7 +1620,8 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
             5);
         return ms < 0 ? ms : ms / t.ts;  // time per lattice step
       },
-      bt);
+      best);
+  const Tile bt = best.t;
   if (pst != LBM_OK) return ist != LBM_OK && ist != LBM_ENOSPACE ? ist : pst;
   batch_drop_graphs(b);
   int st = batch_items(b, bt);

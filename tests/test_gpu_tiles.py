@@ -37,3 +37,54 @@ def test_batch_takes_no_tile_of_a_lattice(L, prec):
         lat.step(n)
     assert np.array_equal(b.get_populations(0), lat.get_populations()[0])
     b.close(); lat.close()
+
+
+def _us(lat, n, reps=60):
+    """Shortest of several means, so that a clock or a neighbour does not decide."""
+    import torch
+    best = float("inf")
+    for _ in range(5):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record(lat.stream)
+        for _ in range(reps):
+            lat.step(n)
+        e[1].record(lat.stream)
+        e[1].synchronize()
+        best = min(best, e[0].elapsed_time(e[1]) * 1e3 / reps)
+    return best
+
+
+@pytest.mark.parametrize("nx,ny,prec", [(64, 8192, 0), (100, 3000, 3), (24, 4096, 0)])
+def test_tuned_single_steps_cost_what_a_tile_of_one_step_does(L, nx, ny, prec):
+    # a program that reads its lattice after each step: the tuned tile takes several steps
+    # per launch, and with its strips of several waves one step took 1.5 to 2.4 times as long
+    # as strips of one wave
+    gp, _ = pair(L, nx, ny, t=0.85, tau=0.8, scheme=2, sigma=0.1, precision=prec)
+    lat = L.Lattice(gp, slab_rho(nx, ny, CS, 0.85, seed=3))
+    lat.tune()
+    tuned = _us(lat, 1)
+    lat.set_tile(1, 4 if ny > 5000 else 2, 1, 1)
+    one = _us(lat, 1)
+    lat.close()
+    assert tuned < 1.3 * one, (tuned, one)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+@pytest.mark.parametrize("nx,ny", [(64, 32), (300, 200), (90, 3000)])
+def test_tuned_steps_of_any_number_are_single_steps(L, nx, ny, prec):
+    # whatever the tuner puts in for the steps left over, eager and in graphs
+    gp, _ = pair(L, nx, ny, t=0.85, tau=0.8, scheme=2, sigma=0.1, precision=prec)
+    rho0 = slab_rho(nx, ny, CS, 0.85, seed=4)
+    a, b = L.Lattice(gp, rho0), L.Lattice(gp, rho0)
+    a.set_tile(2, 8, 1, 1)
+    b.tune()
+    for graph, n in [(0, 1), (0, 2), (0, 3), (0, 7), (6, 25), (10, 33), (2, 5), (0, 5)]:
+        b.set_graph_steps(graph)
+        a.step(n)
+        b.step(n)
+        assert np.array_equal(a.get_populations()[0], b.get_populations()[0]), (graph, n)
+    b.tune()                                      # other remainders perhaps, the same states
+    a.step(11)
+    b.step(11)
+    assert np.array_equal(a.get_populations()[0], b.get_populations()[0])
+    a.close(); b.close()
