@@ -162,6 +162,21 @@ inline void walk(std::vector<Item>& items, int nblocks) {
   items.swap(out);
 }
 
+// Puts the first item of each block (of a list that was dealt or walked) before the list,
+// with its place as row0, and an end: nblocks + 1 entries.  A block without items has its
+// successor's place.
+inline void add_heads(std::vector<Item>& items, int nblocks) {
+  const int n = (int)items.size();
+  std::vector<Item> out(nblocks + 1, Item{0, 0, 0, 0, 0, n});
+  for (int b = 0; b < nblocks; ++b) {
+    const int first = items[b].row0;
+    if (first < n) out[b] = items[first];
+    out[b].row0 = first;
+  }
+  out.insert(out.end(), items.begin(), items.end());
+  items.swap(out);
+}
+
 }  // namespace layout
 
 namespace tuning {

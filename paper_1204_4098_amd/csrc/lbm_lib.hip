@@ -385,8 +385,9 @@ struct BatchArgs {
 
 // Grid of a batch schedule with `resident` blocks of its kernel: item lists take at most
 // one block per item; the balanced schedule (total > 0 rows) at least 8 rows per block.
+constexpr int kMaxBatchGrid = 8192;  // 256 CUs of 32 waves
 int batch_grid(int resident, int nitems, int total) {
-  return std::max(1, std::min(resident, total > 0 ? total / 8 : nitems));
+  return std::max(1, std::min(std::min(resident, kMaxBatchGrid), total > 0 ? total / 8 : nitems));
 }
 
 template <typename S, class Kernel>
@@ -568,8 +569,7 @@ struct Plan {
 // map each: their keys are of one type, and a tile of the one is not always one of the other.
 using TuneKey = std::tuple<int, int, int, int>;
 std::mutex g_tune_mu;
-std::map<TuneKey, Plan> g_tune;
-std::map<TuneKey, Tile> g_batch_tune;
+std::map<TuneKey, Plan> g_tune, g_batch_tune;
 
 }  // namespace
 }  // namespace lbm
@@ -641,10 +641,11 @@ Tile with_steps(Tile t, int ts) {
 }
 
 // The plan of a tile that was not tuned: its own shape with fewer steps (three only where
-// that kernel exists: patches, FP64 arithmetic).
-Plan plan_of(int prec, const Tile& t) {
+// that kernel exists: single lattices' patches and FP64 arithmetic).
+Plan plan_of(int prec, const Tile& t, bool batch = false) {
   Plan p{t, {t, t, t}};
-  for (int r = 1; r < t.ts; ++r) p.rem[r - 1] = with_steps(t, r == 3 && t.nw != 1 && !has_step3(prec) ? 2 : r);
+  const bool three = !batch && (t.nw == 1 || has_step3(prec));
+  for (int r = 1; r < t.ts; ++r) p.rem[r - 1] = with_steps(t, r == 3 && !three ? 2 : r);
   return p;
 }
 
@@ -759,7 +760,7 @@ float time_launches(hipStream_t st, Launch&& launch, int reps) {
 // step, negative on a HIP error, +inf to skip the tile.  Returns LBM_OK (plan unchanged if
 // every tile was skipped) or LBM_EHIP.
 template <class TimeOne>
-int pick_plan(int prec, const std::vector<Tile>& cand, TimeOne&& time_one, Plan& plan) {
+int pick_plan(int prec, bool batch, const std::vector<Tile>& cand, TimeOne&& time_one, Plan& plan) {
   const int n = (int)cand.size();
   std::vector<float> least(n, 1e30f);
   const int k = tuning::pick_best(n, [&](int i) {
@@ -769,7 +770,7 @@ int pick_plan(int prec, const std::vector<Tile>& cand, TimeOne&& time_one, Plan&
   });
   if (k == -2) return LBM_EHIP;
   if (k < 0) return LBM_OK;
-  plan = plan_of(prec, cand[k]);
+  plan = plan_of(prec, cand[k], batch);
   float cost[4] = {};  // of r steps
   for (int r = 1; r < plan.t.ts; ++r) {
     cost[r] = 1e30f;
@@ -1136,7 +1137,7 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
         if (L == 0 && has_step3(c->p.precision) && std::min(c->p.nx, c->p.ny) >= 5) cand.push_back(Tile{4, 0, 1, 3});
       }
   const int pst = pick_plan(
-      c->p.precision, cand,
+      c->p.precision, false, cand,
       [&](const Tile& t) {
         const float ms = time_launches(
             c->st,
@@ -1238,6 +1239,14 @@ int lbm_destroy(lbm_ctx* c) {
 // Batch of independent lattices.
 // ============================================================================
 
+// The work list of one tile on the device: in item lists the blocks' first items (grid + 1
+// entries), then all items.
+struct WorkList {
+  Item* d;
+  int nitems, total;  // total: rows of the balanced schedule (0 for item lists)
+  int grid;           // blocks the list was dealt to, or of the balanced schedule
+};
+
 struct lbm_batch {
   int nruns;
   int prec, esize;
@@ -1250,20 +1259,18 @@ struct lbm_batch {
   void* buf[2];
   int cur;
   RunDev* d_runs;
-  Item* d_items;
-  int nitems, items_cap;
-  int total_rows;  // balanced schedule: rows of all strip items (0 for item lists)
-  int grid;        // blocks the work list was dealt to, or of the balanced schedule
+  WorkList list[3];  // of the tile, and of two and one step left over
+  int items_cap;     // items of a list, without its blocks' first ones
   unsigned long long* flags;
   unsigned long long* ctr;
   double* aux;
   size_t aux_nodes;
   hipStream_t st;
   int64_t step;
-  Tile tile;
+  Plan plan;
   int graph_k;
   hipGraphExec_t gexec[2];
-  Tile gtile;
+  Plan gplan;
   int64_t captures;  // graphs captured so far
   double* coex;      // 2 * nruns doubles: (rho_l, rho_g) per run
   int mrt;           // 1: every run's descriptor carries the MRT collision
@@ -1274,6 +1281,7 @@ namespace {
 struct BatchLayout {
   size_t pool, runs, items, flags, aux, coex, total;
   int items_cap;
+  size_t list_entries;  // of one of the three lists
   size_t aux_nodes;
 };
 
@@ -1292,7 +1300,8 @@ BatchLayout batch_layout(int n, const lbm_params* p) {
   L.pool = align_up(elems * es);
   L.runs = align_up(n * sizeof(RunDev));
   L.items_cap = cap;
-  L.items = align_up((size_t)cap * sizeof(Item));
+  L.list_entries = (size_t)cap + std::min(cap, kMaxBatchGrid) + 1;
+  L.items = align_up(3 * L.list_entries * sizeof(Item));
   L.flags = align_up((n + 1) * sizeof(unsigned long long));
   L.aux_nodes = maxn;
   L.aux = align_up(5 * maxn * sizeof(double));
@@ -1301,16 +1310,16 @@ BatchLayout batch_layout(int n, const lbm_params* p) {
   return L;
 }
 
-// A launch from buffer s into the other.
-BatchArgs batch_args(const lbm_batch* b, int s, const unsigned long long* base, unsigned long long local) {
-  return BatchArgs{b->buf[s], b->buf[s ^ 1], b->d_runs, b->d_items, b->nitems, b->total_rows,
-                   b->grid,   base,          local,     b->flags,   b->st,     nullptr};
+// A launch of list l from buffer s into the other.
+BatchArgs batch_args(const lbm_batch* b, const WorkList& l, int s, const unsigned long long* base,
+                     unsigned long long local) {
+  return BatchArgs{b->buf[s], b->buf[s ^ 1], b->d_runs, l.d, l.nitems, l.total,
+                   l.grid,    base,          local,     b->flags, b->st, nullptr};
 }
 
-// Work list of a tile (layout::build_items, dealt to its grid or walked), uploaded to the
-// device.
-int batch_items(lbm_batch* b, const Tile& t) {
-  std::vector<Item> items;
+// Work list of a tile (layout::build_items, dealt to its kernel's grid or walked) into l and
+// items; nothing on the device changes.
+int make_list(const lbm_batch* b, const Tile& t, WorkList& l, std::vector<Item>& items) {
   std::vector<int> nx(b->nruns), ny(b->nruns);
   for (int r = 0; r < b->nruns; ++r) {
     nx[r] = b->p[r].nx;
@@ -1328,15 +1337,43 @@ int batch_items(lbm_batch* b, const Tile& t) {
   BatchArgs q{};
   q.resident = &resident;
   HIPCHK(launch_batch(b->prec, b->mrt != 0, t, q));
-  b->total_rows = t.L > 0 ? 0 : (int)rows;
-  b->grid = batch_grid(resident, (int)items.size(), b->total_rows);
-  if (t.ts == 1 && t.L > 0 && t.L < layout::kWalkRows) layout::walk(items, b->grid);
-  else if (t.L > 0) layout::deal(items, b->grid, t.ts > 1 ? pipe_fill(t.ts) : kStepFill);
-  HIPCHK(hipMemcpyAsync(b->d_items, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, b->st));
-  HIPCHK(hipStreamSynchronize(b->st));
-  b->nitems = (int)items.size();
-  b->tile = t;
+  l.nitems = (int)items.size();
+  l.total = t.L > 0 ? 0 : (int)rows;
+  l.grid = batch_grid(resident, l.nitems, l.total);
+  if (t.ts == 1 && t.L > 0 && t.L < layout::kWalkRows) layout::walk(items, l.grid);
+  else if (t.L > 0) layout::deal(items, l.grid, t.ts > 1 ? pipe_fill(t.ts) : kStepFill);
+  if (t.L > 0) layout::add_heads(items, l.grid);
   return LBM_OK;
+}
+
+int upload_list(lbm_batch* b, const WorkList& l, const std::vector<Item>& items) {
+  HIPCHK(hipMemcpyAsync(l.d, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, b->st));
+  HIPCHK(hipStreamSynchronize(b->st));
+  return LBM_OK;
+}
+
+// The lists of a plan: every launch has one dealt to the blocks that its own kernel keeps
+// resident.  (With the tile's list and grid, one block per CU for four FP64 steps, single
+// steps of a sweep of 256 runs took 111 us in FP64 and 53 in FP32; so 66 and 27.)
+int batch_plan(lbm_batch* b, const Plan& p) {
+  WorkList l[3] = {b->list[0], b->list[1], b->list[2]};
+  std::vector<Item> items[3];
+  int st = make_list(b, p.t, l[0], items[0]);
+  for (int r = 1; r < p.t.ts && st == LBM_OK; ++r) {
+    const Tile& t = p.rem[r - 1];
+    if (items[3 - t.ts].empty()) st = make_list(b, t, l[3 - t.ts], items[3 - t.ts]);
+  }
+  for (int i = 0; i < 3 && st == LBM_OK; ++i)
+    if (!items[i].empty()) st = upload_list(b, b->list[i] = l[i], items[i]);
+  if (st == LBM_OK) b->plan = p;
+  return st;
+}
+
+// The next launch with `left` steps to go, and its list.
+Tile batch_next(const lbm_batch* b, int64_t left, const WorkList** l) {
+  const Tile& t = b->plan.next(left);
+  *l = &b->list[left >= b->plan.t.ts ? 0 : 3 - t.ts];
+  return t;
 }
 
 void batch_drop_graphs(lbm_batch* b) {
@@ -1347,21 +1384,15 @@ void batch_drop_graphs(lbm_batch* b) {
     }
 }
 
-// Steps of the next launch with `left` steps to go: the tile's, or fewer at the end
-// (the items of a tile suit every kernel of fewer steps: their strips are no wider).
-int batch_next_ts(const Tile& t, int64_t left) {
-  return left >= t.ts ? t.ts : left >= 2 ? 2 : 1;
-}
-
 int batch_capture(lbm_batch* b, int parity) {
   hipGraph_t g;
   HIPCHK(hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   for (int s = parity, done = 0; done < b->graph_k && e == hipSuccess; s ^= 1) {
-    const int ts = batch_next_ts(b->tile, b->graph_k - done);
-    e = launch_batch(b->prec, b->mrt != 0, with_steps(b->tile, ts),
-                     batch_args(b, s, b->ctr, (unsigned long long)done));
-    done += ts;
+    const WorkList* l;
+    const Tile t = batch_next(b, b->graph_k - done, &l);
+    e = launch_batch(b->prec, b->mrt != 0, t, batch_args(b, *l, s, b->ctr, (unsigned long long)done));
+    done += t.ts;
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_counter_add, dim3(1), dim3(1), 0, b->st, b->ctr, (unsigned long long)b->graph_k);
@@ -1377,14 +1408,14 @@ int batch_capture(lbm_batch* b, int parity) {
     b->gexec[parity] = nullptr;
     return LBM_EHIP;
   }
-  b->gtile = b->tile;
+  b->gplan = b->plan;
   ++b->captures;
   return LBM_OK;
 }
 
 int batch_prepare_graphs(lbm_batch* b) {
   if (b->graph_k <= 0) return LBM_OK;
-  if (!same_tile(b->gtile, b->tile)) batch_drop_graphs(b);
+  if (!same_plan(b->gplan, b->plan)) batch_drop_graphs(b);
   for (int parity = 0; parity < 2; ++parity)
     if (!b->gexec[parity]) {
       int st = batch_capture(b, parity);
@@ -1442,7 +1473,8 @@ int lbm_batch_init(int32_t n, const lbm_params* p, const double* const* rho0, vo
   b->buf[0] = b->ws;
   b->buf[1] = b->ws + Lay.pool;
   b->d_runs = reinterpret_cast<RunDev*>(b->ws + 2 * Lay.pool);
-  b->d_items = reinterpret_cast<Item*>(b->ws + 2 * Lay.pool + Lay.runs);
+  for (int i = 0; i < 3; ++i)
+    b->list[i].d = reinterpret_cast<Item*>(b->ws + 2 * Lay.pool + Lay.runs) + i * Lay.list_entries;
   b->items_cap = Lay.items_cap;
   b->flags = reinterpret_cast<unsigned long long*>(b->ws + 2 * Lay.pool + Lay.runs + Lay.items);
   b->ctr = b->flags + n;
@@ -1496,13 +1528,13 @@ int lbm_batch_init(int32_t n, const lbm_params* p, const double* const* rho0, vo
     delete b;
     return LBM_EHIP;
   }
-  Tile t{1, 16, 2};
+  Plan plan = plan_of(b->prec, Tile{1, 16, 2}, true);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_batch_tune.find(batch_key(b));
-    if (it != g_batch_tune.end()) t = it->second;
+    if (it != g_batch_tune.end()) plan = it->second;
   }
-  st = batch_items(b, t);
+  st = batch_plan(b, plan);
   if (st != LBM_OK) {
     delete b;
     return st;
@@ -1515,7 +1547,7 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
   if (!b || n < 0) return LBM_EINVAL;
   int64_t done = 0;
   if (b->graph_k > 0 && n >= b->graph_k) {
-    if (!same_tile(b->gtile, b->tile)) batch_drop_graphs(b);
+    if (!same_plan(b->gplan, b->plan)) batch_drop_graphs(b);
     hipLaunchKernelGGL(k_counter_set, dim3(1), dim3(1), 0, b->st, b->ctr, (unsigned long long)b->step);
     HIPCHK(hipGetLastError());
     while (n - done >= b->graph_k) {
@@ -1526,13 +1558,14 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
       HIPCHK(hipGraphLaunch(b->gexec[b->cur], b->st));
       done += b->graph_k;
       b->step += b->graph_k;
-      for (int k = b->graph_k; k > 0; k -= batch_next_ts(b->tile, k)) b->cur ^= 1;  // a swap per launch
+      for (int k = b->graph_k; k > 0; b->cur ^= 1) k -= b->plan.next(k).ts;  // a swap per launch
     }
   }
   while (done < n) {
     const int s = b->cur;
-    const Tile t = with_steps(b->tile, batch_next_ts(b->tile, n - done));
-    HIPCHK(launch_batch(b->prec, b->mrt != 0, t, batch_args(b, s, nullptr, (unsigned long long)b->step)));
+    const WorkList* l;
+    const Tile t = batch_next(b, n - done, &l);
+    HIPCHK(launch_batch(b->prec, b->mrt != 0, t, batch_args(b, *l, s, nullptr, (unsigned long long)b->step)));
     b->cur ^= 1;
     b->step += t.ts;
     done += t.ts;
@@ -1543,16 +1576,16 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
 int lbm_batch_set_tile(lbm_batch* b, int32_t nw, int32_t L, int32_t depth, int32_t steps) {
   if (!b || !valid_tile(nw, L, depth, 8, steps, true) || (L > 0 && L < 4)) return LBM_EINVAL;
   batch_drop_graphs(b);
-  const int st = batch_items(b, Tile{nw, L, depth, steps});
+  const int st = batch_plan(b, plan_of(b->prec, Tile{nw, L, depth, steps}, true));
   return st != LBM_OK ? st : batch_prepare_graphs(b);
 }
 
 int lbm_batch_get_tile(lbm_batch* b, int32_t* nw, int32_t* L, int32_t* depth, int32_t* steps) {
   if (!b) return LBM_EINVAL;
-  if (steps) *steps = b->tile.ts;
-  if (nw) *nw = b->tile.nw;
-  if (L) *L = b->tile.L;
-  if (depth) *depth = b->tile.pf;
+  if (steps) *steps = b->plan.t.ts;
+  if (nw) *nw = b->plan.t.nw;
+  if (L) *L = b->plan.t.L;
+  if (depth) *depth = b->plan.t.pf;
   return LBM_OK;
 }
 
@@ -1583,7 +1616,8 @@ int lbm_batch_set_mrt(lbm_batch* b, const double* rates) {
   HIPCHK(hipStreamSynchronize(b->st));
   b->mrt = rates ? 1 : 0;
   batch_drop_graphs(b);  // the captured launches are of the other kernels
-  return batch_prepare_graphs(b);
+  const int st = batch_plan(b, b->plan);  // and so are the blocks that the lists were dealt to
+  return st != LBM_OK ? st : batch_prepare_graphs(b);
 }
 
 int lbm_batch_graph_captures(lbm_batch* b, int64_t* n) {
@@ -1595,47 +1629,51 @@ int lbm_batch_graph_captures(lbm_batch* b, int64_t* n) {
 int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth_out,
                    int32_t* steps_out) {
   if (!b) return LBM_EINVAL;
-  Plan best{b->tile, {}};
+  Plan best = b->plan;
   const int s = b->cur;
   // as in lbm_tune, only the likeliest of each family
   std::vector<Tile> cand;
   for (int nw : {1, 2, 4})
-    for (int L : {0, 8, 16}) cand.push_back(Tile{nw, L, 2, 1});
+    for (int L : {0, 4, 8, 16}) cand.push_back(Tile{nw, L, L == 4 ? 1 : 2, 1});
   for (int nw : {2, 4})
     for (int ts : {2, 4})
       for (int L : {0, 16, 32, 64}) cand.push_back(Tile{nw, L, 1, ts});  // 64: whole runs of a sweep
   int ist = LBM_OK;
   const int pst = pick_plan(
-      b->prec, cand,
+      b->prec, true, cand,
       [&](const Tile& t) {
-        ist = batch_items(b, t);
+        std::vector<Item> items;
+        ist = make_list(b, t, b->list[0], items);
         if (ist == LBM_ENOSPACE) return 1e30f;  // too many items for the work list: skipped
+        if (ist == LBM_OK) ist = upload_list(b, b->list[0], items);
         if (ist != LBM_OK) return -1.f;
         const float ms = time_launches(
             b->st,
             [&] {
               return launch_batch(b->prec, b->mrt != 0, t,
-                                  batch_args(b, s, nullptr, (unsigned long long)b->step));
+                                  batch_args(b, b->list[0], s, nullptr, (unsigned long long)b->step));
             },
             5);
         return ms < 0 ? ms : ms / t.ts;  // time per lattice step
       },
       best);
-  const Tile bt = best.t;
-  if (pst != LBM_OK) return ist != LBM_OK && ist != LBM_ENOSPACE ? ist : pst;
+  if (pst != LBM_OK) {
+    (void)batch_plan(b, b->plan);  // the tile's own list again
+    return ist != LBM_OK && ist != LBM_ENOSPACE ? ist : pst;
+  }
   batch_drop_graphs(b);
-  int st = batch_items(b, bt);
+  int st = batch_plan(b, best);
   if (st != LBM_OK) return st;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_batch_tune[batch_key(b)] = bt;
+    g_batch_tune[batch_key(b)] = best;
   }
   st = batch_prepare_graphs(b);
   if (st != LBM_OK) return st;
-  if (nw_out) *nw_out = bt.nw;
-  if (L_out) *L_out = bt.L;
-  if (depth_out) *depth_out = bt.pf;
-  if (steps_out) *steps_out = bt.ts;
+  if (nw_out) *nw_out = best.t.nw;
+  if (L_out) *L_out = best.t.L;
+  if (depth_out) *depth_out = best.t.pf;
+  if (steps_out) *steps_out = best.t.ts;
   return LBM_OK;
 }
 

@@ -88,3 +88,51 @@ def test_tuned_steps_of_any_number_are_single_steps(L, nx, ny, prec):
     b.step(11)
     assert np.array_equal(a.get_populations()[0], b.get_populations()[0])
     a.close(); b.close()
+
+
+def _sweep(L, prec, n=256):
+    import synth
+    from paper_1204_4098_amd import surrogate
+    runs = synth.sweep_runs(n, seed=5, lx=(64, 256, 32), ly=(16, 64, 16), t_range=(0.7, 0.95),
+                            sigma_range=(0.05, 0.15))
+    return surrogate.slab_runs(runs, prec, seed=5, rho_ref=0.0)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_steps_left_over_by_a_batch_tile_have_their_own_blocks(L, prec):
+    # one step of a four-step tile (FP64: one block per CU) against a tile of one step with
+    # strips of the same class; with the four-step list and its blocks it took 1.7 to 2.5 times
+    # as long
+    ps, rhos = _sweep(L, prec)
+    b = L.Batch(ps, rhos)
+    b.set_tile(2, 0, 1, 1)
+    one = _us(b, 1, reps=30)
+    b.set_tile(2, 0, 1, 4)
+    left = _us(b, 1, reps=30)
+    b.close()
+    assert left < 1.3 * one, (left, one)
+
+
+@pytest.mark.parametrize("prec,mrt", [(0, False), (0, True), (1, True), (2, False), (3, False)])
+def test_tuned_batch_steps_of_any_number_are_single_steps(L, prec, mrt):
+    ps, rhos = _sweep(L, prec, 30)
+    a, b = L.Batch(ps, rhos), L.Batch(ps, rhos)
+    a.set_tile(1, 16, 2, 1)
+    b.tune()
+    if mrt:                                       # after tuning: other kernels, other blocks
+        a.set_mrt((1.3, 1.1, 1.2))
+        b.set_mrt((1.3, 1.1, 1.2))
+    for graph, n in [(0, 1), (0, 2), (0, 3), (0, 7), (6, 25), (10, 33), (2, 5), (0, 5)]:
+        b.set_graph_steps(graph)
+        a.step(n)
+        b.step(n)
+        for i in range(0, len(ps), 7):
+            assert np.array_equal(a.get_populations(i), b.get_populations(i)), (graph, n, i)
+    for tile in [(2, 0, 1, 4), (4, 32, 1, 4), (2, 5, 1, 4), (4, 16, 2, 2), (1, 8, 2, 1)]:
+        b.set_tile(*tile)
+        for n in (1, 2, 3, 4, 6):
+            a.step(n)
+            b.step(n)
+        for i in range(0, len(ps), 7):
+            assert np.array_equal(a.get_populations(i), b.get_populations(i)), (tile, i)
+    a.close(); b.close()

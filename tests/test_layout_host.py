@@ -61,3 +61,47 @@ def test_deal_keeps_every_item_and_balances(tmp_path):
                     os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out
+
+
+HEADS = r"""
+#include <cstdio>
+#include "host_layout.hpp"
+using namespace lbm;
+int main() {
+  unsigned seed = 7;
+  auto rnd = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+  for (int trial = 0; trial < 300; ++trial) {
+    std::vector<int> nx(1 + rnd(40)), ny(nx.size());
+    for (size_t i = 0; i < nx.size(); ++i) nx[i] = 3 + rnd(600), ny[i] = 3 + rnd(80);
+    std::vector<Item> items;
+    layout::build_items((int)nx.size(), nx.data(), ny.data(), 1 + rnd(3), 4 + rnd(60), 1, items);
+    const int n = (int)items.size(), blocks = 1 + rnd(n < 300 ? n : 300);
+    if (trial % 2) layout::walk(items, blocks);
+    else layout::deal(items, blocks, rnd(22));
+    std::vector<Item> list = items;
+    layout::add_heads(list, blocks);
+    if ((int)list.size() != blocks + 1 + n) return 1;
+    int at = 0;  // every item once, in the order of the blocks
+    for (int b = 0; b < blocks; ++b) {
+      const int first = list[b].row0, end = list[b + 1].row0;
+      if (first != at || end < first || end > n) return 2;
+      for (int i = first; i < end; ++i, ++at) {
+        const Item &a = i == first ? list[b] : list[blocks + 1 + i], &q = items[i];
+        if (a.run != q.run || a.x0 != q.x0 || a.y0 != q.y0 || a.ncols != q.ncols || a.nrows != q.nrows) return 3;
+      }
+    }
+    if (at != n) return 4;
+  }
+  std::puts("ok");
+  return 0;
+}
+"""
+
+
+def test_first_items_of_blocks(tmp_path):
+    src, exe = tmp_path / "heads.cpp", tmp_path / "heads"
+    src.write_text(HEADS)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=address,undefined", "-I",
+                    os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out
