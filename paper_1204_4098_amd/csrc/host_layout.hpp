@@ -141,22 +141,26 @@ inline void deal(std::vector<Item>& items, int nblocks, int fill) {
 }
 
 // The same for short one-step chunks, which cost little to start but share their halo
-// rows: the blocks of XCD k (every eighth) walk the k-th contiguous eighth of the list side
-// by side, so that neighbouring chunks meet in that XCD's L2.  Sweep of 256 runs, us per
-// step, dealt by cost and walked: FP32 1 x 8 60 and 44, 2 x 8 51 and 43, 2 x 16 51 and 51, 4
-// x 32 56 and 62; FP64 1 x 8 117 and 110, 4 x 32 115 and 120 (waves x rows).  So chunks of
-// fewer than kWalkRows rows are walked.
-constexpr int kWalkRows = 16;
+// rows: the blocks of XCD k (every eighth) walk the k-th part of the list side by side, so
+// that neighbouring chunks meet in that XCD's L2.  Sweep of 256 runs, us per step, dealt by
+// cost and walked: FP32 2 x 16 34.5 and 32.4, 8 x 16 46.9 and 46.0, 4 x 32 46.9 and 53.8;
+// FP64 2 x 16 60.7 and 57.5, 4 x 32 70.1 and 75.5 (waves x rows).  So chunks of fewer than
+// kWalkRows rows are walked.
+constexpr int kWalkRows = 32;
 inline void walk(std::vector<Item>& items, int nblocks) {
-  const int n = (int)items.size(), xcds = std::min(8, nblocks);
+  const int n = (int)items.size();
   std::vector<Item> out;
   std::vector<int> first(nblocks);
   out.reserve(n);
+  // XCD k has (nblocks + 7 - k)/8 blocks; its part of the list is as large a share, so that
+  // no block has two items while another has none
+  int before[9] = {};
+  for (int k = 0; k < 8; ++k) before[k + 1] = before[k] + ((nblocks + 7 - k) >> 3);
   for (int b = 0; b < nblocks; ++b) {
-    const int xcd = b & 7, slots = (nblocks - xcd + 7) >> 3;
+    const int xcd = b & 7, slots = before[xcd + 1] - before[xcd];
     first[b] = (int)out.size();
-    const int hi = (int)((int64_t)n * (xcd + 1) / xcds);
-    for (int i = (int)((int64_t)n * xcd / xcds) + (b >> 3); i < hi; i += slots) out.push_back(items[i]);
+    const int lo = (int)((int64_t)n * before[xcd] / nblocks), hi = (int)((int64_t)n * before[xcd + 1] / nblocks);
+    for (int i = lo + (b >> 3); i < hi; i += slots) out.push_back(items[i]);
   }
   for (int b = 0; b < nblocks; ++b) out[b].row0 = first[b];
   items.swap(out);

@@ -111,8 +111,9 @@ __device__ __forceinline__ void balanced_pieces(const Item* __restrict__ items, 
 
 // List schedule of a batch: entry b of the list is block b's first item and its row0 that
 // item's place among the items behind the gridDim + 1 entries (layout::add_heads), so that a
-// block has its work after one load instead of two that depend on each other (1-3 us of a
-// launch).
+// block that has one item reads no second entry.  Sweep of 256 runs, FP16, us per step, with
+// two dependent loads (place, then item) and with one: 2 x 4 24.9 and 21.7, 8 x 16 33.7 and
+// 30.8; other types the same.
 template <class Piece>
 __device__ __forceinline__ void listed_pieces(const Item* __restrict__ list, Piece&& piece) {
   const Item* __restrict__ items = list + gridDim.x + 1;

@@ -1354,7 +1354,7 @@ int upload_list(lbm_batch* b, const WorkList& l, const std::vector<Item>& items)
 
 // The lists of a plan: every launch has one dealt to the blocks that its own kernel keeps
 // resident.  (With the tile's list and grid, one block per CU for four FP64 steps, single
-// steps of a sweep of 256 runs took 111 us in FP64 and 53 in FP32; so 66 and 27.)
+// steps of a sweep of 256 runs took 111 us in FP64 and 53 in FP32; so 58 and 26.)
 int batch_plan(lbm_batch* b, const Plan& p) {
   WorkList l[3] = {b->list[0], b->list[1], b->list[2]};
   std::vector<Item> items[3];

@@ -105,3 +105,34 @@ def test_first_items_of_blocks(tmp_path):
                     os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out
+
+
+WALK = r"""
+#include <cstdio>
+#include "host_layout.hpp"
+using namespace lbm;
+int main() {
+  for (int n = 1; n < 400; ++n)
+    for (int blocks : {n, (n + 1) / 2, (n + 2) / 3}) {
+      std::vector<Item> items(n);
+      for (int i = 0; i < n; ++i) items[i] = Item{i, 0, 0, 1, 8, 0};
+      layout::walk(items, blocks);
+      for (int b = 0; b < blocks; ++b) {
+        const int k = (b + 1 < blocks ? items[b + 1].row0 : n) - items[b].row0;
+        if (k > (n + blocks - 1) / blocks + (blocks < n)) return 1;   // one each where there are as many
+        if (blocks == n && k != 1) return 2;
+      }
+    }
+  std::puts("ok");
+  return 0;
+}
+"""
+
+
+def test_walk_gives_no_block_two_items_and_another_none(tmp_path):
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(WALK)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=address,undefined", "-I",
+                    os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out
