@@ -156,7 +156,7 @@ class Mlp:
             # steps of this call: to the end of the epoch, or to the next logged step
             m = min(nb - k, steps - s)
             if log_every:
-                m = min(m, -s % log_every + 1, steps - s)
+                m = int(min(m, -s % abs(log_every) + 1, steps - s))
             with torch.cuda.stream(self.stream):
                 if k == 0:
                     # each epoch's permutation is copied on the training stream, so

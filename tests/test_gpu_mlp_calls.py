@@ -41,3 +41,16 @@ def test_many_host_rows_cost_what_a_copy_and_a_launch_do(M):  # noqa: F811
     host = shortest(lambda: net.forward(X))
     net.close()
     assert host < 1.5 * copy, (host, copy)        # in pieces of 4,096 rows: 3 times
+
+
+@pytest.mark.parametrize("every", [-5, 5.0, -1])
+def test_train_logs_at_any_multiple(M, every):  # noqa: F811
+    # a step s is logged where s % log_every is 0, and the last one
+    X, T = _data(200, seed=4)
+    nrm, _ = _norm(M, X, T)
+    a, b = (M.Mlp(_params(2), nrm, max_batch=32) for _ in range(2))
+    want = a.train(X, T, steps=13, lr=1e-3, batch=32, log_every=abs(int(every)))
+    got = b.train(X, T, steps=13, lr=1e-3, batch=32, log_every=every)
+    assert got == want and [s for s, _ in want] == [s for s in range(13) if s % every == 0 or s == 12]
+    assert np.array_equal(a.params(), b.params())
+    a.close(); b.close()
