@@ -220,15 +220,17 @@ int lbm_load_state(lbm_ctx* c, const void* host_buf, size_t bytes);
  * recomputed), and with steps = 4 also 2 for k = 2; strips are spread evenly
  * over nx (FP64: strip edges on 64-byte boundaries).  waves = 1 with steps > 1
  * (rows 0, depth 1, any storage type and size) takes square patches, one node
- * per thread, for small lattices.  steps = 2: depth 1 or 2
+ * per thread, for small lattices (single steps run where they would be 2^32
+ * threads and more: above 5e8 nodes with steps = 4).  steps = 2: depth 1 or 2
  * (the same); steps = 3 and 4: depth 1; steps = 3: FP64 and
  * FP32-storage-FP64-collision lattices of at least 5 x 5 only (else
  * LBM_ENOTSUP or LBM_EINVAL; patches: all).  rows = 0 selects the balanced schedule, in which
  * a grid sized to the GPU's resident capacity splits all strip rows evenly;
  * rows in [0, 128].  A remainder of lbm_step(n) smaller than `steps` runs as
- * one or two launches of fewer steps.  lbm_tune times the candidates
+ * launches of fewer steps.  lbm_tune times the candidates
  * on the current state without advancing it and keeps the fastest per lattice
- * step; the choice is cached per (nx, ny, precision, collision operator) for
+ * step, and for a remainder the launches whose times add up to the least; the
+ * choice is cached per (nx, ny, precision, collision operator) for
  * the life of the process.  Every tile gives bitwise identical results. */
 int lbm_tune(lbm_ctx* c, int32_t* waves, int32_t* rows, int32_t* depth, int32_t* steps);
 int lbm_set_tile(lbm_ctx* c, int32_t waves, int32_t rows, int32_t depth, int32_t steps);

@@ -72,6 +72,20 @@ void decode(int nx, int ny, const S* b, double* f, Dec&& dec) {
 // Elements of one run in the batch pool (rounded up to 64).
 inline int64_t run_elems(int nx, int ny) { return (elems_of(nx, ny) + 63) / 64 * 64; }
 
+// A launch has fewer than 2^32 threads.
+inline bool launchable(int64_t blocks, int threads) { return blocks * threads < (int64_t)1 << 32; }
+// Blocks of a launch of nstrips strips in chunks of L rows (0 for the balanced schedule, L = 0).
+inline int64_t chunks(int nstrips, int ny, int L) { return L > 0 ? (int64_t)nstrips * ((ny + L - 1) / L) : 0; }
+// Square patches (k_patch) of ts steps: nodes along a side, of which 4 ts - 2 are halo, a
+// thread a node in whole waves, and blocks.
+constexpr int patch_side(int ts) { return ts == 4 ? 22 : 32; }
+constexpr int patch_threads(int ts) { return (patch_side(ts) * patch_side(ts) + 63) / 64 * 64; }
+inline int patches_across(int n, int ts) {
+  const int inner = patch_side(ts) - (4 * ts - 2);
+  return (n + inner - 1) / inner;
+}
+inline int64_t patches(int nx, int ny, int ts) { return (int64_t)patches_across(nx, ts) * patches_across(ny, ts); }
+
 // The most items any offered tile can produce for a run (1 wave, 4 rows).
 inline int max_items(int nx, int ny) { return ((nx + 63) / 64) * ((ny + 3) / 4); }
 

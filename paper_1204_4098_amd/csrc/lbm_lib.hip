@@ -234,9 +234,10 @@ hipError_t launch_step_t(const void* src, void* dst, const RunDev& d, int L,
                          unsigned long long* flag, hipStream_t st) {
   const int SW = 64 * NW;
   const int nstrips = (d.nx + SW - 1) / SW;
+  if (!layout::launchable(layout::chunks(nstrips, d.ny, L), SW)) L = 0;
   int grid;
   if (L > 0) {
-    grid = nstrips * ((d.ny + L - 1) / L);
+    grid = (int)layout::chunks(nstrips, d.ny, L);
   } else {  // balanced: resident capacity, at least 8 rows per block
     const int64_t rows = (int64_t)nstrips * d.ny;
     grid = resident_blocks((const void*)k_step<S, NW, PF, MRT>, SW);
@@ -279,9 +280,10 @@ hipError_t launch_pipe_t(const void* src, void* dst, const RunDev& d, int L,
                          unsigned long long* flag, hipStream_t st) {
   const int threads = 64 * NW * TS;
   const int nstrips = pipe_strips<S, NW, TS>(d.nx);
+  if (!layout::launchable(layout::chunks(nstrips, d.ny, L), threads)) L = 0;
   int grid;
   if (L > 0) {
-    grid = nstrips * ((d.ny + L - 1) / L);
+    grid = (int)layout::chunks(nstrips, d.ny, L);
   } else {
     // A second block on a CU halves the rows of a share but not its fill, so it pays only
     // while shares keep nearly a fill's rows (FP32, 128-column strips, us per step with one
@@ -306,9 +308,9 @@ bool has_step3(int prec) { return prec == LBM_PREC_F64 || prec == LBM_PREC_F32DE
 template <typename S, int RX, int RY, int TS, bool MRT>
 hipError_t launch_patch_t(const void* src, void* dst, const RunDev& d, const unsigned long long* base,
                           unsigned long long local, unsigned long long* flag, hipStream_t st) {
-  constexpr int H = 2 * TS - 1, TX = RX - 2 * H, TY = RY - 2 * H;
-  const int ntx = (d.nx + TX - 1) / TX;
-  const int64_t grid = (int64_t)ntx * ((d.ny + TY - 1) / TY);
+  static_assert(RX == RY && RX == layout::patch_side(TS), "layout's patch");
+  const int ntx = layout::patches_across(d.nx, TS);
+  const int64_t grid = layout::patches(d.nx, d.ny, TS);
   using E = typename Store<S>::E;
   hipLaunchKernelGGL((k_patch<S, RX, RY, TS, MRT>), dim3((unsigned)grid), dim3((RX * RY + 63) / 64 * 64), 0, st,
                      static_cast<const E*>(src), static_cast<E*>(dst), d, ntx, base, local, flag);
@@ -655,11 +657,15 @@ bool same_plan(const Plan& a, const Plan& b) {
   return same;
 }
 
-// The next launch of a lattice with `left` steps to go.  Rows of 2^32 bytes and more take
-// single steps: the pipe addresses a row with 32-bit byte offsets.
+// The next launch of a lattice with `left` steps to go.  Single steps take the place of
+// several where rows have 2^32 bytes and more (the pipe addresses a row with 32-bit byte
+// offsets) and of patches that are too many for one launch.
 Tile next_launch(const lbm_ctx* c, int64_t left) {
   const Tile& t = c->plan.next(left);
-  return t.ts > 1 && (int64_t)c->p.nx * c->esize >= (1ll << 32) ? with_steps(t, 1) : t;
+  if (t.ts == 1) return t;
+  const bool fits = t.nw == 1 ? layout::launchable(layout::patches(c->p.nx, c->p.ny, t.ts), layout::patch_threads(t.ts))
+                              : (int64_t)c->p.nx * c->esize < (1ll << 32);
+  return fits ? t : with_steps(t, 1);
 }
 
 // Launches that k steps take.

@@ -136,3 +136,32 @@ def test_walk_gives_no_block_two_items_and_another_none(tmp_path):
                     os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out
+
+
+LAUNCH = r"""
+#include <cstdio>
+#include "host_layout.hpp"
+using namespace lbm::layout;
+int main() {
+  // patches: 8, 26 and 22 nodes stored of 22, 32 and 32
+  if (patches(64, 32, 4) != 8 * 4 || patches(65, 33, 4) != 9 * 5 || patches(26, 27, 2) != 2 || patches(23, 22, 3) != 2) return 1;
+  if (patch_threads(4) != 512 || patch_threads(3) != 1024 || patch_threads(2) != 1024) return 2;
+  // 512 threads for 64 nodes: 2^29 nodes are too many, one row of patches less is not
+  if (launchable(patches(16384, 32768, 4), 512) || !launchable(patches(16384, 32760, 4), 512)) return 3;
+  if (launchable(patches(46340, 46340, 4), 512) || !launchable(patches(46340, 46340, 2), 1024)) return 4;
+  // 768 threads for a strip of three columns and one row
+  if (launchable(chunks(1, 5592406, 1), 768) || !launchable(chunks(1, 5592405, 1), 768)) return 5;
+  if (!launchable(chunks(1, 700000000, 0), 768) || chunks(3, 10, 4) != 9) return 6;
+  std::puts("ok");
+  return 0;
+}
+"""
+
+
+def test_launches_of_fewer_than_2_to_the_32_threads(tmp_path):
+    src, exe = tmp_path / "launch.cpp", tmp_path / "launch"
+    src.write_text(LAUNCH)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=address,undefined", "-I",
+                    os.path.join(ROOT, "paper_1204_4098_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out
