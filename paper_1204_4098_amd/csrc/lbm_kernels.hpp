@@ -1341,7 +1341,7 @@ __global__ __launch_bounds__(256) void k_batch_coex(const typename Store<S>::E* 
 __global__ void k_counter_add(unsigned long long* ctr, unsigned long long k) { *ctr += k; }
 __global__ void k_counter_set(unsigned long long* ctr, unsigned long long v) { *ctr = v; }
 
-// ---- diagnostics (rare; simple one-node-per-thread kernels) ---------------
+// ---- diagnostics -------------------------------------------------------------
 
 // Macroscopic fields: rho, v = u + F/(2 rho) (Table I, actual velocity) and p =
 // p_EOS(rho).  One pass: a block of T threads (at most 256) owns up to T - 2 columns (a

@@ -493,7 +493,7 @@ hipError_t launch_mass(int prec, const void* src, const RunDev& d, __int128* pi,
 }
 
 // Bytes of mass scratch: 128-bit and FP64 partials per work-group, then the
-// three result words.
+// four result words.
 constexpr size_t kMassScratch = kMassBlocks * (sizeof(__int128) + sizeof(double)) + 4 * sizeof(unsigned long long);
 
 }  // namespace
@@ -588,7 +588,7 @@ struct lbm_ctx {
   size_t ws_bytes;
   void* buf[2];
   int cur;
-  double* aux;  // 5 planes of nx*ny doubles: rho, vx, vy, p and one spare
+  double* aux;  // 4 planes of nx*ny doubles: rho, vx, vy, p
   __int128* part_i;   // mass scratch: partials and the result words
   double* part_d;
   unsigned long long* mass_out;
@@ -612,7 +612,7 @@ size_t raw_bytes_of(const lbm_params& p) {
 
 size_t ctx_layout(const lbm_params& p, size_t* pop, size_t* aux, size_t* parts, size_t* misc) {
   *pop = align_up(raw_bytes_of(p));
-  *aux = align_up(5 * (size_t)p.nx * p.ny * sizeof(double));
+  *aux = align_up(4 * (size_t)p.nx * p.ny * sizeof(double));
   *parts = align_up(kMassScratch);
   *misc = align_up(2 * sizeof(unsigned long long));
   return 2 * *pop + *aux + *parts + *misc;
@@ -966,7 +966,7 @@ int lbm_flat_profile(lbm_ctx* c, double* rho_bar, double* p_n) {
   return lbm_status(c, nullptr, nullptr);
 }
 
-// The three result words of the mass kernels into the caller's outputs.
+// The first three result words of the mass kernels into the caller's outputs.
 static void mass_words(const unsigned long long* w, int64_t* fixed, double* mass) {
   if (fixed) {
     fixed[0] = (int64_t)w[0];
@@ -1270,7 +1270,6 @@ struct lbm_batch {
   unsigned long long* flags;
   unsigned long long* ctr;
   double* aux;
-  size_t aux_nodes;
   hipStream_t st;
   int64_t step;
   Plan plan;
@@ -1288,7 +1287,6 @@ struct BatchLayout {
   size_t pool, runs, items, flags, aux, coex, total;
   int items_cap;
   size_t list_entries;  // of one of the three lists
-  size_t aux_nodes;
 };
 
 int64_t run_elems(const lbm_params& q) { return layout::run_elems(q.nx, q.ny); }
@@ -1309,8 +1307,7 @@ BatchLayout batch_layout(int n, const lbm_params* p) {
   L.list_entries = (size_t)cap + std::min(cap, kMaxBatchGrid) + 1;
   L.items = align_up(3 * L.list_entries * sizeof(Item));
   L.flags = align_up((n + 1) * sizeof(unsigned long long));
-  L.aux_nodes = maxn;
-  L.aux = align_up(5 * maxn * sizeof(double));
+  L.aux = align_up(4 * maxn * sizeof(double));
   L.coex = align_up(2 * (size_t)n * sizeof(double));
   L.total = 2 * L.pool + L.runs + L.items + L.flags + L.aux + L.coex;
   return L;
@@ -1485,7 +1482,6 @@ int lbm_batch_init(int32_t n, const lbm_params* p, const double* const* rho0, vo
   b->flags = reinterpret_cast<unsigned long long*>(b->ws + 2 * Lay.pool + Lay.runs + Lay.items);
   b->ctr = b->flags + n;
   b->aux = reinterpret_cast<double*>(b->ws + 2 * Lay.pool + Lay.runs + Lay.items + Lay.flags);
-  b->aux_nodes = Lay.aux_nodes;
   b->coex = reinterpret_cast<double*>(b->ws + 2 * Lay.pool + Lay.runs + Lay.items + Lay.flags + Lay.aux);
   b->st = static_cast<hipStream_t>(stream);
   std::vector<char> pool(Lay.pool, 0);

@@ -96,3 +96,14 @@ def test_pressure_matches_oracle(L):
     op = olbm.Params(nx=8, ny=8, eos=olbm.EOS_PR, a=2 / 49, b=2 / 21, R=1.0, omega=0.344, T=0.6 * Tc, Tc=Tc)
     for rho in (0.01, 1.0, 8.0):
         assert abs(L.lbm_pressure(p, rho) - olbm.p_eos(op, rho)) < 1e-13 * max(1, abs(olbm.p_eos(op, rho)))
+
+
+def test_workspaces_hold_what_is_used(L):
+    # two population buffers, four planes of fields and less than 64 KB besides; a batch has
+    # one run's planes and, for three work lists, less than 1 % of the populations in FP64
+    n = 1024 * 512
+    for prec, es in ((0, 8), (1, 4), (2, 2), (3, 4)):
+        p = L.params(1024, 512, T=0.08, precision=prec)
+        assert 0 <= L.lbm_workspace_bytes(p) - 2 * 9 * es * n - 4 * 8 * n < 1 << 16
+        batch = L.lbm_batch_workspace_bytes([p] * 8)
+        assert 0 <= batch - 8 * 2 * 9 * es * n - 4 * 8 * n < 0.01 * 8 * 2 * 72 * n
