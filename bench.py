@@ -213,7 +213,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                      "traffic": traffic_for(args.workload, args.precision, res["tile"]),
-                     "kernel": "k_step" if ts == 1 else "k_pipe", "steps_per_launch": ts,
+                     "kernel": kernel_name(res["tile"]), "steps_per_launch": ts,
                      "bytes_per_lup": bpl / ts, "kernel_avg_us": round(launch_ms * 1e3, 2),
                      # MLUPS x the single-step 144 B/LUP over the peak (exceeds 1 only
                      # when steps are fused; not a bandwidth)
@@ -375,6 +375,11 @@ def copy_rate(torch, mib=1024, reps=5):
     ms = e0.elapsed_time(e1)
     del a, b
     return 2 * (mib << 20) * reps / (ms * 1e-3) / 1e9
+
+
+def kernel_name(tile):
+    """Step kernel that a tile (waves, rows, depth, steps) runs."""
+    return "k_step" if tile[3] == 1 else "k_patch" if tile[0] == 1 else "k_pipe"
 
 
 def traffic_for(workload, precision, tile):

@@ -21,3 +21,9 @@ def test_cpu_pool_baseline_counts_updates_done():
     assert 1 <= out["cores"] <= 16
     assert out["value"] > 0
     assert "2 of the 256 batched flat-interface runs" in out["sample"]
+
+
+def test_kernel_of_a_tile():
+    assert bench.kernel_name((16, 0, 1, 1)) == "k_step" and bench.kernel_name((1, 4, 1, 1)) == "k_step"
+    assert bench.kernel_name((4, 0, 1, 4)) == bench.kernel_name((2, 16, 1, 2)) == "k_pipe"
+    assert bench.kernel_name((1, 0, 1, 4)) == "k_patch"
