@@ -1117,18 +1117,22 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
   // Tuning is most of the time it takes to set a lattice up, so of each family only the
   // likeliest are timed.  Patches win below 2^16 nodes by 1.8 times and more and lose
   // above 2^18.  Single steps win on narrow lattices only, but are what a program takes that
-  // reads its lattice after every step: below 2^21 nodes strips of 1, 4 and 16 waves in chunks
-  // of about nodes / 2^17 rows (the fastest of all had 1 row below 2^17 nodes, 2 to 4 up to
-  // 2^20), above that the balanced ones.
+  // reads its lattice after every step.  Of all their tiles the fastest had chunks of one or
+  // two rows up to 2^18 nodes (depth 2: 64 x 32 4.0 us, depth 1 4.6), two to four up to 2^20,
+  // with one wave on the smallest and on narrow lattices and up to 16 on others (1024 x 1024
+  // FP16 13.7 us with 16, 13.9 with 4), and the balanced schedule from 2^21 on.
   const bool tiny = nodes < (1 << 16), large = nodes >= (1 << 21);
   if (nodes <= (1 << 18))
     for (int ts : {2, 3, 4}) cand.push_back(Tile{1, 0, 1, ts});
-  if (!large) {
+  if (tiny) {
+    for (int pf : {1, 2})
+      for (int L : {1, 2}) cand.push_back(Tile{1, L, pf, 1});
+  } else if (!large) {
     int rows = 1;
-    while (rows < 16 && 2 * rows <= (nodes >> 17)) rows *= 2;
-    for (int nw : {1, 4, 16})
+    while (2 * rows <= (nodes >> 18)) rows *= 2;
+    for (int nw : {1, 2, 4, 8, 16})
       for (int L : {rows, 2 * rows})
-        if (nw == 1 || 32 * nw < c->p.nx) cand.push_back(Tile{nw, L, 1, 1});
+        if (nw == 1 || 32 * nw < c->p.nx) cand.push_back(Tile{nw, std::min(L, 2 * c->p.ny), rows == 1 ? 2 : 1, 1});
   } else {
     for (const Tile& t : {Tile{1, 0, 2, 1}, Tile{1, 64, 2, 1}, Tile{4, 8, 2, 1}, Tile{16, 0, 1, 1}})
       if (t.L <= 2 * c->p.ny) cand.push_back(t);
