@@ -372,7 +372,7 @@ __device__ __forceinline__ void force3x3(const double* rs, const double* rc, con
 // 1/rho, against 85 of collide_pairs, which evaluates (e.u)^2 and (e.v)(e.F) for each
 // pair.  The density enters each P last, in one fma of its own: error of a node's update over
 // w rho in FP64, mean and largest of 400,000 against quadruple precision: 0.98e-16 and
-// 8.6e-16, collide_pairs 1.05e-16 and 1.05e-15 (FP32 1.67e-8, collide_pairs 1.79e-8).
+// 8.6e-16, collide_pairs 1.05e-16 and 1.05e-15 (FP32 1.65e-8, collide_pairs 1.79e-8).
 template <typename R>
 __device__ __forceinline__ void relax_pair(R& sa, R& sb, R P, R Q, R om1) {
 #pragma clang fp contract(off)
@@ -818,16 +818,17 @@ __global__ __launch_bounds__(64 * NW) void k_step(const typename Store<S>::E* __
 // no lane, row or step in range reads.  All steps use the arithmetic of single
 // launches in the same order: bitwise equal.
 //
-// Why one group per step: a wave holds one step's rows only (149 VGPRs in FP64, 118
+// Why one group per step: a wave holds one step's rows only (145 VGPRs in FP64, 125
 // with FP16 storage, against 254 for one wave doing three steps), so 3-4 waves per
 // SIMD hide latency instead of 2, four steps fit where three did, and rows rotate by
-// the names of unrolled registers and LDS slots instead of moves (121 FP64 and 6
-// other vector instructions per row and step instead of 123 and 46).  4096 x 4096,
-// us per step, one wave for all steps -> one group per step: FP64 195 -> 133 (four
-// steps, 5.0 TB/s: the rate a plain copy gets), FP32 179 -> 115, FP32 with FP64
-// collide 171 -> 116, FP16 124 -> 79 (bound by vector issue); 1024 x 1024 FP64 28 ->
-// 17.  A version with two barriers per row (collision after the exchange of the same
-// row) took 156 in FP64 and 123 in FP16.
+// the names of unrolled registers and LDS slots instead of moves.  us per step, one wave
+// for two or three steps -> one group per step, four steps: FP64 4096 x 4096 231 -> 143
+// (4.8 TB/s counted; a plain copy gets 5.1), FP16 123 -> 93 (bound by vector issue), FP32
+// 3000 x 2501 82 -> 59, FP32 with FP64 collide 1500 x 1001 27 -> 17, FP64 1024 x 1024 29
+// -> 14.  A version with two barriers per row (collision after the exchange of the same
+// row) took 1.2 times as long in FP64 and 1.55 times in FP16.  The figures that follow
+// compare schedules and tiles with one another; the node arithmetic they were taken with was
+// 4 to 10 % faster and less exact than this one.
 
 // Barrier that orders LDS only: global loads and stores in flight stay in flight.
 __device__ __forceinline__ void lds_barrier() {
