@@ -1121,30 +1121,37 @@ int lbm_tune(lbm_ctx* c, int32_t* nw_out, int32_t* L_out, int32_t* depth_out, in
   // two rows up to 2^18 nodes (depth 2: 64 x 32 4.0 us, depth 1 4.6), two to four up to 2^20,
   // with one wave on the smallest and on narrow lattices and up to 16 on others (1024 x 1024
   // FP16 13.7 us with 16, 13.9 with 4), and the balanced schedule from 2^21 on.
+  // Strips twice as wide as the lattice and more are left out, and pipes that use less than a
+  // quarter of their lanes.
   const bool tiny = nodes < (1 << 16), large = nodes >= (1 << 21);
+  auto one = [&](int nw, int L, int pf) {
+    if (nw == 1 || 32 * nw < c->p.nx) cand.push_back(Tile{nw, std::min(L, 2 * c->p.ny), pf, 1});
+  };
   if (nodes <= (1 << 18))
     for (int ts : {2, 3, 4}) cand.push_back(Tile{1, 0, 1, ts});
   if (tiny) {
     for (int pf : {1, 2})
-      for (int L : {1, 2}) cand.push_back(Tile{1, L, pf, 1});
+      for (int L : {1, 2}) one(1, L, pf);
   } else if (!large) {
     int rows = 1;
     while (2 * rows <= (nodes >> 18)) rows *= 2;
     for (int nw : {1, 2, 4, 8, 16})
-      for (int L : {rows, 2 * rows})
-        if (nw == 1 || 32 * nw < c->p.nx) cand.push_back(Tile{nw, std::min(L, 2 * c->p.ny), rows == 1 ? 2 : 1, 1});
+      for (int L : {rows, 2 * rows}) one(nw, L, rows == 1 ? 2 : 1);
   } else {
-    for (const Tile& t : {Tile{1, 0, 2, 1}, Tile{1, 64, 2, 1}, Tile{4, 8, 2, 1}, Tile{16, 0, 1, 1}})
-      if (t.L <= 2 * c->p.ny) cand.push_back(t);
+    one(1, 0, 2);
+    one(1, 64, 2);
+    one(4, 8, 2);
+    one(16, 0, 1);
   }
-  if (!tiny) cand.push_back(Tile{4, 0, 2, 1});
+  if (!tiny) one(4, 0, 2);
+  const bool narrow = c->p.nx >= 32, wide = c->p.nx > 114;  // 114: one narrow strip of four steps
   if ((int64_t)c->p.nx * c->esize < (1ll << 32))
     for (int L : {0, 16, 32, 64, 128})
       if (L <= 2 * c->p.ny && (!tiny || L == 16)) {
-        cand.push_back(Tile{4, L, 1, 4});
-        cand.push_back(Tile{2, L, 1, 4});
-        if (L == 0 || L == 32) cand.push_back(Tile{4, L, 1, 2});
-        if (L == 0 && has_step3(c->p.precision) && std::min(c->p.nx, c->p.ny) >= 5) cand.push_back(Tile{4, 0, 1, 3});
+        if (wide) cand.push_back(Tile{4, L, 1, 4});
+        if (narrow) cand.push_back(Tile{2, L, 1, 4});
+        if (wide && (L == 0 || L == 32)) cand.push_back(Tile{4, L, 1, 2});
+        if (wide && L == 0 && has_step3(c->p.precision) && c->p.ny >= 5) cand.push_back(Tile{4, 0, 1, 3});
       }
   const int pst = pick_plan(
       c->p.precision, false, cand,
@@ -1353,9 +1360,9 @@ int make_list(const lbm_batch* b, const Tile& t, WorkList& l, std::vector<Item>&
   return LBM_OK;
 }
 
+// Enqueues the upload of a list; items must live until the stream has been waited for.
 int upload_list(lbm_batch* b, const WorkList& l, const std::vector<Item>& items) {
   HIPCHK(hipMemcpyAsync(l.d, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, b->st));
-  HIPCHK(hipStreamSynchronize(b->st));
   return LBM_OK;
 }
 
@@ -1372,6 +1379,7 @@ int batch_plan(lbm_batch* b, const Plan& p) {
   }
   for (int i = 0; i < 3 && st == LBM_OK; ++i)
     if (!items[i].empty()) st = upload_list(b, b->list[i] = l[i], items[i]);
+  if (hipStreamSynchronize(b->st) != hipSuccess && st == LBM_OK) st = LBM_EHIP;
   if (st == LBM_OK) b->plan = p;
   return st;
 }
@@ -1652,6 +1660,7 @@ int lbm_batch_tune(lbm_batch* b, int32_t* nw_out, int32_t* L_out, int32_t* depth
         ist = make_list(b, t, b->list[0], items);
         if (ist == LBM_ENOSPACE) return 1e30f;  // too many items for the work list: skipped
         if (ist == LBM_OK) ist = upload_list(b, b->list[0], items);
+        if (hipStreamSynchronize(b->st) != hipSuccess && ist == LBM_OK) ist = LBM_EHIP;
         if (ist != LBM_OK) return -1.f;
         const float ms = time_launches(
             b->st,

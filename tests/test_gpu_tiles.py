@@ -136,3 +136,16 @@ def test_tuned_batch_steps_of_any_number_are_single_steps(L, prec, mrt):
         for i in range(0, len(ps), 7):
             assert np.array_equal(a.get_populations(i), b.get_populations(i)), (tile, i)
     a.close(); b.close()
+
+
+def test_tuning_a_narrow_lattice_times_no_wide_tiles(L):
+    # 3 columns: strips of 192 lanes took 0.3 s of the tuner's time and more, strips of one
+    # wave take 20 ms
+    import time
+    gp, _ = pair(L, 3, 200000, t=0.85, tau=0.8, scheme=2, sigma=0.1)
+    lat = L.Lattice(gp, np.full((200000, 3), 0.12))
+    t0 = time.perf_counter()
+    tile = lat.tune()
+    took = time.perf_counter() - t0
+    lat.close()
+    assert tile[0] == 1 and took < 0.15, (tile, took)
