@@ -314,7 +314,7 @@ __device__ __forceinline__ double psi2_of(double rho, const RunDev& d) {
 // Before its rounding that is within 2^-50 ulp of the root; the 365 arguments of two binades
 // whose root lies within 2^-46 ulp of a midpoint of two doubles were enumerated and all give
 // the result of sqrt() (as do 2^30 random ones).  No scaling and no special cases: 9
-// operations where sqrt() takes 20.  Not a number for x = 0, infinite or negative: a node
+// operations where sqrt() takes 17.  Not a number for x = 0, infinite or negative: a node
 // with such a psi^2 has diverged.
 __device__ __forceinline__ double root_of(double x, double& r) {
 #pragma clang fp contract(off)
